@@ -539,8 +539,8 @@ rise_status launch_stencil2d(const StencilArgs& a, const rise_stencil_schedule& 
 //              dIn[p] = sum_d w[d] sum { dOut[o] : clamp(o + d - r) = p },
 //              evaluated separately per dimension.
 // dW:  dW[dy][dx] = sum over outputs (y, x) of dOut[y][x] * window(y, x)[dy][dx],
-//      a reduction over all pixels: per-wave partial sums (streaming the input
-//      like the forward kernel) then one deterministic reduction.
+//      a reduction over all pixels: one partial sum per tap and workgroup, then
+//      one deterministic reduction.
 // ===========================================================================
 namespace {
 
@@ -599,101 +599,241 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// Per-wave partial sums of dW over one 256-column strip segment of L output rows.
-template <int K, bool VEC, int L>
-__global__ __launch_bounds__(kThreads) void stencil_dw_stream(
-    float* __restrict__ partial, const float* __restrict__ dout, int64_t ld_dout,
-    const float* __restrict__ in, int64_t ld_in, int H, int W, int zero_pad, int segs,
-    int tasks) {
+// Both gradients of a square K x K window (1, 3, 5, 7) from one pass over the
+// image: a workgroup owns TY output rows x 256 columns, stages the halo tile of
+// dOut in LDS (zero outside the image), reduces dIn from it with the rotated
+// window, keeps the tile's own dOut values in registers, stages the halo tile of
+// the input (pad2D applied) in the same LDS and accumulates the K*K sums of dW.
+// Both tiles' loads are issued at the start, so the input is in flight while
+// dIn is computed, and dOut is read once for both gradients.
+//
+// Bound: HBM for large images with small windows (8 B per pixel read, 4 B
+// written), the 2 K*K FMAs per pixel for 7 x 7, latency for small images, where
+// the number of waves decides: 1531 x 2047 has 768 tiles of 16 rows.  Both
+// gradients, clamp padding, with the final reduction of dW, back to back:
+//   1531 x 2047: 3 x 3 40.1 -> 14.3 us, 5 x 5 56.9 -> 18.1, 7 x 7 83.3 -> 23.2
+//   4096 x 4096: 3 x 3 54.5 -> 44.7 us, 5 x 5 70.4 -> 55.5, 7 x 7 134 -> 79
+// (before: a rotation kernel, a zero-padded stencil and a border kernel whose
+// threads walked K*K taps of dynamic extent for dIn; one wave per 256 columns x
+// 32 rows for dW, 384 waves at 1531 x 2047, value by value on rows that are not
+// 16-byte aligned).  One kernel per gradient instead takes 25.7 and 82 us for
+// 7 x 7.
+//
+// Clamp padding (pad2D's adjoint): a first or last row or column also collects
+// the taps that clamping mapped onto it.  All the dOut values it needs lie in its own
+// window, so the tile re-reduces those pixels from LDS with summed weights:
+// along a dimension, window position j of the first pixel takes the rotated
+// weights j .. K-1 (positions below R are outside the image and hold zeros), of
+// the last pixel 0 .. j, and an image one pixel wide takes all at j = R.
+//
+// dW: every lane sums its 4 columns x TY/4 rows per tap; the 64 lanes' sums of
+// up to 64 taps are combined by halving (63 exchanges in all instead of 6 per
+// tap) and the four waves in order, one value per tap and workgroup, laid out
+// tap-major for the final reduction.  Fixed orders throughout.
+template <int K>
+struct AdjWeights {
+  // [row kind: interior, first, last, both][window row][window column], rotated
+  float w[4][K][K];
+};
+
+// Window row `row` (weights wy) of a pixel of the first and / or last column.
+template <int K>
+__device__ __forceinline__ float adjoint_edge_row(const float* row, const float (&wy)[K],
+                                                  bool first, bool last) {
   constexpr int R = (K - 1) / 2;
-  constexpr int P = K >= 4 ? K : K * ((4 + K - 1) / K);
-  constexpr int NIN = L + 2 * R;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int task = xcd_contiguous(blockIdx.x, gridDim.x) * 4 + wave;
-  if (task >= tasks) return;
-  const int strip = task / segs, seg = task - strip * segs;
-  const int x0 = strip * TX, x = x0 + 4 * lane;
-  const int ys = seg * L;
-  const int edge_x = lane == 0 ? x0 - 4 : x0 + TX;
-  const bool edge_lane = lane == 0 || lane == 63;
+  float acc = 0.f, up = 0.f, down = 0.f;  // weights 0 .. i and K - 1 .. K - 1 - i
+#pragma unroll
+  for (int i = 0; i <= R; i++) {
+    up += wy[i];
+    if (i < R) down += wy[K - 1 - i];
+    if (!first)
+      acc = fmaf(row[i], up, acc);
+    else if (i < R && !last)
+      acc = fmaf(row[K - 1 - i], down, acc);
+  }
+  // the pixel's own column: the first pixel takes weights R .. K - 1, an image
+  // one pixel wide all of them
+  if (first) acc = fmaf(row[R], last ? up + down : wy[R] + down, acc);
+  return acc;
+}
 
-  f32x4 raw[P], edge[P], grad[P];
-  float win[K][12];
-  float acc[K][K];
+// Sums of v[0 .. N-1] over the 64 lanes (N a power of two up to 64): lane l ends
+// with the sum of v[l % N] in v[0].  Each exchange halves the values a lane
+// holds; the lanes that then hold the same value add up at the end.
+template <int N, int OFF>
+__device__ __forceinline__ void halve_sums(float (&v)[N]) {
+  if constexpr (OFF >= 1) {
+    const bool up = threadIdx.x & OFF;
 #pragma unroll
-  for (int p = 0; p < P; p++) edge[p] = grad[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < OFF; i++) {
+      const float keep = up ? v[i + OFF] : v[i], send = up ? v[i] : v[i + OFF];
+      v[i] = keep + __shfl_xor(send, OFF);
+    }
+    halve_sums<N, OFF / 2>(v);
+  }
+}
+template <int N>
+__device__ __forceinline__ float wave_sums(float (&v)[N]) {
+  halve_sums<N, N / 2>(v);
 #pragma unroll
-  for (int dy = 0; dy < K; dy++)
-#pragma unroll
-    for (int dx = 0; dx < K; dx++) acc[dy][dx] = 0.f;
+  for (int off = N; off < 64; off *= 2) v[0] += __shfl_xor(v[0], off);
+  return v[0];
+}
 
-  // dOut chunk of output row o (zero outside the image: those outputs do not exist)
-  auto fetch_grad = [&](int o) -> f32x4 {
-    const int y = ys + o;
-    if (o < 0 || o >= L || y >= H) return f32x4{0.f, 0.f, 0.f, 0.f};
-    const float* rp = dout + (int64_t)y * ld_dout;
-    if (VEC && x + 3 < W) return *reinterpret_cast<const f32x4*>(rp + x);
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (x + 0 < W) v.x = rp[x + 0];
-    if (x + 1 < W) v.y = rp[x + 1];
-    if (x + 2 < W) v.z = rp[x + 2];
-    if (x + 3 < W) v.w = rp[x + 3];
-    return v;
-  };
-  auto fetch = [&](int t, int slot) {
-    const int gy = ys - R + t;
-    raw[slot] = load_chunk4<VEC>(in, ld_in, H, W, gy, x, zero_pad);
-    if (edge_lane) edge[slot] = load_chunk4<VEC>(in, ld_in, H, W, gy, edge_x, zero_pad);
-    grad[slot] = fetch_grad(t - 2 * R);  // the output row this input row completes
-  };
-
+template <int K, bool VEC, int TY, bool DIN, bool DW>
+__global__ __launch_bounds__(kThreads, DIN && DW && K > 3 ? 3 : 4) void stencil_bwd_tiled(
+    float* __restrict__ din, int64_t ld_din, float* __restrict__ partial,
+    const float* __restrict__ dout, int64_t ld_dout, const float* __restrict__ in, int64_t ld_in,
+    int H, int W, const float* __restrict__ w, int zero_pad, int tiles_x, int ntiles) {
+  using Cfg = tiles::StencilCfg<K, TY>;
+  constexpr int R = Cfg::R, RW = TY / 4, LC = tiles::kLChunks, KK = K * K;
+  constexpr int NT = KK > 32 ? 64 : KK > 16 ? 32 : KK > 1 ? 16 : 1;  // taps, a power of two
+  __shared__ f32x4 lds[Cfg::LDS_CHUNKS];
+  __shared__ AdjWeights<K> adj;
+  __shared__ float edge[2][TY];  // dIn of the first and last column
+  __shared__ float red[4][64];
+  static_assert(TY == 16 && K <= 8, "eight lanes per pixel of two columns");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float total = 0.f;  // dW of tap `tid` over this workgroup's tiles
+  for (int t = xcd_contiguous(blockIdx.x, gridDim.x); t < ntiles; t += gridDim.x) {
+    const int y0 = (t / tiles_x) * TY, x0 = (t % tiles_x) * TX;
+    tiles::StencilRegs<K, TY> gv, xv;
+    f32x4 g[RW];  // this lane's dOut values (zero outside the image)
+    bool inside = false;
+    if (DIN) {
+      inside = tiles::stencil_load_tile<K, VEC, TY>(gv, dout, ld_dout, H, W, 1, y0, x0);
+    } else {  // no window of dOut is needed
+      const int x = x0 + 4 * lane;
 #pragma unroll
-  for (int p = 0; p < P; p++)
-    if (p < NIN) fetch(p, p);
-
-  for (int t0 = 0; t0 < NIN; t0 += P) {
-#pragma unroll
-    for (int p = 0; p < P; p++) {
-      const int t = t0 + p;
-      if (t >= NIN) break;
-      float* row = win[p % K];
-      const f32x4 c = raw[p];
-      const f32x4 e = edge[p];
-      const f32x4 g = grad[p];
-      row[4] = c.x; row[5] = c.y; row[6] = c.z; row[7] = c.w;
-      if (R > 0) {
-        float l0 = wave_from_left(c.x), l1 = wave_from_left(c.y);
-        float l2 = wave_from_left(c.z), l3 = wave_from_left(c.w);
-        float r0 = wave_from_right(c.x), r1 = wave_from_right(c.y);
-        float r2 = wave_from_right(c.z), r3 = wave_from_right(c.w);
-        if (lane == 0) { l0 = e.x; l1 = e.y; l2 = e.z; l3 = e.w; }
-        if (lane == 63) { r0 = e.x; r1 = e.y; r2 = e.z; r3 = e.w; }
-        row[0] = l0; row[1] = l1; row[2] = l2; row[3] = l3;
-        row[8] = r0; row[9] = r1; row[10] = r2; row[11] = r3;
+      for (int o = 0; o < RW; o++) {
+        const float* row = dout + (int64_t)min(y0 + wave * RW + o, H - 1) * ld_dout;
+        if (W >= 4)
+          g[o] = *reinterpret_cast<const tiles::f32x4u*>(row + min(x, W - 4));
+        else
+          g[o] = f32x4{row[0], row[min(1, W - 1)], row[W - 1], 0.f};
       }
-      if (t + P < NIN) fetch(t + P, p);
-      if (t >= 2 * R) {
-        const float gq[4] = {g.x, g.y, g.z, g.w};
+    }
+    if (DW) inside = tiles::stencil_load_tile<K, VEC, TY>(xv, in, ld_in, H, W, zero_pad, y0, x0);
+    const bool border = DIN && R > 0 && !zero_pad &&
+                        (y0 == 0 || x0 == 0 || y0 + TY >= H || x0 + TX >= W);
+    float wsum = 0.f;  // entry `tid` of the summed weights
+    if (border && tid < 4 * KK) {
+      const int kind = tid / KK, j = tid / K % K, i = tid % K;
+      const bool any = kind == 0 || (kind == 1 && j >= R) || (kind == 2 && j <= R) || j == R;
 #pragma unroll
-        for (int dy = 0; dy < K; dy++)
+      for (int q = 0; q < K; q++) {  // all loads at once, with the tiles' in flight
+        const float v = w[KK - 1 - (q * K + i)];
+        const bool take = kind == 0 ? q == j : kind == 1 ? q >= j : kind == 2 ? q <= j : true;
+        wsum += any && take ? v : 0.f;
+      }
+    }
+    __syncthreads();  // the previous tile's LDS values are no longer read
+    if (DIN) tiles::stencil_put_tile<K, TY>(gv, lds, H, W, 1, y0, x0, inside);
+    if (border && tid < 4 * KK) (&adj.w[0][0][0])[tid] = wsum;
+    if (DIN) {
+      __syncthreads();
+      float wt[K][K];
 #pragma unroll
-          for (int dx = 0; dx < K; dx++) {
-            float a = acc[dy][dx];
+      for (int e = 0; e < KK; e++) wt[e / K][e % K] = w[KK - 1 - e];
+      float res[RW][4];
+      tiles::stencil_compute<K, TY, false, true>(res, wt, lds);
+      if (border) {
+        const float* tile = reinterpret_cast<const float*>(lds);
 #pragma unroll
-            for (int q = 0; q < 4; q++)
-              a = fmaf(gq[q], win[(p + K - 2 * R + dy) % K][4 + q + dx - R], a);
-            acc[dy][dx] = a;
+        for (int o = 0; o < RW; o++) {  // a first or last row: the whole row again
+          const int y = y0 + wave * RW + o;
+          const int kind = (y == 0 ? 1 : 0) + (y == H - 1 ? 2 : 0);
+          if (!kind) continue;  // wave-uniform
+#pragma unroll
+          for (int q = 0; q < 4; q++) res[o][q] = 0.f;
+#pragma unroll 1
+          for (int j = 0; j < K; j++) {  // rolled: these registers are the kernel's most
+            float win[12];
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+              const f32x4 v = lds[(wave * RW + o + j) * LC + lane + c];
+              win[4 * c] = v.x; win[4 * c + 1] = v.y; win[4 * c + 2] = v.z; win[4 * c + 3] = v.w;
+            }
+#pragma unroll
+            for (int i = 0; i < K; i++) {
+              const float wv = adj.w[kind][j][i];
+#pragma unroll
+              for (int q = 0; q < 4; q++) res[o][q] = fmaf(win[4 + q + i - R], wv, res[o][q]);
+            }
           }
+        }
+        if (x0 == 0 || x0 + TX >= W) {
+          // first or last column: eight lanes a pixel, one window row each
+          const int side = tid >> 7, r = (tid >> 3) & (TY - 1), j = tid & 7;
+          const int x = side ? W - 1 : 0, y = y0 + r;
+          const int kind = (y == 0 ? 1 : 0) + (y == H - 1 ? 2 : 0);
+          const bool mine = y < H && x >= x0 && x < x0 + TX && !(side && W == 1);
+          float v = 0.f;
+          if (mine && j < K)
+            v = adjoint_edge_row<K>(tile + (r + j) * 4 * LC + tiles::kHalo - R + x - x0,
+                                    adj.w[kind][j], x == 0, x == W - 1);
+#pragma unroll
+          for (int off = 1; off < 8; off *= 2) v += __shfl_xor(v, off);
+          if (j == 0) edge[side][r] = v;
+          __syncthreads();
+          const int xl = x0 + 4 * lane;
+#pragma unroll
+          for (int o = 0; o < RW; o++)
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+              if (xl + q == W - 1) res[o][q] = edge[1][wave * RW + o];
+              if (xl + q == 0) res[o][q] = edge[0][wave * RW + o];
+            }
+        }
       }
+      tiles::stencil_store<VEC, TY, true>(din, ld_din, H, W, res, y0, x0);
+    }
+    if (DW) {
+      if (DIN) {
+#pragma unroll
+        for (int o = 0; o < RW; o++) g[o] = lds[(wave * RW + o + R) * LC + lane + 1];
+        __syncthreads();
+      } else {
+#pragma unroll
+        for (int o = 0; o < RW; o++) {
+          const int x = x0 + 4 * lane;
+          if (W >= 4) g[o] = tiles::chunk_any(g[o], x, W, 1);
+#pragma unroll
+          for (int q = 0; q < 4; q++)
+            if (y0 + wave * RW + o >= H || x + q >= W) g[o][q] = 0.f;
+        }
+      }
+      tiles::stencil_put_tile<K, TY>(xv, lds, H, W, zero_pad, y0, x0, inside);
+      __syncthreads();
+      float acc[NT];
+#pragma unroll
+      for (int e = 0; e < NT; e++) acc[e] = 0.f;
+      int base = wave * RW * LC + lane;
+#pragma unroll
+      for (int j = 0; j < RW + 2 * R; j++) {
+        float win[12];
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+          const f32x4 v = R > 0 || c == 1 ? lds[base + j * LC + c] : f32x4{0.f, 0.f, 0.f, 0.f};
+          win[4 * c] = v.x; win[4 * c + 1] = v.y; win[4 * c + 2] = v.z; win[4 * c + 3] = v.w;
+        }
+#pragma unroll
+        for (int o = 0; o < RW; o++) {
+          const int dy = j - o;
+          if (dy < 0 || dy >= K) continue;
+#pragma unroll
+          for (int q = 0; q < 4; q++)
+#pragma unroll
+            for (int dx = 0; dx < K; dx++)
+              acc[dy * K + dx] = fmaf(g[o][q], win[4 + q + dx - R], acc[dy * K + dx]);
+        }
+      }
+      red[wave][lane] = wave_sums<NT>(acc);
+      __syncthreads();
+      if (tid < KK) total += (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
     }
   }
-#pragma unroll
-  for (int dy = 0; dy < K; dy++)
-#pragma unroll
-    for (int dx = 0; dx < K; dx++) {
-      float v = wave_sum(acc[dy][dx]);
-      if (lane == 0) partial[(int64_t)task * K * K + dy * K + dx] = v;
-    }
+  if (DW && tid < KK) partial[(int64_t)tid * gridDim.x + blockIdx.x] = total;
 }
 
 // Any odd kh x kw: block (chunk, tap) sums dOut * window over a chunk of pixels.
@@ -722,17 +862,17 @@ __global__ __launch_bounds__(kThreads) void stencil_dw_direct(
   if (threadIdx.x == 0) {
     float s = 0.f;
     for (int q = 0; q < kThreads / 64; q++) s += red[q];
-    partial[(int64_t)blockIdx.x * gridDim.y + tap] = s;
+    partial[(int64_t)tap * gridDim.x + blockIdx.x] = s;
   }
 }
 
-// dW[t] = sum over parts of partial[part][t] (one block per tap, fixed order).
+// dW[t] = sum over parts of partial[t][part] (one block per tap, fixed order).
 __global__ __launch_bounds__(kThreads) void reduce_partials(float* __restrict__ dW,
                                                             const float* __restrict__ partial,
-                                                            int parts, int taps) {
+                                                            int parts) {
   const int t = blockIdx.x;
   float acc = 0.f;
-  for (int p = threadIdx.x; p < parts; p += kThreads) acc += partial[(int64_t)p * taps + t];
+  for (int p = threadIdx.x; p < parts; p += kThreads) acc += partial[(int64_t)t * parts + p];
   __shared__ float red[kThreads / 64];
   acc = wave_sum(acc);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
@@ -744,27 +884,46 @@ __global__ __launch_bounds__(kThreads) void reduce_partials(float* __restrict__ 
   }
 }
 
-constexpr int kDwRows = 32;       // output rows per wave in the streaming dW kernel
+constexpr int kBwdRows = 16;      // output rows per tile of the fused backward kernel
+constexpr int kBwdGrid = 4096;    // most workgroups of it (and dW partials per tap)
 constexpr int kDwChunk = 65536;   // pixels per block in the direct dW kernel
 
-bool dw_streaming(int kh, int kw) { return kh == kw && (kh == 1 || kh == 3 || kh == 5 || kh == 7); }
+// windows the fused backward kernel covers
+bool bwd_tiled(int kh, int kw) { return kh == kw && (kh == 1 || kh == 3 || kh == 5 || kh == 7); }
+
+int64_t bwd_tiles(int H, int W) {
+  return ((int64_t)(W + TX - 1) / TX) * ((H + kBwdRows - 1) / kBwdRows);
+}
 
 int64_t dw_parts(int H, int W, int kh, int kw) {
-  if (dw_streaming(kh, kw)) {
-    int64_t strips = (W + TX - 1) / TX, segs = (H + kDwRows - 1) / kDwRows;
-    return strips * segs;
-  }
+  if (bwd_tiled(kh, kw)) return std::min<int64_t>(bwd_tiles(H, W), kBwdGrid);
   return ((int64_t)H * W + kDwChunk - 1) / kDwChunk;
 }
 
-template <int K, bool VEC>
-rise_status launch_dw_stream(float* partial, const StencilBwdArgs& a, hipStream_t s) {
-  int strips = (a.W + TX - 1) / TX, segs = (a.H + kDwRows - 1) / kDwRows;
-  int tasks = strips * segs;
-  hipLaunchKernelGGL((stencil_dw_stream<K, VEC, kDwRows>), dim3((tasks + 3) / 4), dim3(kThreads),
-                     0, s, partial, a.dout, a.ld_dout, a.in, a.ld_in, a.H, a.W,
-                     (int)(a.pad == RISE_PAD_ZERO), segs, tasks);
-  return check_launch("stencil_dw_stream");
+template <int K, bool VEC, bool DIN, bool DW>
+rise_status launch_bwd(float* partial, const StencilBwdArgs& a, hipStream_t s) {
+  const int64_t n = bwd_tiles(a.H, a.W);
+  if (n > INT32_MAX - kBwdGrid) return fail(RISE_ERR_SHAPE, "rise_stencil2d_backward: too many tiles");
+  hipLaunchKernelGGL((stencil_bwd_tiled<K, VEC, kBwdRows, DIN, DW>),
+                     dim3((unsigned)std::min<int64_t>(n, kBwdGrid)), dim3(kThreads), 0, s, a.din,
+                     a.ld_din, partial, a.dout, a.ld_dout, a.in, a.ld_in, a.H, a.W, a.w,
+                     (int)(a.pad == RISE_PAD_ZERO), (a.W + TX - 1) / TX, (int)n);
+  return check_launch("stencil_bwd_tiled");
+}
+
+template <int K>
+rise_status launch_bwd_k(float* partial, const StencilBwdArgs& a, hipStream_t s) {
+  auto aligned = [](const void* p, int64_t ld) { return ((uintptr_t)p & 15) == 0 && ld % 4 == 0; };
+  const bool vec = aligned(a.dout, a.ld_dout) && (!a.din || aligned(a.din, a.ld_din)) &&
+                   (!a.dw || aligned(a.in, a.ld_in));
+  if (a.din && a.dw)
+    return vec ? launch_bwd<K, true, true, true>(partial, a, s)
+               : launch_bwd<K, false, true, true>(partial, a, s);
+  if (a.din)
+    return vec ? launch_bwd<K, true, true, false>(partial, a, s)
+               : launch_bwd<K, false, true, false>(partial, a, s);
+  return vec ? launch_bwd<K, true, false, true>(partial, a, s)
+             : launch_bwd<K, false, false, true>(partial, a, s);
 }
 
 }  // namespace
@@ -781,7 +940,17 @@ rise_status launch_stencil2d_backward(const StencilBwdArgs& a, void* ws, hipStre
   float* rot = (float*)ws;
   float* partial = (float*)((char*)ws + ((size_t)taps * 4 + 255) / 256 * 256);
   rise_status st = RISE_OK;
-  if (a.din) {
+  const bool tiled = bwd_tiled(a.kh, a.kw);
+  if (tiled) {
+    switch (a.kh) {
+      case 1: st = launch_bwd_k<1>(partial, a, s); break;
+      case 3: st = launch_bwd_k<3>(partial, a, s); break;
+      case 5: st = launch_bwd_k<5>(partial, a, s); break;
+      default: st = launch_bwd_k<7>(partial, a, s); break;
+    }
+    if (st != RISE_OK) return st;
+  }
+  if (a.din && !tiled) {
     hipLaunchKernelGGL(rotate180_kernel, dim3(1), dim3(256), 0, s, rot, a.w, taps);
     if ((st = check_launch("rotate180_kernel")) != RISE_OK) return st;
     StencilArgs f{a.din, a.ld_din, a.dout, a.ld_dout, a.H, a.W, rot, a.kh, a.kw, RISE_PAD_ZERO};
@@ -797,16 +966,7 @@ rise_status launch_stencil2d_backward(const StencilBwdArgs& a, void* ws, hipStre
   }
   if (a.dw) {
     const int64_t parts = dw_parts(a.H, a.W, a.kh, a.kw);
-    auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-    bool vec = aligned(a.in) && aligned(a.dout) && a.ld_in % 4 == 0 && a.ld_dout % 4 == 0;
-    if (dw_streaming(a.kh, a.kw)) {
-      switch (a.kh) {
-        case 1: st = vec ? launch_dw_stream<1, true>(partial, a, s) : launch_dw_stream<1, false>(partial, a, s); break;
-        case 3: st = vec ? launch_dw_stream<3, true>(partial, a, s) : launch_dw_stream<3, false>(partial, a, s); break;
-        case 5: st = vec ? launch_dw_stream<5, true>(partial, a, s) : launch_dw_stream<5, false>(partial, a, s); break;
-        default: st = vec ? launch_dw_stream<7, true>(partial, a, s) : launch_dw_stream<7, false>(partial, a, s); break;
-      }
-    } else {
+    if (!tiled) {
       hipLaunchKernelGGL(stencil_dw_direct, dim3((unsigned)parts, (unsigned)taps), dim3(kThreads),
                          0, s, partial, a.dout, a.ld_dout, a.in, a.ld_in, a.H, a.W, a.kh, a.kw,
                          (int)(a.pad == RISE_PAD_ZERO), kDwChunk);
@@ -814,7 +974,7 @@ rise_status launch_stencil2d_backward(const StencilBwdArgs& a, void* ws, hipStre
     }
     if (st != RISE_OK) return st;
     hipLaunchKernelGGL(reduce_partials, dim3(taps), dim3(kThreads), 0, s, a.dw, partial,
-                       (int)parts, taps);
+                       (int)parts);
     if ((st = check_launch("reduce_partials")) != RISE_OK) return st;
   }
   return RISE_OK;

@@ -618,6 +618,96 @@ __device__ __forceinline__ void stencil_stash(const StencilRegs<K, TY>& st,
   }
 }
 
+// Rows of any width >= 4 and any alignment, without branches between the
+// loads: each chunk is one 16-byte load from the nearest position that lies
+// wholly inside its (clamped) row, and what pad2D makes of it is decided when
+// the chunk is written to LDS (stencil_stash_any), so all loads of an edge tile
+// are in flight together.  Element-wise loads under per-chunk branches instead
+// waited out one memory latency per chunk: the 7 x 7 stencil of a 1531 x 2047
+// image, a third of whose tiles touch an edge, ran 11.6 us with them.
+template <int K, int TY>
+__device__ __forceinline__ void stencil_fetch_any(StencilRegs<K, TY>& st,
+                                                  const float* __restrict__ in, int64_t ld_in,
+                                                  int H, int W, int y0, int x0) {
+  using Cfg = StencilCfg<K, TY>;
+#pragma unroll
+  for (int p = 0; p < Cfg::PER; p++) {
+    const int c = min((int)threadIdx.x + p * kThreads, Cfg::LDS_CHUNKS - 1);
+    const int lr = c / kLChunks, cc = c - lr * kLChunks;
+    const int gy = clampi(y0 - Cfg::R + lr, 0, H - 1), gx = clampi(x0 - kHalo + cc * 4, 0, W - 4);
+    st[p] = *reinterpret_cast<const f32x4u*>(in + (int64_t)gy * ld_in + gx);
+  }
+}
+
+// Columns gx .. gx + 3 under pad2D from the chunk loaded at clamp(gx, 0, W - 4).
+__device__ __forceinline__ f32x4 chunk_any(f32x4 v, int gx, int W, int zero_pad) {
+  if (gx < 0 || gx > W - 4) {
+    const int at = clampi(gx, 0, W - 4);
+    f32x4 u;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int i = clampi(gx + q, 0, W - 1) - at;
+      const float lo = i == 0 ? v.x : v.y, hi = i == 2 ? v.z : v.w;
+      u[q] = zero_pad && (gx + q < 0 || gx + q >= W) ? 0.f : i < 2 ? lo : hi;
+    }
+    v = u;
+  }
+  return v;
+}
+
+template <int K, int TY>
+__device__ __forceinline__ void stencil_stash_any(const StencilRegs<K, TY>& st, f32x4* lds, int H,
+                                                  int W, int zero_pad, int y0, int x0) {
+  using Cfg = StencilCfg<K, TY>;
+#pragma unroll
+  for (int p = 0; p < Cfg::PER; p++) {
+    const int c = threadIdx.x + p * kThreads;
+    if (c < Cfg::LDS_CHUNKS) {
+      const int lr = c / kLChunks, cc = c - lr * kLChunks;
+      const int gy = y0 - Cfg::R + lr, gx = x0 - kHalo + cc * 4;
+      f32x4 v = chunk_any(st[p], gx, W, zero_pad);
+      if (zero_pad && (gy < 0 || gy >= H)) v = f32x4{0.f, 0.f, 0.f, 0.f};
+      lds[c] = v;
+    }
+  }
+}
+
+// The loads of a halo tile (returned: whether it lies wholly inside the image)
+// and its place in LDS with pad2D applied, for any alignment and width.
+template <int K, bool VEC, int TY>
+__device__ __forceinline__ bool stencil_load_tile(StencilRegs<K, TY>& st,
+                                                  const float* __restrict__ in, int64_t ld_in,
+                                                  int H, int W, int zero_pad, int y0, int x0) {
+  using Cfg = StencilCfg<K, TY>;
+  if (y0 >= Cfg::R && y0 + TY + Cfg::R <= H && x0 >= kHalo && x0 + kStencilTX + kHalo <= W) {
+    // interior tile: no padding, every chunk at a fixed offset from the corner
+    // (16-byte aligned when VEC, otherwise at the rows' own 4-byte alignment)
+    const float* corner = in + (int64_t)(y0 - Cfg::R) * ld_in + (x0 - kHalo);
+#pragma unroll
+    for (int p = 0; p < Cfg::PER; p++) {
+      const int c = min((int)threadIdx.x + p * kThreads, Cfg::LDS_CHUNKS - 1);
+      const int lr = c / kLChunks, cc = c - lr * kLChunks;
+      const float* q = corner + (int64_t)lr * ld_in + 4 * cc;
+      st[p] = VEC ? *reinterpret_cast<const f32x4*>(q) : f32x4(*reinterpret_cast<const f32x4u*>(q));
+    }
+    return true;
+  }
+  if (W >= 4)
+    stencil_fetch_any<K, TY>(st, in, ld_in, H, W, y0, x0);
+  else
+    stencil_fetch<K, VEC, TY>(st, in, ld_in, H, W, zero_pad, y0, x0);
+  return false;
+}
+template <int K, int TY>
+__device__ __forceinline__ void stencil_put_tile(const StencilRegs<K, TY>& st, f32x4* lds, int H,
+                                                 int W, int zero_pad, int y0, int x0,
+                                                 bool inside) {
+  if (inside || W < 4)
+    stencil_stash<K, TY>(st, lds);
+  else
+    stencil_stash_any<K, TY>(st, lds, H, W, zero_pad, y0, x0);
+}
+
 // Aligned rows (VEC and W % 4 == 0, which the callers check): every 16-byte
 // chunk of the halo tile is either wholly inside or wholly outside the image
 // (its columns start at a multiple of 4), so the fetch can be branch-free: each chunk is loaded from a clamped,
@@ -819,25 +909,15 @@ __device__ __forceinline__ void stencil_lds_tile(float* __restrict__ out, int64_
   using Cfg = StencilCfg<K, TY>;
   float wt[K][K];
   if (SCALAR_W) stencil_weights<K, true>(wt, w);  // scalar loads, in flight during the fetch
-  if (y0 >= Cfg::R && y0 + TY + Cfg::R <= H && x0 >= kHalo && x0 + kStencilTX + kHalo <= W) {
-    // interior tile: no padding, every chunk at a fixed offset from the corner
-    // (16-byte aligned when VEC, otherwise at the rows' own 4-byte alignment)
-    const float* corner = in + (int64_t)(y0 - Cfg::R) * ld_in + (x0 - kHalo);
-#pragma unroll
-    for (int p = 0; p < Cfg::PER; p++) {
-      const int c = min((int)threadIdx.x + p * kThreads, Cfg::LDS_CHUNKS - 1);
-      const int lr = c / kLChunks, cc = c - lr * kLChunks;
-      const float* q = corner + (int64_t)lr * ld_in + 4 * cc;
-      st[p] = VEC ? *reinterpret_cast<const f32x4*>(q) : f32x4(*reinterpret_cast<const f32x4u*>(q));
-    }
-    stencil_stash<K, TY>(st, lds);
-  } else if (VEC && (W & 3) == 0) {
+  const bool interior =
+      y0 >= Cfg::R && y0 + TY + Cfg::R <= H && x0 >= kHalo && x0 + kStencilTX + kHalo <= W;
+  if (VEC && !interior && (W & 3) == 0) {
     uint32_t mode;
     stencil_fetch_aligned<K, TY>(st, mode, in, ld_in, H, W, zero_pad, y0, x0);
     stencil_stash_aligned<K, TY>(st, mode, lds);
   } else {
-    stencil_fetch<K, VEC, TY>(st, in, ld_in, H, W, zero_pad, y0, x0);
-    stencil_stash<K, TY>(st, lds);
+    stencil_load_tile<K, VEC, TY>(st, in, ld_in, H, W, zero_pad, y0, x0);
+    stencil_put_tile<K, TY>(st, lds, H, W, zero_pad, y0, x0, interior);
   }
   __syncthreads();
   if (!SCALAR_W) stencil_weights<K, false>(wt, w);

@@ -124,6 +124,40 @@ def test_stencil_backward_other_windows(rise, kh, kw, pad):
     stencil_bwd_case(rise, 45, 77, kh, kw, pad, kh * 7 + kw)
 
 
+@pytest.mark.parametrize("pad", list(PADS))
+@pytest.mark.parametrize("k", [3, 5, 7])
+@pytest.mark.parametrize("H,W,off", [(65700, 5, 0), (16, 256, 0), (17, 255, 1), (7, 4, 0),
+                                     (31, 513, 3), (3, 258, 2), (40, 2, 0)])
+def test_stencil_backward_tiles(rise, H, W, k, pad, off):
+    # edges of the 16 x 256 tiles: one tile exactly, one row or column more or less,
+    # rows at every 4-byte offset, more tiles than workgroups (65700 rows); each
+    # gradient alone equals the two together (dIn bit for bit, dW within the bound)
+    import torch
+
+    print(f"stencil_backward tiles H={H} W={W} k={k} pad={pad} off={off}", flush=True)
+    g = ri.rng(H + 3 * W + k)
+    img = ri.uniform_matrix(g, H, W, 0.0, 1.0)
+    w = ri.uniform_matrix(g, k, k)
+    G = ri.uniform_matrix(g, H, W)
+
+    def shifted(x):
+        buf = torch.empty(x.size + off, device="cuda")
+        buf[off:] = dev(x).reshape(-1)
+        return buf[off:].view(H, W)
+
+    tG, tI, tw = shifted(G), shifted(img), dev(w)
+    dIn, dW = rise.stencil2d_backward(tG, tI, tw, pad=pad)
+    only_in, none_w = rise.stencil2d_backward(tG, tI, tw, pad=pad, need_dw=False)
+    none_in, only_w = rise.stencil2d_backward(tG, tI, tw, pad=pad, need_din=False)
+    assert none_w is None and none_in is None
+    rin, rw = oracle.stencil2d_backward(G, img, w, PADS[pad])
+    sin, sw = oracle.stencil2d_backward(np.abs(G), np.abs(img), np.abs(w), PADS[pad])
+    assert componentwise(host(dIn), rin, sin) <= TOL
+    assert componentwise(host(dW), rw, sw) <= TOL
+    assert componentwise(host(only_w), rw, sw) <= TOL
+    assert np.array_equal(host(only_in), host(dIn))
+
+
 def test_stencil_backward_4096(rise):
     H = W = 4096
     img = ri.image_uniform(H, W, ri.SEED_STENCIL)

@@ -44,6 +44,26 @@ def test_tiled_kernel_vs_oracle(rise, pad, H, W, k):
 
 
 @pytest.mark.parametrize("pad", list(PADS))
+@pytest.mark.parametrize("k", [1, 3, 5, 7])
+@pytest.mark.parametrize("H,W,off", [(9, 4, 0), (8, 6, 1), (20, 254, 2), (24, 261, 0), (33, 515, 3),
+                                     (40, 770, 1)])
+def test_edge_tiles_of_any_width_and_alignment(rise, pad, H, W, k, off):
+    # images whose rows start at every 4-byte offset and end at every remainder of
+    # a 16-byte chunk: edge tiles load clamped chunks and place them when staging
+    import torch
+
+    g = ri.rng(H * 7 + W + k)
+    img = ri.uniform_matrix(g, H, W)
+    w = ri.uniform_matrix(g, k, k)
+    buf = torch.empty(img.size + off, device="cuda")
+    buf[off:] = dev(img).reshape(-1)
+    print(f"stencil edge tiles {H}x{W} k={k} pad={pad} off={off}", flush=True)
+    out = host(rise.stencil2d(buf[off:].view(H, W), dev(w), pad=pad))
+    assert componentwise(out, oracle.stencil2d(img, w, PADS[pad]),
+                         stencil_scale(img, w, PADS[pad])) <= TOL_F32
+
+
+@pytest.mark.parametrize("pad", list(PADS))
 @pytest.mark.parametrize("H,W", [(2050, 2100), (4099, 513)])
 @pytest.mark.parametrize("k", [3, 5, 7])
 def test_resident_grid_walks_several_tiles(rise, pad, H, W, k):
