@@ -160,7 +160,7 @@ def main():
     # (contiguous, 16-byte aligned rows, K a multiple of 16); other tiles run the
     # register-staged one
     gt = rise.rise_gemm_default_tile(M, N, K, "f32")
-    gemm_kernel = "gemm_f32_async_kernel" if tuple(gt) == (256, 128, 16) else "gemm_f32_kernel"
+    gemm_kernel = "gemm_f32_kernel"
     gemm_traffic = traffic_for(gemm_kernel, ["paper_2201_03611_amd/csrc/gemm_f32.hip",
                                              "paper_2201_03611_amd/csrc/async_copy.h",
                                              "paper_2201_03611_amd/csrc/tiles.h",

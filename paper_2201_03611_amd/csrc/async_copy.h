@@ -64,5 +64,33 @@ __device__ __forceinline__ void copy4(const void* src, void* lds_base) {
 #endif
 }
 
+// A value every lane of the wave holds alike, in scalar registers.
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+template <typename T>
+__device__ __forceinline__ T* uniform(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)(uint64_t)uniform((int64_t)(uint64_t)p);
+}
+
+// The same copies from a wave-uniform base plus a 32-bit byte offset per lane:
+// no vector arithmetic per copy when the base advances by a uniform step.
+__device__ __forceinline__ void copy16_at(const void* base, uint32_t off, void* lds_base) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const uint32_t to = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)lds_base));
+  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(to) : "memory");
+#endif
+}
+__device__ __forceinline__ void copy4_at(const void* base, uint32_t off, void* lds_base) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const uint32_t to = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)lds_base));
+  asm volatile("global_load_lds_dword %0, %1" ::"v"(off), "s"(base), "{m0}"(to) : "memory");
+#endif
+}
+
 }  // namespace async
 }  // namespace rise

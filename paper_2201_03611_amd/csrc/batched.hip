@@ -74,14 +74,12 @@ struct Item {
 };
 
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
-// FP32 tiles of problems whose storage allows it (tiles::f32_async_eligible)
-// run the asynchronous-ring schedule with this many slabs in flight
-constexpr int kF32Stages = 3;
+// FP32 tiles: 2 x 2 waves, a ring of three slabs
+template <int BM, int BN>
+using F32Tile = tiles::F32Cfg<BM, BN, kF32BK, 3, 2, 2, 1>;
 // the largest GEMM tile of any kind
 constexpr int kGemmLdsBytes =
-    cmax(cmax(cmax(4 * tiles::F32Cfg<128, 128, kF32BK, false, false>::LDS_FLOATS,
-                   4 * tiles::F32Cfg<128, 128, kF32BK, false, true>::LDS_FLOATS),
-              16 * tiles::F32AsyncCfg<128, 128, kF32Stages>::LDS_CHUNKS),
+    cmax(16 * F32Tile<128, 128>::LDS_CHUNKS,
          16 * tiles::Bf16Cfg<128, 128, kBf16BK>::LDS_CHUNKS);
 static_assert(kGemmLdsBytes * kGemmOccupancy <= 160 * 1024, "LDS of the resident workgroups");
 
@@ -98,14 +96,14 @@ __device__ __noinline__ void item_f32(const Desc& d, int tm, int tn, char* lds) 
   const float* A = gptr<const float>(d.a);
   const float* B = gptr<const float>(d.b);
   float* C = gptr<float>(d.out);
-  if (tiles::f32_async_eligible(A, d.lda, B, d.ldb, d.M, d.N, d.K, false, TB))
-    tiles::gemm_f32_async_tile<BM, BN, kF32Stages, false, TB>(
+  if (tiles::f32_vec(A, d.lda, B, d.ldb, d.M, d.N, d.K, false, TB))
+    tiles::gemm_f32_tile<F32Tile<BM, BN>, false, TB, true>(
         C, d.ldc, A, d.lda, B, d.ldb, d.M, d.N, d.K, tm * BM, tn * BN,
         reinterpret_cast<f32x4*>(lds));
   else
-    tiles::gemm_f32_tile<BM, BN, kF32BK, false, TB, true>(C, d.ldc, A, d.lda, B, d.ldb, d.M, d.N,
-                                                          d.K, tm * BM, tn * BN,
-                                                          reinterpret_cast<float*>(lds));
+    tiles::gemm_f32_tile<F32Tile<BM, BN>, false, TB, false>(
+        C, d.ldc, A, d.lda, B, d.ldb, d.M, d.N, d.K, tm * BM, tn * BN,
+        reinterpret_cast<f32x4*>(lds));
 }
 template <int BM, int BN, bool TB>
 __device__ __noinline__ void item_bf16(const Desc& d, int tm, int tn, char* lds) {

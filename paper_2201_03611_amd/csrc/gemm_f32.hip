@@ -1,14 +1,12 @@
-// FP32 GEMM on the gfx950 FP32 matrix cores (v_mfma_f32_32x32x2_f32): one
-// workgroup per output tile, tiles visited in an XCD-contiguous, grouped order
-// so that concurrently running tiles share A and B panels in their XCD's L2.
-// Two schedules of the K loop (reduceSeq over split(BK) slabs, each slab staged
-// in LDS: toMem(Local), paper Sec. V-B/C):
-//   register-staged (tiles::gemm_f32_tile): every shape and alignment, slabs
-//     fetched into registers and written to a double-buffered LDS slab;
-//   asynchronous ring (gemm_f32_async_kernel, the 256 x 128 x 16 tile when K
-//     is a multiple of 16 and rows are 16-byte aligned): slabs copied from
-//     global memory straight into a ring of three LDS slabs two slabs ahead,
-//     two workgroups per CU.
+// FP32 GEMM on the gfx950 FP32 matrix cores (v_mfma_f32_32x32x2_f32).  Two kernels:
+//   gemm_f32_kernel: one workgroup per BM x BN output tile, tiles visited in an
+//     XCD-contiguous, grouped order so that concurrently running tiles share A and
+//     B panels in their XCD's L2; the K loop (reduceSeq over split(BK) slabs, each
+//     staged in LDS: toMem(Local), paper Sec. V-B/C) is tiles::gemm_f32_tile;
+//   gemm_f32_split_kernel: one workgroup per 32 x 32 output tile whose waves take
+//     alternate slabs of K and add their sums at the end, for small products.
+#include <algorithm>
+
 #include "common.h"
 #include "tiles.h"
 
@@ -17,112 +15,212 @@ namespace {
 
 using tiles::kThreads;
 
-template <int BM, int BN, int BK, bool TA, bool TB, bool VEC>
-__global__ __launch_bounds__(kThreads, 2) void gemm_f32_kernel(
+template <typename T, bool TA, bool TB, bool VEC>
+__global__ __launch_bounds__(T::THREADS, T::WAVES / 4) void gemm_f32_kernel(
     float* __restrict__ C, int64_t ldc, const float* __restrict__ A, int64_t lda,
     const float* __restrict__ B, int64_t ldb, int M, int N, int K, int tiles_m, int tiles_n) {
-  __shared__ float lds[tiles::F32Cfg<BM, BN, BK, TA, TB>::LDS_FLOATS];
+  __shared__ f32x4 lds[T::LDS_CHUNKS];
   int tm, tn;
   grouped_tile(xcd_contiguous(blockIdx.x, gridDim.x), tiles_m, tiles_n, 8, tm, tn);
-  tiles::gemm_f32_tile<BM, BN, BK, TA, TB, VEC>(C, ldc, A, lda, B, ldb, M, N, K, tm * BM, tn * BN,
-                                                lds);
+  tiles::gemm_f32_tile<T, TA, TB, VEC>(C, ldc, A, lda, B, ldb, M, N, K, tm * T::BM, tn * T::BN, lds);
 }
 
-// Asynchronous-ring schedule (tiles::gemm_f32_async_tile): one workgroup per
-// 256 x 128 tile, two resident per CU.
-template <int BM, int BN, int STAGES, bool TA, bool TB>
-__global__ __launch_bounds__(kThreads, 2) void gemm_f32_async_kernel(
+// Few output tiles: a workgroup of NW waves owns a 32 x 32 tile, and wave w sums
+// the 32-k slabs w, w + NW, ... of it, loading its MFMA fragments straight from
+// global memory into registers one slab ahead (no LDS and no barrier until the
+// NW partial tiles are added, in wave order).  What bounds such a product is the
+// chain of slabs, one memory latency each: with NW waves it is NW times shorter,
+// and 32 x 32 tiles are four times as many workgroups as 64 x 64 (128^3: one slab
+// per wave on 16 workgroups, kernel 6.6 -> 4.1 us; 512^3 13.1 -> 7.7).
+//   rows along k: a lane reads 16 bytes (4 k of its row, at the row's own 4-byte
+//     alignment; gfx950 runs global memory in unaligned-access mode);
+//   rows along m or n: a lane reads one value per k, 32 lanes 128 contiguous bytes.
+// Rows past the edge repeat the last one and feed outputs that are not stored;
+// k past the end reads as zero.
+constexpr int kSplitMaxK = 1024;  // longest K the library picks it for
+
+template <bool ALONG_K>
+struct SplitFrag {
+  f32x4 v[4];  // v[s][t]: k = 8 s + 4 kl + t of the slab
+  __device__ void load(const float* X, int64_t ld, int mn, int k0, int K, int kl) {
+    if (k0 + 32 <= K) {
+#pragma unroll
+      for (int s = 0; s < 4; s++) {
+        const int k = k0 + 8 * s + 4 * kl;
+        if (ALONG_K) {
+          v[s] = *reinterpret_cast<const tiles::f32x4u*>(X + (int64_t)mn * ld + k);
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; t++) v[s][t] = X[(int64_t)(k + t) * ld + mn];
+        }
+      }
+      return;
+    }
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+      for (int t = 0; t < 4; t++) {
+        const int k = k0 + 8 * s + 4 * kl + t, kc = min(k, K - 1);
+        const float x = ALONG_K ? X[(int64_t)mn * ld + kc] : X[(int64_t)kc * ld + mn];
+        v[s][t] = k < K ? x : 0.f;
+      }
+  }
+};
+
+template <int NW, bool TA, bool TB>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_split_kernel(
     float* __restrict__ C, int64_t ldc, const float* __restrict__ A, int64_t lda,
     const float* __restrict__ B, int64_t ldb, int M, int N, int K, int tiles_m, int tiles_n) {
-  __shared__ f32x4 lds[tiles::F32AsyncCfg<BM, BN, STAGES>::LDS_CHUNKS];
+  __shared__ float part[NW][32 * 32];
   int tm, tn;
   grouped_tile(xcd_contiguous(blockIdx.x, gridDim.x), tiles_m, tiles_n, 8, tm, tn);
-  tiles::gemm_f32_async_tile<BM, BN, STAGES, TA, TB>(C, ldc, A, lda, B, ldb, M, N, K, tm * BM,
-                                                     tn * BN, lds);
+  const int m0 = tm * 32, n0 = tn * 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int kl = lane >> 5, il = lane & 31;
+  const int m = min(m0 + il, M - 1), n = min(n0 + il, N - 1);
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; r++) acc[r] = 0.f;
+  SplitFrag<!TA> a[2];
+  SplitFrag<TB> b[2];
+  auto mfmas = [&](const SplitFrag<!TA>& x, const SplitFrag<TB>& y) {
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+      for (int t = 0; t < 4; t++)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.v[s][t], y.v[s][t], acc, 0, 0, 0);
+  };
+  int k0 = 32 * wave;
+  if (k0 < K) {
+    a[0].load(A, lda, m, k0, K, kl);
+    b[0].load(B, ldb, n, k0, K, kl);
+  }
+  for (; k0 < K; k0 += 64 * NW) {  // two slabs a round, so the register sets alternate
+    const int k1 = k0 + 32 * NW, k2 = k1 + 32 * NW;
+    if (k1 < K) {
+      a[1].load(A, lda, m, k1, K, kl);
+      b[1].load(B, ldb, n, k1, K, kl);
+    }
+    mfmas(a[0], b[0]);
+    if (k1 >= K) break;
+    if (k2 < K) {
+      a[0].load(A, lda, m, k2, K, kl);
+      b[0].load(B, ldb, n, k2, K, kl);
+    }
+    mfmas(a[1], b[1]);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; r++) part[wave][(8 * (r >> 2) + 4 * kl + (r & 3)) * 32 + il] = acc[r];
+  __syncthreads();
+#pragma unroll
+  for (int o = tid; o < 32 * 32; o += 64 * NW) {
+    float s = part[0][o];
+#pragma unroll
+    for (int w = 1; w < NW; w++) s += part[w][o];
+    const int row = m0 + o / 32, col = n0 + o % 32;
+    if (row < M && col < N) C[(int64_t)row * ldc + col] = s;
+  }
 }
 
-template <bool TA, bool TB>
-rise_status launch_async(const GemmF32Args& a, hipStream_t s) {
-  constexpr int BM = 256, BN = 128;
-  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
-  hipLaunchKernelGGL((gemm_f32_async_kernel<BM, BN, 3, TA, TB>), dim3(tiles_m * tiles_n),
-                     dim3(kThreads), 0, s, a.C, a.ldc, a.A, a.lda, a.B, a.ldb, a.M, a.N, a.K,
-                     tiles_m, tiles_n);
-  return check_launch("gemm_f32_async_kernel");
-}
-
-bool async_eligible(const GemmF32Args& a) {
-  return tiles::f32_async_eligible(a.A, a.lda, a.B, a.ldb, a.M, a.N, a.K, a.ta, a.tb);
-}
-
-template <int BM, int BN, int BK, bool TA, bool TB, bool VEC>
-rise_status launch_cfg(const GemmF32Args& a, hipStream_t s) {
-  int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
-  dim3 grid(tiles_m * tiles_n), block(kThreads);
-  hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BK, TA, TB, VEC>), grid, block, 0, s, a.C, a.ldc,
-                     a.A, a.lda, a.B, a.ldb, a.M, a.N, a.K, tiles_m, tiles_n);
+template <typename T, bool VEC>
+rise_status launch_tile(const GemmF32Args& a, hipStream_t s) {
+  const int tiles_m = (a.M + T::BM - 1) / T::BM, tiles_n = (a.N + T::BN - 1) / T::BN;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n), dim3(T::THREADS), 0, s, a.C, a.ldc, a.A,
+                       a.lda, a.B, a.ldb, a.M, a.N, a.K, tiles_m, tiles_n);
+  };
+  if (!a.ta && !a.tb) go(gemm_f32_kernel<T, false, false, VEC>);
+  else if (!a.ta) go(gemm_f32_kernel<T, false, true, VEC>);
+  else if (!a.tb) go(gemm_f32_kernel<T, true, false, VEC>);
+  else go(gemm_f32_kernel<T, true, true, VEC>);
   return check_launch("gemm_f32_kernel");
 }
 
-template <int BM, int BN, int BK>
-rise_status launch_ops(const GemmF32Args& a, bool vec, hipStream_t s) {
-  if (vec) {
-    if (!a.ta && !a.tb) return launch_cfg<BM, BN, BK, false, false, true>(a, s);
-    if (!a.ta && a.tb) return launch_cfg<BM, BN, BK, false, true, true>(a, s);
-    if (a.ta && !a.tb) return launch_cfg<BM, BN, BK, true, false, true>(a, s);
-    return launch_cfg<BM, BN, BK, true, true, true>(a, s);
-  }
-  if (!a.ta && !a.tb) return launch_cfg<BM, BN, BK, false, false, false>(a, s);
-  if (!a.ta && a.tb) return launch_cfg<BM, BN, BK, false, true, false>(a, s);
-  if (a.ta && !a.tb) return launch_cfg<BM, BN, BK, true, false, false>(a, s);
-  return launch_cfg<BM, BN, BK, true, true, false>(a, s);
+template <int NW>
+rise_status launch_split(const GemmF32Args& a, hipStream_t s) {
+  const int tiles_m = (a.M + 31) / 32, tiles_n = (a.N + 31) / 32;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n), dim3(64 * NW), 0, s, a.C, a.ldc, a.A,
+                       a.lda, a.B, a.ldb, a.M, a.N, a.K, tiles_m, tiles_n);
+  };
+  if (!a.ta && !a.tb) go(gemm_f32_split_kernel<NW, false, false>);
+  else if (!a.ta) go(gemm_f32_split_kernel<NW, false, true>);
+  else if (!a.tb) go(gemm_f32_split_kernel<NW, true, false>);
+  else go(gemm_f32_split_kernel<NW, true, true>);
+  return check_launch("gemm_f32_split_kernel");
 }
 
-const rise_tile kTiles[] = {{128, 128, 32}, {128, 64, 32}, {64, 128, 32}, {64, 64, 32},
-                            {256, 128, 16}};
+// The tiles, and nanoseconds per 64 x 64 outputs and k that one CU takes on them
+// (measured: 256 x 128 at 4096^3, 32 x 32 x 32 at 512^3, 32 x 32 x 128 at 64 x 64 x
+// 4096, the others at 1024^3, 1000 x 1531 x 777 and 1500 x 300 x 6000; the matrix
+// cores alone need 13.6 at 2.3 GHz).  0: only where asked for.
+struct TileCost {
+  rise_tile t;
+  double ns;
+};
+const TileCost kTiles[] = {{{128, 128, 32}, 0},  {{128, 64, 32}, 16.0}, {{64, 128, 32}, 16.0},
+                           {{64, 64, 32}, 16.5}, {{256, 128, 16}, 14.6}, {{64, 96, 32}, 17.0},
+                           {{96, 64, 32}, 16.5}, {{64, 32, 64}, 19.5},  {{32, 64, 64}, 19.5},
+                           {{32, 32, 32}, 36.0}, {{32, 32, 128}, 18.5}};
 
 }  // namespace
 
 bool gemm_f32_tile_supported(const rise_tile& t) {
   for (const auto& k : kTiles)
-    if (k.bm == t.bm && k.bn == t.bn && k.bk == t.bk) return true;
+    if (k.t.bm == t.bm && k.t.bn == t.bn && k.t.bk == t.bk) return true;
   return false;
 }
 
 int gemm_f32_tiles(rise_tile* out, int cap) {
   int n = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
-  for (int i = 0; out && i < n && i < cap; i++) out[i] = kTiles[i];
+  for (int i = 0; out && i < n && i < cap; i++) out[i] = kTiles[i].t;
   return n;
 }
 
 rise_tile gemm_f32_default_tile(int M, int N, int K) {
-  // Largest tile that still gives every CU at least one tile: 256 x 128 has the
-  // best operand reuse from LDS (measured 123-125 TFLOP/s at 4096^3 and 8192^3).
-  long t256 = (long)((M + 255) / 256) * ((N + 127) / 128);
-  if (t256 >= 256) return rise_tile{256, 128, 16};
-  long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-  if (t128 >= 256) return rise_tile{128, 128, 32};
-  long t64 = (long)((M + 127) / 128) * ((N + 63) / 64);
-  if (t64 >= 256) return rise_tile{128, 64, 32};
-  return rise_tile{64, 64, 32};
+  // The tile with the shortest time for the CU that gets the most tiles: what the
+  // shapes differ in is mainly how evenly they cover 256 CUs (1000 x 1531: 384
+  // tiles of 64 x 64, two on half of the CUs, 36 us; 256 of 64 x 96, one each, 31
+  // us; 512 x 512 x 512: 64 of 64 x 64, 14 us, 256 of 32 x 32, 8 us).  256 x 128
+  // only where rows are whole 16-byte chunks whichever way they are stored:
+  // copied value by value it measured slower than 64 x 64 (4095 x 4097 x 4096:
+  // 1.52 against 1.10 ms).
+  // 32 x 32 tiles of a short K run gemm_f32_split_kernel, whose waves wait out
+  // one memory latency per 32 k but need no ring to fill (128^3: 4.1 against 4.9
+  // us); of a long K the ring (64 x 64 x 4096: 22 against 38 us).
+  const bool chunks = M % 4 == 0 && N % 4 == 0 && K % 4 == 0;
+  rise_tile best{64, 64, 32};
+  double least = 0;
+  for (const auto& c : kTiles) {
+    if (c.ns == 0 || (c.t.bm == 256 && !chunks)) continue;
+    if (c.t.bm == 32 && c.t.bn == 32 && (c.t.bk == 128) != (K > kSplitMaxK)) continue;
+    const int64_t tiles = (((int64_t)M + c.t.bm - 1) / c.t.bm) * (((int64_t)N + c.t.bn - 1) / c.t.bn);
+    const double t = (double)((tiles + 255) / 256) * c.t.bm * c.t.bn * c.ns;
+    if (least == 0 || t < least) least = t, best = c.t;
+  }
+  return best;
 }
 
 rise_status launch_gemm_f32(const GemmF32Args& a, const rise_tile& t, hipStream_t s) {
-  auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-  bool vec = aligned(a.A) && aligned(a.B) && a.lda % 4 == 0 && a.ldb % 4 == 0;
-  if (t.bm == 128 && t.bn == 128) return launch_ops<128, 128, 32>(a, vec, s);
-  if (t.bm == 128 && t.bn == 64) return launch_ops<128, 64, 32>(a, vec, s);
-  if (t.bm == 64 && t.bn == 128) return launch_ops<64, 128, 32>(a, vec, s);
-  if (t.bm == 64 && t.bn == 64) return launch_ops<64, 64, 32>(a, vec, s);
-  if (t.bm == 256 && t.bn == 128) {
-    if (async_eligible(a)) {
-      if (!a.ta && !a.tb) return launch_async<false, false>(a, s);
-      if (!a.ta && a.tb) return launch_async<false, true>(a, s);
-      if (a.ta && !a.tb) return launch_async<true, false>(a, s);
-      return launch_async<true, true>(a, s);
-    }
-    return launch_ops<256, 128, 16>(a, vec, s);
+  const bool vec = tiles::f32_vec(a.A, a.lda, a.B, a.ldb, a.M, a.N, a.K, a.ta, a.tb);
+#define RISE_F32_TILE(BM, BN, BK, ...)                                         \
+  if (t.bm == BM && t.bn == BN && t.bk == BK) {                                \
+    using T = tiles::F32Cfg<BM, BN, BK, __VA_ARGS__>;                          \
+    return vec ? launch_tile<T, true>(a, s) : launch_tile<T, false>(a, s);     \
   }
+  RISE_F32_TILE(256, 128, 16, 3, 2, 2, 1)
+  RISE_F32_TILE(128, 128, 32, 3, 2, 2, 2)
+  RISE_F32_TILE(128, 64, 32, 3, 2, 2, 2)
+  RISE_F32_TILE(64, 128, 32, 3, 2, 2, 2)
+  RISE_F32_TILE(64, 64, 32, 3, 2, 2, 2)
+  RISE_F32_TILE(64, 96, 32, 3, 2, 3, 2)
+  RISE_F32_TILE(96, 64, 32, 3, 3, 2, 2)
+  RISE_F32_TILE(64, 32, 64, 3, 2, 1, 4)
+  RISE_F32_TILE(32, 64, 64, 3, 1, 2, 4)
+  RISE_F32_TILE(32, 32, 128, 3, 1, 1, 8)
+#undef RISE_F32_TILE
+  if (t.bm == 32 && t.bn == 32 && t.bk == 32)
+    return a.K <= 512 ? launch_split<4>(a, s) : launch_split<8>(a, s);
   return fail(RISE_ERR_UNSUPPORTED, "gemm_f32: unsupported tile");
 }
 

@@ -4,6 +4,8 @@
 // that runs several kinds of tiles can overlay them in one buffer.
 #pragma once
 
+#include <type_traits>
+
 #include "async_copy.h"
 #include "common.h"
 
@@ -12,294 +14,210 @@ namespace tiles {
 
 constexpr int kThreads = 256;
 
+// a 16-byte vector of floats that may sit at any 4-byte boundary (gfx950 runs
+// global memory in unaligned-access mode: one dwordx4 access either way)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
 __device__ __forceinline__ int clampi(int v, int lo, int hi) {
   return v < lo ? lo : (v > hi ? hi : v);
 }
 
 // ===========================================================================
 // FP32 GEMM tile (v_mfma_f32_32x32x2_f32): C[m0:m0+BM, n0:n0+BN] = A B
-// ===========================================================================
-template <int BM, int BN, int BK, bool TA, bool TB>
-struct F32Cfg {
-  // LDS layout: k-major slabs, [BK][BM + pad] and [BK][BN + pad], double buffered.
-  // Transposing writes (operand stored K-contiguous) use an odd pad so that the
-  // scalar writes of a half-wave hit distinct banks; direct float4 writes use
-  // pad 4 to keep rows 16-byte aligned.
-  static constexpr int PA = TA ? 4 : 1;
-  static constexpr int PB = TB ? 1 : 4;
-  static constexpr int LA = BM + PA;
-  static constexpr int LB = BN + PB;
-  static constexpr int NA = BM * BK / 4 / kThreads;  // float4 chunks per thread
-  static constexpr int NB = BN * BK / 4 / kThreads;
-  static constexpr int LDS_FLOATS = 2 * BK * (LA + LB);
-  static_assert(NA >= 1 && NB >= 1, "tile too small for 256 threads");
-  static_assert(BM * BK / 4 % kThreads == 0 && BN * BK / 4 % kThreads == 0, "tile split");
-};
-
-__device__ __forceinline__ f32x4 load4_guarded(const float* p, int valid) {
-  // valid = number of in-bounds elements (<= 4) along the contiguous direction
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
-  if (valid > 0) v.x = p[0];
-  if (valid > 1) v.y = p[1];
-  if (valid > 2) v.z = p[2];
-  if (valid > 3) v.w = p[3];
-  return v;
-}
-
-template <bool VEC>
-__device__ __forceinline__ f32x4 load_chunk(const float* base, int64_t row_off, int col,
-                                            bool row_ok, int cols) {
-  // 4 consecutive elements from base[row_off + col]; out-of-range elements read 0
-  if (!row_ok) return f32x4{0.f, 0.f, 0.f, 0.f};
-  const float* p = base + row_off + col;
-  const int valid = cols - col;
-  if (VEC && valid >= 4) return *reinterpret_cast<const f32x4*>(p);
-  return load4_guarded(p, valid > 4 ? 4 : valid);
-}
-
+//
 // Pattern -> hardware mapping (paper Sec. IV-B/C: splitJoinMap, the map lowerings
 // and fuseReduceMap; Sec. V-C: toMem and reduceSeq): the workgroup owns one
 // split(BM) x split(BN) tile (mapWorkGroup); its 2 x 2 sub-tiles go to the four
 // waves (mapLocal); split(BK) + reduceSeq(Private) is the K loop with register
-// accumulators; each slab is staged in LDS (toMem(Local)), double buffered so the
-// global fetch of slab i+1 is in flight while the matrix cores consume slab i;
-// zip |> map(*) |> reduce(+) is v_mfma_f32_32x32x2_f32; join . join is the
-// guarded row-major store.  Operands may be read through transpose (TA, TB)
-// without copies.  Ragged M/N/K: guarded loads supply zeros (exact for the
-// sum), stores are guarded.
-template <int BM, int BN, int BK, bool TA, bool TB, bool VEC>
-__device__ __forceinline__ void gemm_f32_tile(float* __restrict__ C, int64_t ldc,
-                                              const float* __restrict__ A, int64_t lda,
-                                              const float* __restrict__ B, int64_t ldb, int M,
-                                              int N, int K, int m0, int n0, float* lds) {
-  using T = F32Cfg<BM, BN, BK, TA, TB>;
-  constexpr int WM = BM / 2, WN = BN / 2;  // wave tile (2 x 2 waves)
-  constexpr int TM = WM / 32, TN = WN / 32;
-  static_assert(TM >= 1 && TN >= 1, "wave tile below one 32x32 block");
-  auto As = reinterpret_cast<float(*)[BK][T::LA]>(lds);
-  auto Bs = reinterpret_cast<float(*)[BK][T::LB]>(lds + 2 * BK * T::LA);
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm0 = (wave >> 1) * WM;
-  const int wn0 = (wave & 1) * WN;
-
-  f32x4 ra[T::NA], rb[T::NB];
-  auto fetch = [&](int k0) {
-#pragma unroll
-    for (int p = 0; p < T::NA; p++) {
-      int c = tid + kThreads * p;
-      if (!TA) {  // stored M x K, K contiguous
-        int row = c / (BK / 4), kc = (c % (BK / 4)) * 4;
-        ra[p] = load_chunk<VEC>(A, (int64_t)(m0 + row) * lda, k0 + kc, m0 + row < M, K);
-      } else {  // stored K x M, M contiguous
-        int k = c / (BM / 4), mc = (c % (BM / 4)) * 4;
-        ra[p] = load_chunk<VEC>(A, (int64_t)(k0 + k) * lda, m0 + mc, k0 + k < K, M);
-      }
-    }
-#pragma unroll
-    for (int p = 0; p < T::NB; p++) {
-      int c = tid + kThreads * p;
-      if (!TB) {  // stored K x N, N contiguous
-        int k = c / (BN / 4), nc = (c % (BN / 4)) * 4;
-        rb[p] = load_chunk<VEC>(B, (int64_t)(k0 + k) * ldb, n0 + nc, k0 + k < K, N);
-      } else {  // stored N x K, K contiguous
-        int n = c / (BK / 4), kc = (c % (BK / 4)) * 4;
-        rb[p] = load_chunk<VEC>(B, (int64_t)(n0 + n) * ldb, k0 + kc, n0 + n < N, K);
-      }
-    }
-  };
-  auto stash = [&](int buf) {
-#pragma unroll
-    for (int p = 0; p < T::NA; p++) {
-      int c = tid + kThreads * p;
-      if (!TA) {
-        int row = c / (BK / 4), kc = (c % (BK / 4)) * 4;
-        As[buf][kc + 0][row] = ra[p].x;
-        As[buf][kc + 1][row] = ra[p].y;
-        As[buf][kc + 2][row] = ra[p].z;
-        As[buf][kc + 3][row] = ra[p].w;
-      } else {
-        int k = c / (BM / 4), mc = (c % (BM / 4)) * 4;
-        *reinterpret_cast<f32x4*>(&As[buf][k][mc]) = ra[p];
-      }
-    }
-#pragma unroll
-    for (int p = 0; p < T::NB; p++) {
-      int c = tid + kThreads * p;
-      if (!TB) {
-        int k = c / (BN / 4), nc = (c % (BN / 4)) * 4;
-        *reinterpret_cast<f32x4*>(&Bs[buf][k][nc]) = rb[p];
-      } else {
-        int n = c / (BK / 4), kc = (c % (BK / 4)) * 4;
-        Bs[buf][kc + 0][n] = rb[p].x;
-        Bs[buf][kc + 1][n] = rb[p].y;
-        Bs[buf][kc + 2][n] = rb[p].z;
-        Bs[buf][kc + 3][n] = rb[p].w;
-      }
-    }
-  };
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; i++)
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
-
-  const int nk = (K + BK - 1) / BK;
-  if (nk > 0) {
-    fetch(0);
-    stash(0);
-    __syncthreads();
-  }
-  const int kl = lane >> 5;  // which k of the pair this lane supplies
-  const int il = lane & 31;  // row of A / column of B this lane supplies
-  for (int kt = 0; kt < nk; kt++) {
-    const int cur = kt & 1;
-    const bool more = kt + 1 < nk;
-    if (more) fetch((kt + 1) * BK);  // in flight while the slab below is consumed
-#pragma unroll
-    for (int s = 0; s < BK / 2; s++) {
-      float a[TM], b[TN];
-#pragma unroll
-      for (int i = 0; i < TM; i++) a[i] = As[cur][2 * s + kl][wm0 + i * 32 + il];
-#pragma unroll
-      for (int j = 0; j < TN; j++) b[j] = Bs[cur][2 * s + kl][wn0 + j * 32 + il];
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    if (more) stash(cur ^ 1);
-    __syncthreads();
-  }
-
-  // D layout of a 32x32 block: lane l holds column l % 32 and rows
-  // 8*(r/4) + 4*(l/32) + r%4 for r = 0..15
-#pragma unroll
-  for (int i = 0; i < TM; i++)
-#pragma unroll
-    for (int j = 0; j < TN; j++) {
-      const int col = n0 + wn0 + j * 32 + il;
-      if (col >= N) continue;
-#pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const int row = m0 + wm0 + i * 32 + 8 * (r >> 2) + 4 * kl + (r & 3);
-        if (row < M) C[(int64_t)row * ldc + col] = acc[i][j][r];
-      }
-    }
-}
-
-// ===========================================================================
-// FP32 GEMM tile, asynchronous-ring schedule.
-// Each operand's slab (16 values of k by BM or BN values of m or n) is staged
-// in the orientation it is stored in, so every 16-byte chunk goes from global
-// memory to LDS unchanged (global_load_lds: lane i's 16 bytes land at the
-// wave-uniform base + 16 i; the swizzle below is applied on the global side by
-// choosing which chunk each lane fetches):
-//   rows along k (A as stored, B read through transpose): MN rows of 4 chunks;
-//     chunk p of row r holds logical chunk p ^ ((r >> 2) & 3), so the 16 rows
-//     one 16-lane group reads at one logical chunk fall in 16 distinct 16-byte
-//     slots of a 256-byte (64-bank) LDS line;
-//   rows along m or n (A read through transpose, B as stored): 16 rows of MN/4
-//     chunks; chunk p of row k holds logical chunk p ^ (8 ((k >> 3) & 1)), so
-//     rows k and k + 8, which the two halves of a wave read together, use
-//     different banks.
-// The 32x32x2 MFMA's k pair is (k, k + 8) at step t = 0..7 of a slab (lane
+// accumulators; each slab is staged in LDS (toMem(Local)); zip |> map(*) |>
+// reduce(+) is v_mfma_f32_32x32x2_f32; join . join is the guarded row-major
+// store.  Operands may be read through transpose (TA, TB) without copies.
+//
+// Slabs flow global -> LDS through a ring of STAGES buffers by asynchronous
+// copies (global_load_lds: lane i's bytes land at the wave-uniform base + its
+// size * i; no registers hold data in flight), STAGES - 1 slabs ahead.  Each
+// operand's slab (BK values of k by BM or BN values of m or n) is staged in the
+// orientation it is stored in:
+//   rows along k (A as stored, B read through transpose): MN rows of BK/4
+//     16-byte chunks; the chunks of a row are XOR-swizzled by a key of the row, so
+//     the 16 rows one 16-lane group reads at one logical chunk fall in 16
+//     distinct 16-byte slots of a 256-byte (64-bank) LDS line;
+//   rows along m or n (A read through transpose, B as stored): BK rows of MN/4
+//     chunks; with whole 256-byte lines (MN a multiple of 64), chunk p of row k
+//     holds logical chunk p ^ (8 ((k >> 3) & 1)), so rows k and k + 8, which the
+//     two halves of a wave read together, use different banks.
+// The swizzles are applied on the global side, by choosing what each lane
+// fetches.  VEC copies move 16 bytes per lane and need 16-byte aligned rows of
+// whole chunks; otherwise each lane copies one value (4 bytes, any alignment)
+// to the same place: four times the copies and the same MFMAs and LDS reads.
+// Register staging through guarded value-by-value loads, which such storage took
+// before, ran 1000 x 1531 x 777 in 58 us and 3001^3 in 1188 us, where an aligned
+// neighbour took 45 and 839.
+// The 32x32x2 MFMA's k pair is (k, k + 8) at step t = 0..7 of 16 values of k (lane
 // half kl supplies k = 8 kl + t): the sum over a slab is the same, and a lane
 // of a rows-along-k operand then reads its values of four steps with one
 // 16-byte LDS read.
-// Ragged M and N: rows (chunks) past the edge are fetched from the last valid
-// row (chunk) and only feed outputs that are not stored.  K is a whole number
-// of slabs (checked by the launcher), so no k beyond K is ever added.
-template <int MN, bool ALONG_K>
+// Ragged M and N: rows (chunks, values) past the edge are fetched from the last
+// valid one and only feed outputs that are not stored.  Ragged K: in the last
+// slab, what lies beyond K is copied from a page of zeros, for both operands.
+// ===========================================================================
+__device__ __align__(16) static float g_zero_chunk[4];  // never written: zeros
+
+template <int MN, bool ALONG_K, int BK, bool VEC>
 struct AsyncSlab {
-  static constexpr int CHUNKS = MN * 4;  // 16-byte chunks of a 16 x MN slab
-  // source of slab chunk `idx` for slab 0, and the advance per slab
-  __device__ static const float* src(const float* X, int64_t ld, int mn0, int mn_total, int idx,
-                                     int64_t& step) {
-    if (ALONG_K) {
-      const int r = idx >> 2, c = (idx & 3) ^ ((r >> 2) & 3);
-      const int row = min(mn0 + r, mn_total - 1);
-      step = 16;
-      return X + (int64_t)row * ld + 4 * c;
-    }
-    const int k = idx / (MN / 4), c = (idx % (MN / 4)) ^ (8 * ((k >> 3) & 1));
-    const int col = min(mn0 + 4 * c, mn_total - 4);
-    step = 16 * ld;
-    return X + (int64_t)k * ld + col;
+  static_assert((BK == 16 || BK == 32 || BK == 64 || BK == 128) && MN % 32 == 0, "slab shape");
+  static constexpr int CHUNKS = MN * BK / 4;                 // 16-byte chunks of a slab
+  static constexpr int COPIES = CHUNKS * (VEC ? 1 : 4) / 64;  // wave copies of a slab
+  static constexpr int COPY_BYTES = VEC ? 1024 : 256;
+  static constexpr int CPR = BK / 4;  // chunks per row along k
+  __device__ static int key(int r) {
+    return BK == 16 ? (r >> 2) & 3 : BK == 32 ? (r >> 1) & 7 : r & 15;
   }
-  // values at k = 8 kl + 4 h + s (s = 0..3) of row/column r of the slab
-  __device__ static f32x4 frag(const f32x4* slab, int r, int kl, int h) {
-    if (ALONG_K) return slab[r * 4 + ((2 * kl + h) ^ ((r >> 2) & 3))];
+  // rows along m or n; rows that are not whole 256-byte lines stay as they are
+  __device__ static int key_mn(int k) { return MN % 64 == 0 ? 8 * ((k >> 3) & 1) : 0; }
+  // index of this lane's source in wave copy i of a slab, from the slab's first
+  // value of the tile (row or column mn0), and the (first) k it holds
+  __device__ static int64_t index(int64_t ld, int mn0, int mn_total, int i, int lane, int& k) {
+    const int d = i * 64 + lane, ch = VEC ? d : d >> 2, e = VEC ? 0 : d & 3;
+    if (ALONG_K) {
+      const int r = ch / CPR;
+      k = 4 * ((ch % CPR) ^ key(r)) + e;
+      return min(r, mn_total - 1 - mn0) * ld + k;
+    }
+    k = ch / (MN / 4);
+    const int col = 4 * ((ch % (MN / 4)) ^ key_mn(k)) + e;
+    return k * ld + min(col, mn_total - mn0 - (VEC ? 4 : 1));
+  }
+  __device__ static void copy(const float* base, uint32_t off, void* to) {
+    if (VEC)
+      async::copy16_at(base, off, to);
+    else
+      async::copy4_at(base, off, to);
+  }
+  // by 64-bit address, zeros when !valid
+  __device__ static void copy_any(const float* from, bool valid, void* to) {
+    if (VEC)
+      async::copy16(valid ? from : g_zero_chunk, to);
+    else
+      async::copy4(valid ? from : g_zero_chunk, to);
+  }
+  // values at k = 16 u + 8 kl + 4 h + s (s = 0..3) of row/column r of the slab
+  __device__ static f32x4 frag(const f32x4* slab, int r, int kl, int u, int h) {
+    if (ALONG_K) return slab[r * CPR + ((4 * u + 2 * kl + h) ^ key(r))];
     const float* f = reinterpret_cast<const float*>(slab);
     f32x4 v;
 #pragma unroll
     for (int s = 0; s < 4; s++) {
-      const int k = 8 * kl + 4 * h + s;
-      v[s] = f[k * MN + 4 * ((r >> 2) ^ (8 * ((k >> 3) & 1))) + (r & 3)];
+      const int k = 16 * u + 8 * kl + 4 * h + s;
+      v[s] = f[k * MN + 4 * ((r >> 2) ^ key_mn(k)) + (r & 3)];
     }
     return v;
   }
 };
 
-template <int BM, int BN, int STAGES>
-struct F32AsyncCfg {
-  static constexpr int SL = BM * 4 + BN * 4;   // chunks per ring stage: A slab, then B slab
+// A tile: BM x BN outputs in GM x GN waves, slabs of BK values of k in a ring of
+// STAGES, KG groups of waves that share every slab's k.
+template <int BM_, int BN_, int BK_, int STAGES_, int GM_, int GN_, int KG_>
+struct F32Cfg {
+  static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_, GM = GM_, GN = GN_, KG = KG_;
+  static constexpr int WAVES = GM * GN * KG, THREADS = 64 * WAVES;
+  static constexpr int TM = BM / GM / 32, TN = BN / GN / 32;  // 32 x 32 blocks of a wave
+  static_assert(TM * GM * 32 == BM && TN * GN * 32 == BN, "whole blocks per wave");
+  static constexpr int SL = (BM + BN) * BK / 4;  // chunks per ring stage: A slab, then B slab
   static constexpr int LDS_CHUNKS = STAGES * SL;
 };
 
-// The operands' storage allows the asynchronous ring: 16-byte chunks and
-// whole slabs of 16 k (K > 0, K % 16 == 0, 16-byte aligned rows, and the rows
-// along m or n whole chunks).
-__host__ __device__ inline bool f32_async_eligible(const float* A, int64_t lda, const float* B,
-                                                   int64_t ldb, int M, int N, int K, bool ta,
-                                                   bool tb) {
-  return K > 0 && K % 16 == 0 && M > 0 && N > 0 && ((uintptr_t)A & 15) == 0 &&
-         ((uintptr_t)B & 15) == 0 && lda % 4 == 0 && ldb % 4 == 0 && (!ta || M % 4 == 0) &&
-         (tb || N % 4 == 0);
+// Below this leading dimension a copy's byte offset in a slab (up to 255 rows) fits
+// 32 bits, and copies take a uniform base and that offset; longer rows are
+// addressed with 64 bits, lane by lane.
+constexpr int64_t kF32OffsetLd = (int64_t)1 << 22;
+
+// The operands' storage allows 16-byte copies: 16-byte aligned rows that are
+// whole chunks.
+__host__ __device__ inline bool f32_vec(const float* A, int64_t lda, const float* B, int64_t ldb,
+                                        int M, int N, int K, bool ta, bool tb) {
+  return ((uintptr_t)A & 15) == 0 && ((uintptr_t)B & 15) == 0 && lda % 4 == 0 && ldb % 4 == 0 &&
+         (ta ? M : K) % 4 == 0 && (tb ? K : N) % 4 == 0;
 }
 
-// C[m0:m0+BM, n0:n0+BN] = A B with the whole 256-thread workgroup (2 x 2
-// waves); lds holds F32AsyncCfg::LDS_CHUNKS 16-byte chunks.  No copy is in
-// flight into lds when it returns.
-template <int BM, int BN, int STAGES, bool TA, bool TB>
-__device__ __forceinline__ void gemm_f32_async_tile(float* __restrict__ C, int64_t ldc,
-                                                    const float* __restrict__ A, int64_t lda,
-                                                    const float* __restrict__ B, int64_t ldb,
-                                                    int M, int N, int K, int m0, int n0,
-                                                    f32x4* lds_base) {
-  using SA = AsyncSlab<BM, !TA>;
-  using SB = AsyncSlab<BN, TB>;
-  constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
-  constexpr int SL = F32AsyncCfg<BM, BN, STAGES>::SL;
-  constexpr int NCP = SL / kThreads;           // copies per thread per slab
-  static_assert(SL % kThreads == 0 && SA::CHUNKS % 64 == 0, "a copy is all A or all B");
-  static_assert(STAGES >= 3, "ring of at least three slabs");
-  static_assert(TM >= 1 && TN >= 1 && BM >= 64 && BN >= 64, "tile of at least 64 x 64");
+// C[m0:m0+BM, n0:n0+BN] = A B with the whole workgroup of T::THREADS: KG groups
+// of GM x GN waves, each group summing its share of every slab's k (the groups'
+// tiles are added at the end, group 0 first).  lds holds T::LDS_CHUNKS 16-byte
+// chunks.  No copy is in flight into lds when it returns.
+template <typename T, bool TA, bool TB, bool VEC>
+__device__ __forceinline__ void gemm_f32_tile(float* __restrict__ C, int64_t ldc,
+                                              const float* __restrict__ A, int64_t lda,
+                                              const float* __restrict__ B, int64_t ldb, int M,
+                                              int N, int K, int m0, int n0, f32x4* lds_base) {
+  constexpr int BM = T::BM, BN = T::BN, BK = T::BK, STAGES = T::STAGES, KG = T::KG;
+  constexpr int TM = T::TM, TN = T::TN, SL = T::SL, NW = T::WAVES;
+  using SA = AsyncSlab<BM, !TA, BK, VEC>;
+  using SB = AsyncSlab<BN, TB, BK, VEC>;
+  // copies of a slab, A's then B's; copy j of wave w is number j NW + w, or the
+  // last one again where the waves do not share them evenly
+  constexpr int COPIES = SA::COPIES + SB::COPIES, NCP = (COPIES + NW - 1) / NW;
+  static_assert(BK % (16 * KG) == 0, "the groups share the k evenly");
+  static_assert(KG == 1 || (KG - 1) * BM * BN / 4 <= T::LDS_CHUNKS, "the groups' tiles fit the ring");
+  static_assert(STAGES >= 2 && (STAGES - 1) * NCP < 64, "ring and its vmcnt");
   auto lds = reinterpret_cast<f32x4(*)[SL]>(lds_base);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm0 = (wave >> 1) * WM, wn0 = (wave & 1) * WN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = wave / (T::GM * T::GN), wing = wave % (T::GM * T::GN);
+  const int wm0 = wing / T::GN * (32 * TM), wn0 = wing % T::GN * (32 * TN);
 
-  const float* src[NCP];
-  int64_t step[NCP];
+  // wave-uniform for the compiler too (in a batch they come from memory)
+  lda = async::uniform(lda);
+  ldb = async::uniform(ldb);
+  K = __builtin_amdgcn_readfirstlane(K);
+  auto number = [&](int j) { return min(j * NW + wave, COPIES - 1); };
+  auto is_a = [&](int j) {  // known at compile time where the waves share A's copies evenly
+    return (j + 1) * NW <= SA::COPIES || (j * NW < SA::COPIES && number(j) < SA::COPIES);
+  };
+  auto index = [&](int j, int ln, int& k) {
+    return is_a(j) ? SA::index(lda, m0, M, number(j), ln, k)
+                   : SB::index(ldb, n0, N, number(j) - SA::COPIES, ln, k);
+  };
+  uint32_t off[NCP];
 #pragma unroll
   for (int j = 0; j < NCP; j++) {
-    const int slot = (wave * NCP + j) * 64 + lane;
-    src[j] = slot < SA::CHUNKS ? SA::src(A, lda, m0, M, slot, step[j])
-                               : SB::src(B, ldb, n0, N, slot - SA::CHUNKS, step[j]);
+    int k;
+    off[j] = 4 * (uint32_t)index(j, lane, k);
   }
-  const int nk = K / 16;
-  auto issue = [&](int kt) {  // slab min(kt, nk - 1) -> ring stage kt % STAGES
-    const int64_t kk = kt < nk ? kt : nk - 1;
-    const int buf = kt % STAGES;
+  const int64_t step_a = TA ? (int64_t)BK * lda : BK, step_b = TB ? BK : (int64_t)BK * ldb;
+  const int nk = (K + BK - 1) / BK, krem = K - (nk - 1) * BK;
+  const bool wide = lda >= kF32OffsetLd || ldb >= kF32OffsetLd;
+  // the next slab to copy (its first value in the tile's first row or column);
+  // past the last slab the last one is copied again, into a stage nothing reads
+  const float* pa = async::uniform(A + (TA ? m0 : (int64_t)m0 * lda));
+  const float* pb = async::uniform(B + (TB ? (int64_t)n0 * ldb : n0));
+  int next = 0, stage = 0;  // that slab and its ring stage
+  auto copies = [&](auto from, auto to) {  // copies from .. to - 1 of that slab by this wave
+    char* dst = reinterpret_cast<char*>(&lds[stage][0]);
+    if (wide || (next >= nk - 1 && krem < BK)) {
+      const int kend = next >= nk - 1 ? krem : BK;
+      int ln = lane;  // opaque: what this computes stays out of the loop's registers
+      asm volatile("" : "+v"(ln));
 #pragma unroll
-    for (int j = 0; j < NCP; j++) async::copy16(src[j] + kk * step[j], &lds[buf][(wave * NCP + j) * 64]);
+      for (int j = from; j < to; j++) {
+        int k;
+        const int64_t at = index(j, ln, k);
+        SA::copy_any((is_a(j) ? pa : pb) + at, k < kend, dst + number(j) * SA::COPY_BYTES);
+      }
+      return;
+    }
+#pragma unroll
+    for (int j = from; j < to; j++)
+      if (is_a(j))  // wave-uniform
+        SA::copy(pa, off[j], dst + number(j) * SA::COPY_BYTES);
+      else
+        SB::copy(pb, off[j], dst + number(j) * SB::COPY_BYTES);
+  };
+  auto advance = [&] {
+    pa += next < nk - 1 ? step_a : 0;
+    pb += next < nk - 1 ? step_b : 0;
+    next++;
+    stage = stage == STAGES - 1 ? 0 : stage + 1;
   };
 
   f32x16 acc[TM][TN];
@@ -311,33 +229,90 @@ __device__ __forceinline__ void gemm_f32_async_tile(float* __restrict__ C, int64
       for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
 
   const int kl = lane >> 5, il = lane & 31;
+  // A group's share of a slab is NS steps of 8 k.  A step's fragments are read
+  // while the step before runs its MFMAs, across slabs too: the barrier that
+  // publishes slab kt + 1 stands before the last step of slab kt, whose
+  // fragments are in registers by then, so it also frees the stage of slab kt for
+  // the copies of slab kt + STAGES, which the next slab's steps issue.  (With
+  // the barrier at the start of a slab every wave waited out an LDS latency
+  // there: 64 x 64 tiles took 1700 cycles for the 1024 of a slab's MFMAs.)
+  constexpr int NS = BK / 8 / KG;
+  static_assert(NS % 2 == 0, "the fragment sets alternate by step");
+  f32x4 a[2][TM], b[2][TN];
+  int buf = 0;
+  auto read = [&](int at, int st) {
+    const f32x4* As = &lds[at][0];
+    const f32x4* Bs = &lds[at][SA::CHUNKS];
 #pragma unroll
-  for (int st = 0; st < STAGES - 1; st++) issue(st);
-  for (int kt = 0; kt < nk; kt++) {
-    const int buf = kt % STAGES;
-    async::wait_vmcnt<(STAGES - 2) * NCP>();  // this wave's copies of slab kt have landed
-    async::wait_lgkmcnt0();                   // and its reads of slab kt - 1 are done
-    async::barrier();                         // so every copy of slab kt is visible and
-    issue(kt + STAGES - 1);                   // the stage of slab kt - 1 can be refilled
-    const f32x4* As = &lds[buf][0];
-    const f32x4* Bs = &lds[buf][SA::CHUNKS];
+    for (int i = 0; i < TM; i++)
+      a[st & 1][i] = SA::frag(As, wm0 + 32 * i + il, kl, group * (NS / 2) + (st >> 1), st & 1);
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
-      f32x4 a[TM], b[TN];
+    for (int j = 0; j < TN; j++)
+      b[st & 1][j] = SB::frag(Bs, wn0 + 32 * j + il, kl, group * (NS / 2) + (st >> 1), st & 1);
+  };
+  if (nk > 0) {
 #pragma unroll
-      for (int i = 0; i < TM; i++) a[i] = SA::frag(As, wm0 + 32 * i + il, kl, h);
-#pragma unroll
-      for (int j = 0; j < TN; j++) b[j] = SB::frag(Bs, wn0 + 32 * j + il, kl, h);
-#pragma unroll
-      for (int s = 0; s < 4; s++)
-#pragma unroll
-        for (int i = 0; i < TM; i++)
-#pragma unroll
-          for (int j = 0; j < TN; j++)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][s], b[j][s], acc[i][j], 0, 0, 0);
+    for (int st = 0; st < STAGES; st++) {
+      copies(std::integral_constant<int, 0>{}, std::integral_constant<int, NCP>{});
+      advance();
     }
+    async::wait_vmcnt<(STAGES - 1) * NCP>();  // slab 0 has landed
+    async::barrier();
+    read(0, 0);
   }
-  async::wait_vmcnt<0>();  // the clamped copies past the last slab land before the exit
+  for (int kt = 0; kt < nk; kt++) {
+    const int after = buf == STAGES - 1 ? 0 : buf + 1;
+    auto steps = [&](auto self, auto st_tag) {
+      constexpr int st = decltype(st_tag)::value;
+      if constexpr (st < NS) {
+        if constexpr (st == NS - 1) {
+          async::wait_vmcnt<(STAGES - 2) * NCP>();  // this wave's copies of slab kt + 1 landed
+          async::wait_lgkmcnt0();                   // and it has read all of slab kt
+          async::barrier();
+          read(after, 0);
+        } else {
+          read(buf, st + 1);
+          if (kt > 0)
+            copies(std::integral_constant<int, NCP * st / (NS - 1)>{},
+                   std::integral_constant<int, NCP*(st + 1) / (NS - 1)>{});
+        }
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+#pragma unroll
+          for (int i = 0; i < TM; i++)
+#pragma unroll
+            for (int j = 0; j < TN; j++)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[st & 1][i][s], b[st & 1][j][s],
+                                                               acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        self(self, std::integral_constant<int, st + 1>{});
+      }
+    };
+    steps(steps, std::integral_constant<int, 0>{});
+    if (kt > 0) advance();
+    buf = after;
+  }
+  async::wait_vmcnt<0>();  // the copies past the last slab land before the exit
+
+  if constexpr (KG > 1) {
+    async::wait_lgkmcnt0();
+    __syncthreads();  // every wave is done with the ring
+    constexpr int TILE = TM * TN * 16 * 64;  // values of a wave's tile
+    constexpr int GROUP = T::GM * T::GN * TILE;
+    float* part = reinterpret_cast<float*>(lds_base) + wing * TILE + lane;
+    if (group > 0) {
+#pragma unroll
+      for (int e = 0; e < TM * TN * 16; e++)
+        part[(group - 1) * GROUP + e * 64] = acc[e / 16 / TN][e / 16 % TN][e % 16];
+    }
+    __syncthreads();
+    if (group > 0) return;
+#pragma unroll
+    for (int g = 1; g < KG; g++)
+#pragma unroll
+      for (int e = 0; e < TM * TN * 16; e++)
+        acc[e / 16 / TN][e / 16 % TN][e % 16] += part[(g - 1) * GROUP + e * 64];
+  }
 
   // join . join: D layout of a 32x32 block, lane l holds column l % 32 and rows
   // 8 (r / 4) + 4 (l / 32) + r % 4; stores guarded on edge tiles only
@@ -554,9 +529,6 @@ struct StencilCfg {
 template <int K, int TY>
 using StencilRegs = f32x4[StencilCfg<K, TY>::PER];  // one thread's share of a halo tile
 
-// a 16-byte vector of floats that may sit at any 4-byte boundary (gfx950 runs
-// global memory in unaligned-access mode: one dwordx4 access either way)
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // Global -> registers: the (TY + 2R) x (256 + 8) halo tile of output rows
 // [y0, y0 + TY), columns [x0, x0 + 256), with pad2D applied as index remapping.

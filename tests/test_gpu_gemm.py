@@ -189,6 +189,58 @@ MODES = {"bf16": oracle.MODE_BF16, "bf16x3": oracle.MODE_BF16X3, "bf16x6": oracl
          "fp8": oracle.MODE_FP8}
 
 
+@pytest.mark.parametrize("ops", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (32, 96, 64), (33, 97, 65), (95, 63, 127),
+                                   (257, 130, 33), (64, 64, 1040), (129, 65, 1100)])
+def test_f32_tile_edges_integer_exact(rise, ops, off, M, N, K):
+    # every FP32 tile at, below and above its edges and slab lengths, with rows of
+    # whole 16-byte chunks and rows at an odd 4-byte offset (value-by-value copies);
+    # integer inputs make every order of additions exact
+    import torch
+
+    g = ri.rng(M + 5 * N + 11 * K + off)
+    A, B = ri.integer_matrix(g, M, K, bound=3), ri.integer_matrix(g, K, N, bound=3)
+    exact = (A.astype(np.int64) @ B.astype(np.int64)).astype(np.float32)
+
+    def placed(x, t):  # stored (transposed) rows of 4-multiples, NaN around them, shifted by off
+        x = np.ascontiguousarray(x.T) if t else x
+        ld = (x.shape[1] + 3) // 4 * 4 + off
+        buf = torch.full((x.shape[0] * ld + 8,), float("nan"), device="cuda")
+        v = buf[off:off + x.shape[0] * ld].view(x.shape[0], ld)
+        v[:, :x.shape[1]] = dev(x)
+        return v, ld
+
+    (dA, lda), (dB, ldb) = placed(A, ops[0]), placed(B, ops[1])
+    for tile in rise.rise_gemm_tiles("f32"):
+        print(f"gemm f32 edges {M}x{N}x{K} ops={ops} off={off} tile={tile}", flush=True)
+        C = torch.full((M, N), float("nan"), device="cuda")
+        rise.rise_gemm(C, dA, dB, M, N, K, lda=lda, ldb=ldb, ldc=N, opA=int(ops[0]),
+                       opB=int(ops[1]), mode="f32", tile=tile)
+        assert np.array_equal(host(C), exact), tile
+
+
+@pytest.mark.parametrize("trans", [False, True])
+def test_f32_long_rows_integer_exact(rise, trans):
+    # leading dimensions whose byte offsets within a tile exceed 32 bits (64 rows
+    # of 2^24 + 4 values): copies addressed lane by lane
+    import torch
+
+    M, N, K, ld = 64, 40, 64, 2 ** 24 + 4
+    g = ri.rng(77 + trans)
+    A, B = ri.integer_matrix(g, M, K, bound=3), ri.integer_matrix(g, K, N, bound=3)
+    exact = (A.astype(np.int64) @ B.astype(np.int64)).astype(np.float32)
+    st = np.ascontiguousarray(A.T) if trans else A
+    buf = torch.zeros(64 * ld, device="cuda")
+    buf.view(64, ld)[:, :64] = dev(st)
+    for tile in rise.rise_gemm_tiles("f32"):
+        print(f"gemm f32 long rows trans={trans} tile={tile}", flush=True)
+        C = torch.full((M, N), float("nan"), device="cuda")
+        rise.rise_gemm(C, buf, dev(B), M, N, K, lda=ld, ldb=N, ldc=N, opA=int(trans), mode="f32",
+                       tile=tile)
+        assert np.array_equal(host(C), exact), tile
+
+
 @pytest.mark.parametrize("mode", list(MODES))
 def test_modes_integer_exact(rise, mode):
     g = ri.rng(21)
