@@ -3,22 +3,21 @@ HIP kernels (rise_gemm / rise_gemm_backward, rise_stencil2d /
 rise_stencil2d_backward); torch only supplies device memory and the stream."""
 import torch
 
+# imported at the end of the package's __init__, where these are defined
+from . import (conv2d, conv2d_backward, gemm, gemm_backward, stencil2d, stencil2d_backward)
+
 
 class RiseGemmFn(torch.autograd.Function):
     """C = A . B (FP32 row-major), gradients dA = dC B^T, dB = A^T dC."""
 
     @staticmethod
     def forward(ctx, A, B, mode="f32"):
-        from . import gemm
-
         ctx.save_for_backward(A, B)
         ctx.mode = mode
         return gemm(A, B, mode=mode)
 
     @staticmethod
     def backward(ctx, dC):
-        from . import gemm_backward
-
         A, B = ctx.saved_tensors
         # the backward products read FP32 operands; bfloat16 operands (mode "bf16")
         # widen exactly, and each gradient is returned in its operand's type
@@ -37,16 +36,12 @@ class RiseStencil2dFn(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, img, w, pad="clamp"):
-        from . import stencil2d
-
         ctx.save_for_backward(img, w)
         ctx.pad = pad
         return stencil2d(img, w, pad=pad)
 
     @staticmethod
     def backward(ctx, dOut):
-        from . import stencil2d_backward
-
         img, w = ctx.saved_tensors
         dIn, dW = stencil2d_backward(dOut, img, w, pad=ctx.pad,
                                      need_din=ctx.needs_input_grad[0],
@@ -59,15 +54,11 @@ class RiseConv2dFn(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, x, w):
-        from . import conv2d
-
         ctx.save_for_backward(x, w)
         return conv2d(x, w, pad="zero")
 
     @staticmethod
     def backward(ctx, dOut):
-        from . import conv2d_backward
-
         x, w = ctx.saved_tensors
         dIn, dW = conv2d_backward(dOut.to(torch.bfloat16), x, w, pad="zero",
                                   need_din=ctx.needs_input_grad[0],
