@@ -75,20 +75,33 @@ __device__ __forceinline__ T* uniform(T* p) {
   return (T*)(__attribute__((address_space(1))) T*)(uint64_t)uniform((int64_t)(uint64_t)p);
 }
 
-// The same copies from a wave-uniform base plus a 32-bit byte offset per lane:
-// no vector arithmetic per copy when the base advances by a uniform step.
-__device__ __forceinline__ void copy16_at(const void* base, uint32_t off, void* lds_base) {
+// LDS byte address of a pointer into LDS, wave-uniform.
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const char*)p));
+}
+
+// The same copies to an LDS byte address, from a wave-uniform base plus a 32-bit
+// byte offset per lane: no vector arithmetic per copy when the base advances by a
+// uniform step.
+__device__ __forceinline__ void copy16_at(const void* base, uint32_t off, uint32_t to) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  const uint32_t to = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)lds_base));
   asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(to) : "memory");
 #endif
 }
-__device__ __forceinline__ void copy4_at(const void* base, uint32_t off, void* lds_base) {
+__device__ __forceinline__ void copy4_at(const void* base, uint32_t off, uint32_t to) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  const uint32_t to = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)lds_base));
   asm volatile("global_load_lds_dword %0, %1" ::"v"(off), "s"(base), "{m0}"(to) : "memory");
+#endif
+}
+__device__ __forceinline__ void copy16_from(const void* src, uint32_t to) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(to) : "memory");
+#endif
+}
+__device__ __forceinline__ void copy4_from(const void* src, uint32_t to) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("global_load_lds_dword %0, off" ::"v"(src), "{m0}"(to) : "memory");
 #endif
 }
 

@@ -80,7 +80,7 @@ using F32Tile = tiles::F32Cfg<BM, BN, kF32BK, 3, 2, 2, 1>;
 // the largest GEMM tile of any kind
 constexpr int kGemmLdsBytes =
     cmax(16 * F32Tile<128, 128>::LDS_CHUNKS,
-         16 * tiles::Bf16Cfg<128, 128, kBf16BK>::LDS_CHUNKS);
+         16 * tiles::Bf16StagedCfg<128, 128, kBf16BK>::LDS_CHUNKS);
 static_assert(kGemmLdsBytes * kGemmOccupancy <= 160 * 1024, "LDS of the resident workgroups");
 
 // A descriptor address as a pointer into global memory: built from the integer
@@ -96,12 +96,12 @@ __device__ __noinline__ void item_f32(const Desc& d, int tm, int tn, char* lds) 
   const float* A = gptr<const float>(d.a);
   const float* B = gptr<const float>(d.b);
   float* C = gptr<float>(d.out);
-  if (tiles::f32_vec(A, d.lda, B, d.ldb, d.M, d.N, d.K, false, TB))
-    tiles::gemm_f32_tile<F32Tile<BM, BN>, false, TB, true>(
+  if (tiles::whole_chunks(A, d.lda, B, d.ldb, d.M, d.N, d.K, false, TB))
+    tiles::gemm_ring_tile<F32Tile<BM, BN>, false, TB, true>(
         C, d.ldc, A, d.lda, B, d.ldb, d.M, d.N, d.K, tm * BM, tn * BN,
         reinterpret_cast<f32x4*>(lds));
   else
-    tiles::gemm_f32_tile<F32Tile<BM, BN>, false, TB, false>(
+    tiles::gemm_ring_tile<F32Tile<BM, BN>, false, TB, false>(
         C, d.ldc, A, d.lda, B, d.ldb, d.M, d.N, d.K, tm * BM, tn * BN,
         reinterpret_cast<f32x4*>(lds));
 }

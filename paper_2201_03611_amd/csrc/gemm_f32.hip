@@ -2,7 +2,7 @@
 //   gemm_f32_kernel: one workgroup per BM x BN output tile, tiles visited in an
 //     XCD-contiguous, grouped order so that concurrently running tiles share A and
 //     B panels in their XCD's L2; the K loop (reduceSeq over split(BK) slabs, each
-//     staged in LDS: toMem(Local), paper Sec. V-B/C) is tiles::gemm_f32_tile;
+//     staged in LDS: toMem(Local), paper Sec. V-B/C) is tiles::gemm_ring_tile;
 //   gemm_f32_split_kernel: one workgroup per 32 x 32 output tile whose waves take
 //     alternate slabs of K and add their sums at the end, for small products.
 #include <algorithm>
@@ -22,7 +22,7 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES / 4) void gemm_f32_kernel(
   __shared__ f32x4 lds[T::LDS_CHUNKS];
   int tm, tn;
   grouped_tile(xcd_contiguous(blockIdx.x, gridDim.x), tiles_m, tiles_n, 8, tm, tn);
-  tiles::gemm_f32_tile<T, TA, TB, VEC>(C, ldc, A, lda, B, ldb, M, N, K, tm * T::BM, tn * T::BN, lds);
+  tiles::gemm_ring_tile<T, TA, TB, VEC>(C, ldc, A, lda, B, ldb, M, N, K, tm * T::BM, tn * T::BN, lds);
 }
 
 // Few output tiles: a workgroup of NW waves owns a 32 x 32 tile, and wave w sums
@@ -202,7 +202,7 @@ rise_tile gemm_f32_default_tile(int M, int N, int K) {
 }
 
 rise_status launch_gemm_f32(const GemmF32Args& a, const rise_tile& t, hipStream_t s) {
-  const bool vec = tiles::f32_vec(a.A, a.lda, a.B, a.ldb, a.M, a.N, a.K, a.ta, a.tb);
+  const bool vec = tiles::whole_chunks(a.A, a.lda, a.B, a.ldb, a.M, a.N, a.K, a.ta, a.tb);
 #define RISE_F32_TILE(BM, BN, BK, ...)                                         \
   if (t.bm == BM && t.bn == BN && t.bk == BK) {                                \
     using T = tiles::F32Cfg<BM, BN, BK, __VA_ARGS__>;                          \

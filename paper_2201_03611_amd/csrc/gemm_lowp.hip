@@ -1,15 +1,17 @@
 // Reduced-precision GEMM on the gfx950 matrix cores, FP32 accumulation.
 //
-// The operands arrive prepared (prep.hip): A as Mp x Kp rows and B as Np x Kp
-// rows of transpose(B), K contiguous and zero padded to whole tiles, so the K
-// loop needs no bounds checks (zero padding adds exact zeros to the sum).
+// The split and FP8 operands arrive prepared (prep.hip): A as Mp x Kp rows and B as
+// Np x Kp rows of transpose(B), K contiguous and zero padded to whole tiles, so
+// the K loop needs no bounds checks (zero padding adds exact zeros to the sum).
+// BF16 runs the ring of tiles.h, on prepared operands or in place on the caller's
+// bf16 storage (gemm_bf16_kernel below).
 //
 // Pattern -> hardware mapping (paper Sec. IV-B/C, V-C):
 //   split(BM) / split(BN) + mapWorkGroup -> one workgroup per BM x BN tile of C
-//   mapLocal                             -> 2 x 2 waves, each (BM/2) x (BN/2)
+//   mapLocal                             -> a grid of waves, 32 x 32 blocks each
 //   split(BK) + reduceSeq(Private)       -> K loop, accumulators in registers
-//   toMem(Local)                         -> double-buffered LDS slabs; 16-byte
-//                                           chunks XOR-swizzled by row so the
+//   toMem(Local)                         -> LDS slabs; 16-byte chunks
+//                                           XOR-swizzled by row so the
 //                                           fragment reads are conflict free
 //   zip |> map(*) |> reduce(+)           -> v_mfma_f32_32x32x16_bf16, or
 //                                           v_mfma_scale_f32_32x32x64_f8f6f4
@@ -20,6 +22,7 @@
 //                                           registers: no extra pass over C.
 #include "async_copy.h"
 #include "gemm_lowp.h"
+#include "tiles.h"
 
 #include <type_traits>
 
@@ -393,7 +396,7 @@ __device__ __forceinline__ void copy4_to_lds(const void* src, void* lds_base) {
 }
 
 // ---------------------------------------------------------------------------
-// 256 x 256 tiles over K-blocked operands, every format.  A K-blocked part
+// 256 x 256 tiles over K-blocked operands, split formats and FP8.  A K-blocked part
 // holds the K block b of row r (KBB bytes: 64 FP8 codes, 32 bf16 values, or 16
 // for the split formats) at (b * rows + r) * KBB, so the blocks of consecutive
 // rows are contiguous (an FP8 row's two scale bytes of a block sit together in
@@ -612,17 +615,61 @@ __global__ __launch_bounds__(kThreads, 1) void packed_kblock_kernel(
   store_tile<TM, TN>(C, ldc, M, N, m0 + wm0, n0 + wn0, lane, acc);
 }
 
+// BF16 operands in row-major storage, as the caller holds them or as prepared: the
+// ring of tiles.h with bf16 slabs.  Eight waves a workgroup (sixteen where K is
+// shared four ways), one barrier per slab, copies and fragment reads placed
+// between the MFMAs.  8192^3: 858 us, matrix cores busy 80 % of 1.31 M cycles; it
+// replaced the register-staged kernel (1156 us with preparation) and, for bf16,
+// the K-blocked one (1.77 M cycles).  The clock falls to 1.4-1.75 GHz under this
+// load, so time no longer follows cycles one for one.
+template <typename T, bool TA, bool TB, bool KBLOCKED = false>
+__global__ __launch_bounds__(T::THREADS, T::WAVES / 4) void gemm_bf16_kernel(
+    float* __restrict__ C, int64_t ldc, const uint16_t* __restrict__ A, int64_t lda,
+    const uint16_t* __restrict__ B, int64_t ldb, int M, int N, int K, int tiles_m, int tiles_n) {
+  __shared__ f32x4 lds[T::LDS_CHUNKS];
+  int tm, tn;
+  grouped_tile(xcd_contiguous(blockIdx.x, gridDim.x), tiles_m, tiles_n, 4, tm, tn);
+  tiles::gemm_ring_tile<T, TA, TB, true, KBLOCKED>(C, ldc, A, lda, B, ldb, M, N, K, tm * T::BM,
+                                                   tn * T::BN, lds);
+}
+
+template <typename T>
+rise_status launch_ring(const GemmLowpArgs& a, bool kblocked, hipStream_t s) {
+  const int tiles_m = (a.M + T::BM - 1) / T::BM, tiles_n = (a.N + T::BN - 1) / T::BN;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n), dim3(T::THREADS), 0, s, a.C, a.ldc,
+                       (const uint16_t*)a.A, a.lda, (const uint16_t*)a.B, a.ldb, a.M, a.N, a.K,
+                       tiles_m, tiles_n);
+  };
+  if (kblocked) {
+    if constexpr (T::BM == 256 && T::BN == 256 && T::BK == 32) go(gemm_bf16_kernel<T, false, true, true>);
+  } else if (!a.ta && !a.tb) go(gemm_bf16_kernel<T, false, false>);
+  else if (!a.ta) go(gemm_bf16_kernel<T, false, true>);
+  else if (!a.tb) go(gemm_bf16_kernel<T, true, false>);
+  else go(gemm_bf16_kernel<T, true, true>);
+  return check_launch("gemm_bf16_kernel");
+}
+
+// The tiles; for BF16, nanoseconds per 64 x 64 outputs and k that one CU takes
+// on them (measured: 256 x 256 at 8192^3, 256 x 128 and 128 x 128 at 2048 x 4096 x
+// 4096, the smaller ones at 1024^3 and 512 x 2048 x 4096; the matrix cores alone
+// need 0.84 at 2.4 GHz), 0: only where asked for.
 struct TileRow {
   rise_mode mode;
   rise_tile t;
+  double ns = 0;
 };
 const TileRow kTiles[] = {
-    {RISE_MODE_BF16, {256, 256, 64}},   {RISE_MODE_BF16, {128, 128, 64}},
-    {RISE_MODE_BF16, {256, 256, 32}},   {RISE_MODE_BF16X3, {256, 256, 16}},
-    {RISE_MODE_BF16X3, {256, 256, 32}}, {RISE_MODE_BF16X3, {128, 128, 32}},
-    {RISE_MODE_BF16X6, {256, 256, 16}}, {RISE_MODE_BF16X6, {128, 128, 16}},
-    {RISE_MODE_FP8, {256, 256, 128}},   {RISE_MODE_FP8, {128, 128, 128}},
+    {RISE_MODE_BF16, {256, 256, 64}},       {RISE_MODE_BF16, {128, 128, 64}, 1.9},
+    {RISE_MODE_BF16, {256, 256, 32}, 1.65}, {RISE_MODE_BF16, {256, 128, 64}, 1.68},
+    {RISE_MODE_BF16, {128, 256, 64}, 1.68}, {RISE_MODE_BF16, {128, 64, 64}, 2.5},
+    {RISE_MODE_BF16, {64, 64, 64}, 4.2},    {RISE_MODE_BF16, {64, 64, 128}, 3.2},
+    {RISE_MODE_BF16, {64, 32, 128}, 4.6},   {RISE_MODE_BF16X3, {256, 256, 16}},
+    {RISE_MODE_BF16X3, {256, 256, 32}},     {RISE_MODE_BF16X3, {128, 128, 32}},
+    {RISE_MODE_BF16X6, {256, 256, 16}},     {RISE_MODE_BF16X6, {128, 128, 16}},
+    {RISE_MODE_FP8, {256, 256, 128}},       {RISE_MODE_FP8, {128, 128, 128}},
 };
+constexpr int kLongK = 2048;  // from here 64 x 64 x 128 beats 64 x 64 x 64 (4096: 17.5 against 21 us)
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
@@ -674,16 +721,29 @@ bool gemm_lowp_tile_supported(rise_mode mode, const rise_tile& t) {
 }
 
 rise_tile gemm_lowp_default_tile(rise_mode mode, int M, int N, int K) {
+  if (mode == RISE_MODE_BF16) {
+    // the shortest time for the CU that gets the most tiles (as for FP32: what the
+    // shapes differ in is mainly how evenly they cover 256 CUs)
+    rise_tile best{128, 128, 64};
+    double least = 0;
+    for (const auto& r : kTiles) {
+      if (r.mode != mode || r.ns == 0) continue;
+      if (r.t.bm == 64 && r.t.bn == 64 && (r.t.bk == 128) != (K > kLongK)) continue;
+      const int64_t tiles =
+          (((int64_t)M + r.t.bm - 1) / r.t.bm) * (((int64_t)N + r.t.bn - 1) / r.t.bn);
+      const double t = (double)((tiles + 255) / 256) * r.t.bm * r.t.bn * r.ns;
+      if (least == 0 || t < least) least = t, best = r.t;
+    }
+    return best;
+  }
   // 256 x 256 when it still gives every CU a tile, else 128 x 128; at 256 x
   // 256 the K-blocked kernel where it is the faster one (measured at 8192^3
-  // with preparation: bf16 1.08-1.24 ms against 1.12-1.32 for the row-major
-  // 256 x 256 x 64 tile, bf16x3 2.71-2.91 against 3.12-3.18 ms for 256 x 256
+  // with preparation: bf16x3 2.71-2.91 against 3.12-3.18 ms for 256 x 256
   // x 32, bf16x6 5.06 against 6.78 ms for the row-major 256 x 256 x 16 tile,
   // fp8 0.62 against 0.83 ms for 128 x 128)
   long tiles_big = (long)((M + 255) / 256) * ((N + 255) / 256);
   const bool big = tiles_big >= 256;
   switch (mode) {
-    case RISE_MODE_BF16: return big ? rise_tile{256, 256, 32} : rise_tile{128, 128, 64};
     case RISE_MODE_BF16X3: return big ? rise_tile{256, 256, 16} : rise_tile{128, 128, 32};
     case RISE_MODE_BF16X6: return big ? rise_tile{256, 256, 16} : rise_tile{128, 128, 16};
     default: return big ? rise_tile{256, 256, 128} : rise_tile{128, 128, 128};
@@ -697,8 +757,8 @@ size_t gemm_lowp_workspace(int M, int N, int K, rise_mode mode, const rise_tile&
 
 // K-blocked layout (K per block) of the tiles packed_kblock_kernel runs
 int packed_kblock(rise_mode mode, const rise_tile& t) {
+  if (mode == RISE_MODE_BF16 && t.bm == 256 && t.bn == 256 && t.bk == 32) return 32;
   if (mode == RISE_MODE_FP8 && t.bm == 256) return KBlock<RISE_MODE_FP8>::elems;
-  if (mode == RISE_MODE_BF16 && t.bm == 256 && t.bk == 32) return KBlock<RISE_MODE_BF16>::elems;
   if (mode == RISE_MODE_BF16X3 && t.bm == 256 && t.bk == 16)
     return KBlock<RISE_MODE_BF16X3>::elems;
   if (mode == RISE_MODE_BF16X6 && t.bm == 256 && t.bk == 16)
@@ -710,10 +770,6 @@ rise_status launch_packed_gemm(const PackedGemm& g, const rise_tile& t, hipStrea
   if (g.kblock != packed_kblock(g.mode, t))
     return fail(RISE_ERR_UNSUPPORTED, "packed gemm: operand layout does not match the tile");
   switch (g.mode) {
-    case RISE_MODE_BF16:
-      if (t.bm == 256 && t.bk == 32) return launch_kblock<RISE_MODE_BF16>(g, s);
-      if (t.bm == 256) return launch_bf16<256, 256, 64, RISE_MODE_BF16>(g, s);
-      return launch_bf16<128, 128, 64, RISE_MODE_BF16>(g, s);
     case RISE_MODE_BF16X3:
       if (t.bm == 256 && t.bk == 16) return launch_kblock<RISE_MODE_BF16X3>(g, s);
       if (t.bm == 256) return launch_bf16<256, 256, 32, RISE_MODE_BF16X3>(g, s);
@@ -729,7 +785,34 @@ rise_status launch_packed_gemm(const PackedGemm& g, const rise_tile& t, hipStrea
   }
 }
 
+namespace {
+rise_status launch_bf16_tile(const GemmLowpArgs& a, const rise_tile& t, bool kblocked,
+                             hipStream_t s) {
+#define RISE_BF16_TILE(BM, BN, BK, ...)               \
+  if (t.bm == BM && t.bn == BN && t.bk == BK)         \
+    return launch_ring<tiles::Bf16Cfg<BM, BN, BK, __VA_ARGS__>>(a, kblocked, s);
+  RISE_BF16_TILE(256, 256, 64, 2, 2, 4, 1)
+  RISE_BF16_TILE(256, 256, 32, 4, 2, 4, 1)
+  RISE_BF16_TILE(256, 128, 64, 3, 4, 2, 1)
+  RISE_BF16_TILE(128, 256, 64, 3, 2, 4, 1)
+  RISE_BF16_TILE(128, 128, 64, 3, 4, 2, 1)
+  RISE_BF16_TILE(128, 64, 64, 3, 2, 2, 2)
+  RISE_BF16_TILE(64, 64, 64, 3, 2, 2, 2)
+  RISE_BF16_TILE(64, 64, 128, 3, 2, 2, 4)
+  RISE_BF16_TILE(64, 32, 128, 3, 2, 1, 4)
+#undef RISE_BF16_TILE
+  return fail(RISE_ERR_UNSUPPORTED, "gemm_bf16: unsupported tile");
+}
+}  // namespace
+
 rise_status launch_gemm_lowp(const GemmLowpArgs& a, const rise_tile& t, void* ws, hipStream_t s) {
+  // bf16 operands whose rows are whole 16-byte chunks are read where they are (a
+  // dense layer of 2048 x 4096 x 4096: 127 us with both operands prepared first,
+  // 59 without)
+  if (a.mode == RISE_MODE_BF16 && a.tA == RISE_BF16 && a.tB == RISE_BF16 && a.K > 0 &&
+      tiles::whole_chunks((const uint16_t*)a.A, a.lda, (const uint16_t*)a.B, a.ldb, a.M, a.N, a.K,
+                          a.ta, a.tb))
+    return launch_bf16_tile(a, t, false, s);
   const int64_t Mp = round_up(a.M, t.bm), Np = round_up(a.N, t.bn), Kp = round_up(a.K, t.bk);
   uint8_t* wsA = (uint8_t*)ws;
   uint8_t* wsB = wsA + round_up((int64_t)prep_bytes(Mp, Kp, a.mode), 256);
@@ -743,6 +826,11 @@ rise_status launch_gemm_lowp(const GemmLowpArgs& a, const rise_tile& t, void* ws
   if (st != RISE_OK) return st;
   st = launch_prep(pb, s);
   if (st != RISE_OK) return st;
+  if (a.mode == RISE_MODE_BF16) {  // the prepared operands, B as rows of transpose(B)
+    GemmLowpArgs p{a.C, a.ldc, wsA, RISE_BF16, kb ? Mp : Kp, false, wsB, RISE_BF16, kb ? Np : Kp,
+                   true, a.M, a.N, (int)Kp, a.mode};
+    return launch_bf16_tile(p, t, kb != 0, s);
+  }
   PackedGemm g{a.C, a.ldc, wsA, wsB, a.M, a.N, (int)Kp, (int)Mp, (int)Np, a.mode, kb};
   return launch_packed_gemm(g, t, s);
 }

@@ -106,8 +106,13 @@ __device__ __forceinline__ float load_src<float>(const float* p) { return *p; }
 template <>
 __device__ __forceinline__ float load_src<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
 
-// layout: 0 = strided scalar loads, 1 = K contiguous (ld_k == 1) with float4,
-// 2 = rows contiguous (ld_r == 1) with float4
+// a 16-byte load from any 4-byte boundary (gfx950 runs global memory in
+// unaligned-access mode)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// layout: 0 = scalar loads, lanes along K, 1 = K contiguous (ld_k == 1), 16-byte
+// loads, 2 = rows contiguous (ld_r == 1), 16-byte loads, 3 = scalar loads, lanes
+// along the rows
 template <typename SRC, int MODE, int LAYOUT>
 __global__ __launch_bounds__(kThreads) void prep_kernel(void* __restrict__ out, int64_t rows_out,
                                                         int64_t k_out,
@@ -130,7 +135,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(void* __restrict__ out, 
       if (gr < rows) {
         const float* q = reinterpret_cast<const float*>(src) + gr * ld_r + gk;
         if (gk + 3 < K) {
-          v = *reinterpret_cast<const f32x4*>(q);
+          v = *reinterpret_cast<const f32x4u*>(q);
         } else {
           if (gk + 0 < K) v.x = q[0];
           if (gk + 1 < K) v.y = q[1];
@@ -152,7 +157,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(void* __restrict__ out, 
       if (gk < K) {
         const float* q = reinterpret_cast<const float*>(src) + gk * ld_k + gr;
         if (gr + 3 < rows) {
-          v = *reinterpret_cast<const f32x4*>(q);
+          v = *reinterpret_cast<const f32x4u*>(q);
         } else {
           if (gr + 0 < rows) v.x = q[0];
           if (gr + 1 < rows) v.y = q[1];
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(void* __restrict__ out, 
     }
   } else {
     for (int c = tid; c < TR * TK; c += kThreads) {
-      int row = c / TK, kk = c % TK;
+      int row = LAYOUT == 3 ? c % TR : c / TK, kk = LAYOUT == 3 ? c / TR : c % TK;
       int64_t gr = r0 + row, gk = k0 + kk;
       tile[row][kk] = (gr < rows && gk < K) ? load_src<SRC>(src + gr * ld_r + gk * ld_k) : 0.f;
     }
@@ -235,7 +240,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(void* __restrict__ out, 
   }
 }
 
-// Source rows already K-contiguous (ld_k == 1, 16-byte aligned rows): no
+// Source rows already K-contiguous (ld_k == 1): no
 // transpose is needed, so the bf16 modes stream without LDS.  Each thread
 // converts 8 consecutive K of one row (two 16-byte loads, one 16-byte store
 // per part), threads placed by stream_pos.
@@ -248,7 +253,7 @@ __global__ __launch_bounds__(kThreads) void prep_stream_kernel(
   if (!stream_pos(t, rows_out, k_out, kb, 2, gr, gk)) return;
   float x[8];
   if (gr < rows && gk + 8 <= K) {
-    const f32x4* q = reinterpret_cast<const f32x4*>(src + gr * ld_r + gk);
+    const f32x4u* q = reinterpret_cast<const f32x4u*>(src + gr * ld_r + gk);
     const f32x4 v0 = q[0], v1 = q[1];
     x[0] = v0.x; x[1] = v0.y; x[2] = v0.z; x[3] = v0.w;
     x[4] = v1.x; x[5] = v1.y; x[6] = v1.z; x[7] = v1.w;
@@ -293,7 +298,7 @@ __global__ __launch_bounds__(kThreads) void prep_stream_fp8_kernel(
   if (!stream_pos(t, rows_out, k_out, kb, 1, gr, gk)) return;
   float x[8];
   if (gr < rows && gk + 8 <= K) {
-    const f32x4* q = reinterpret_cast<const f32x4*>(src + gr * ld_r + gk);
+    const f32x4u* q = reinterpret_cast<const f32x4u*>(src + gr * ld_r + gk);
     const f32x4 v0 = q[0], v1 = q[1];
     x[0] = v0.x; x[1] = v0.y; x[2] = v0.z; x[3] = v0.w;
     x[4] = v1.x; x[5] = v1.y; x[6] = v1.z; x[7] = v1.w;
@@ -322,11 +327,8 @@ rise_status launch_mode(const PrepArgs& a, hipStream_t s) {
   int elem_out = MODE == RISE_MODE_FP8 ? 1 : 2;
   int vec_out = aligned(a.out) && (a.k_out * elem_out) % 16 == 0;
   const SRC* src = reinterpret_cast<const SRC*>(a.src);
-  int layout = 0;
-  if (sizeof(SRC) == 4 && aligned(a.src)) {
-    if (a.ld_k == 1 && a.ld_r % 4 == 0) layout = 1;
-    else if (a.ld_r == 1 && a.ld_k % 4 == 0) layout = 2;
-  }
+  int layout = a.ld_r == 1 && a.ld_k != 1 ? 3 : 0;
+  if (sizeof(SRC) == 4) layout = a.ld_k == 1 ? 1 : a.ld_r == 1 ? 2 : 0;
   if (layout == 1 && MODE != RISE_MODE_FP8) {
     const int64_t threads = stream_threads(a.rows_out, a.k_out, a.kblock, 2);
     hipLaunchKernelGGL((prep_stream_kernel<MODE>), dim3((unsigned)((threads + kThreads - 1) / kThreads)),
@@ -346,6 +348,9 @@ rise_status launch_mode(const PrepArgs& a, hipStream_t s) {
                        src, a.rows, a.K, a.ld_r, a.ld_k, vec_out, a.kblock);
   else if (layout == 2)
     hipLaunchKernelGGL((prep_kernel<SRC, MODE, 2>), grid, block, 0, s, a.out, a.rows_out, a.k_out,
+                       src, a.rows, a.K, a.ld_r, a.ld_k, vec_out, a.kblock);
+  else if (layout == 3)
+    hipLaunchKernelGGL((prep_kernel<SRC, MODE, 3>), grid, block, 0, s, a.out, a.rows_out, a.k_out,
                        src, a.rows, a.K, a.ld_r, a.ld_k, vec_out, a.kblock);
   else
     hipLaunchKernelGGL((prep_kernel<SRC, MODE, 0>), grid, block, 0, s, a.out, a.rows_out, a.k_out,

@@ -22,15 +22,33 @@ __device__ __forceinline__ int clampi(int v, int lo, int hi) {
   return v < lo ? lo : (v > hi ? hi : v);
 }
 
+// Four bf16 values of one column from four consecutive LDS rows (gfx950
+// ds_read_b64_tr_b16).  Within each group of 16 lanes, lane s supplies the
+// address of 4 consecutive 16-bit values M[s][0..3] and lane i receives
+// M[4 j + i / 4][i % 4] as element j: with lane s = 4 j + q pointing at
+// columns c0 + 4 q .. c0 + 4 q + 3 of row r0 + j, lane i receives column
+// c0 + i of rows r0 .. r0 + 3.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ s16x4_t lds_read_tr16(const void* p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p);
+#else
+  (void)p;
+  return s16x4_t{0, 0, 0, 0};
+#endif
+}
+
 // ===========================================================================
-// FP32 GEMM tile (v_mfma_f32_32x32x2_f32): C[m0:m0+BM, n0:n0+BN] = A B
+// GEMM tile: C[m0:m0+BM, n0:n0+BN] = A B, FP32 (v_mfma_f32_32x32x2_f32) or bf16
+// operands with FP32 accumulation (v_mfma_f32_32x32x16_bf16)
 //
 // Pattern -> hardware mapping (paper Sec. IV-B/C: splitJoinMap, the map lowerings
 // and fuseReduceMap; Sec. V-C: toMem and reduceSeq): the workgroup owns one
 // split(BM) x split(BN) tile (mapWorkGroup); its 2 x 2 sub-tiles go to the four
 // waves (mapLocal); split(BK) + reduceSeq(Private) is the K loop with register
 // accumulators; each slab is staged in LDS (toMem(Local)); zip |> map(*) |>
-// reduce(+) is v_mfma_f32_32x32x2_f32; join . join is the guarded row-major
+// reduce(+) is the matrix instruction; join . join is the guarded row-major
 // store.  Operands may be read through transpose (TA, TB) without copies.
 //
 // Slabs flow global -> LDS through a ring of STAGES buffers by asynchronous
@@ -45,7 +63,9 @@ __device__ __forceinline__ int clampi(int v, int lo, int hi) {
 //   rows along m or n (A read through transpose, B as stored): BK rows of MN/4
 //     chunks; with whole 256-byte lines (MN a multiple of 64), chunk p of row k
 //     holds logical chunk p ^ (8 ((k >> 3) & 1)), so rows k and k + 8, which the
-//     two halves of a wave read together, use different banks.
+//     two halves of a wave read together, use different banks.  bf16: the four rows
+//     that one transposed read touches (lds_read_tr16) fall in four different
+//     quarters of a 256-byte line.
 // The swizzles are applied on the global side, by choosing what each lane
 // fetches.  VEC copies move 16 bytes per lane and need 16-byte aligned rows of
 // whole chunks; otherwise each lane copies one value (4 bytes, any alignment)
@@ -53,7 +73,7 @@ __device__ __forceinline__ int clampi(int v, int lo, int hi) {
 // Register staging through guarded value-by-value loads, which such storage took
 // before, ran 1000 x 1531 x 777 in 58 us and 3001^3 in 1188 us, where an aligned
 // neighbour took 45 and 839.
-// The 32x32x2 MFMA's k pair is (k, k + 8) at step t = 0..7 of 16 values of k (lane
+// The FP32 MFMA's k pair is (k, k + 8) at step t = 0..7 of 16 values of k (lane
 // half kl supplies k = 8 kl + t): the sum over a slab is the same, and a lane
 // of a rows-along-k operand then reads its values of four steps with one
 // 16-byte LDS read.
@@ -63,69 +83,118 @@ __device__ __forceinline__ int clampi(int v, int lo, int hi) {
 // ===========================================================================
 __device__ __align__(16) static float g_zero_chunk[4];  // never written: zeros
 
-template <int MN, bool ALONG_K, int BK, bool VEC>
+// Element types of the ring: what a 16-byte chunk holds, the k of one step (one
+// fragment per 32 rows or columns) and its matrix instructions.
+struct F32Elem {
+  typedef float Value;
+  typedef f32x4 Frag;  // k = 8 kl + 4 (step % 2) + s of 16 values of k, s = 0..3
+  static constexpr int PER_CHUNK = 4, KSTEP = 8, SUBSTEPS = 4;
+  __device__ static f32x16 mfma(const Frag& a, const Frag& b, const f32x16& c, int s) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], c, 0, 0, 0);
+  }
+};
+struct Bf16Elem {
+  typedef uint16_t Value;
+  typedef bf16x8 Frag;  // k = 16 step + 8 kl + 0..7
+  static constexpr int PER_CHUNK = 8, KSTEP = 16, SUBSTEPS = 1;
+  __device__ static f32x16 mfma(const Frag& a, const Frag& b, const f32x16& c, int) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  }
+};
+
+template <typename E, int MN, bool ALONG_K, int BK, bool VEC>
 struct AsyncSlab {
-  static_assert((BK == 16 || BK == 32 || BK == 64 || BK == 128) && MN % 32 == 0, "slab shape");
-  static constexpr int CHUNKS = MN * BK / 4;                 // 16-byte chunks of a slab
+  typedef typename E::Value Value;
+  typedef typename E::Frag Frag;
+  static constexpr bool F32 = sizeof(Value) == 4;
+  static constexpr int PC = E::PER_CHUNK;
+  static constexpr int CHUNKS = MN * BK / PC;                 // 16-byte chunks of a slab
   static constexpr int COPIES = CHUNKS * (VEC ? 1 : 4) / 64;  // wave copies of a slab
   static constexpr int COPY_BYTES = VEC ? 1024 : 256;
-  static constexpr int CPR = BK / 4;  // chunks per row along k
+  static constexpr int CPR = BK / PC;  // chunks per row along k
+  static constexpr int CPM = MN / PC;  // chunks per row along m or n
+  static_assert((CPR == 4 || CPR == 8 || CPR == 16 || CPR == 32) && MN % 32 == 0, "slab shape");
+  static_assert(VEC || F32, "value-by-value copies move 4 bytes");
   __device__ static int key(int r) {
-    return BK == 16 ? (r >> 2) & 3 : BK == 32 ? (r >> 1) & 7 : r & 15;
+    return CPR == 4 ? (r >> 2) & 3 : CPR == 8 ? (r >> 1) & 7 : r & 15;
   }
-  // rows along m or n; rows that are not whole 256-byte lines stay as they are
-  __device__ static int key_mn(int k) { return MN % 64 == 0 ? 8 * ((k >> 3) & 1) : 0; }
+  __device__ static int key_mn(int k) {
+    if (F32) return MN % 64 == 0 ? 8 * ((k >> 3) & 1) : 0;
+    return CPM % 16 == 0 ? 4 * (k & 3) : CPM == 8 ? 4 * ((k >> 1) & 1) : 0;
+  }
   // index of this lane's source in wave copy i of a slab, from the slab's first
   // value of the tile (row or column mn0), and the (first) k it holds
   __device__ static int64_t index(int64_t ld, int mn0, int mn_total, int i, int lane, int& k) {
     const int d = i * 64 + lane, ch = VEC ? d : d >> 2, e = VEC ? 0 : d & 3;
     if (ALONG_K) {
       const int r = ch / CPR;
-      k = 4 * ((ch % CPR) ^ key(r)) + e;
+      k = PC * ((ch % CPR) ^ key(r)) + e;
       return min(r, mn_total - 1 - mn0) * ld + k;
     }
-    k = ch / (MN / 4);
-    const int col = 4 * ((ch % (MN / 4)) ^ key_mn(k)) + e;
-    return k * ld + min(col, mn_total - mn0 - (VEC ? 4 : 1));
+    k = ch / CPM;
+    const int col = PC * ((ch % CPM) ^ key_mn(k)) + e;
+    return k * ld + min(col, mn_total - mn0 - (VEC ? PC : 1));
   }
-  __device__ static void copy(const float* base, uint32_t off, void* to) {
+  __device__ static void copy(const Value* base, uint32_t off, uint32_t to) {
     if (VEC)
       async::copy16_at(base, off, to);
     else
       async::copy4_at(base, off, to);
   }
   // by 64-bit address, zeros when !valid
-  __device__ static void copy_any(const float* from, bool valid, void* to) {
+  __device__ static void copy_any(const Value* from, bool valid, uint32_t to) {
+    const void* src = valid ? (const void*)from : (const void*)g_zero_chunk;
     if (VEC)
-      async::copy16(valid ? from : g_zero_chunk, to);
+      async::copy16_from(src, to);
     else
-      async::copy4(valid ? from : g_zero_chunk, to);
+      async::copy4_from(src, to);
   }
-  // values at k = 16 u + 8 kl + 4 h + s (s = 0..3) of row/column r of the slab
-  __device__ static f32x4 frag(const f32x4* slab, int r, int kl, int u, int h) {
-    if (ALONG_K) return slab[r * CPR + ((4 * u + 2 * kl + h) ^ key(r))];
-    const float* f = reinterpret_cast<const float*>(slab);
-    f32x4 v;
+  // fragment of step `st` of the slab for rows/columns r0 .. r0 + 31
+  __device__ static Frag frag(const f32x4* slab, int r0, int lane, int st) {
+    const int kl = lane >> 5, r = r0 + (lane & 31);
+    if constexpr (F32) {
+      const int u = st >> 1, h = st & 1;
+      if (ALONG_K) return slab[r * CPR + ((4 * u + 2 * kl + h) ^ key(r))];
+      const float* f = reinterpret_cast<const float*>(slab);
+      f32x4 v;
 #pragma unroll
-    for (int s = 0; s < 4; s++) {
-      const int k = 16 * u + 8 * kl + 4 * h + s;
-      v[s] = f[k * MN + 4 * ((r >> 2) ^ key_mn(k)) + (r & 3)];
+      for (int s = 0; s < 4; s++) {
+        const int k = 16 * u + 8 * kl + 4 * h + s;
+        v[s] = f[k * MN + 4 * ((r >> 2) ^ key_mn(k)) + (r & 3)];
+      }
+      return v;
+    } else {
+      if (ALONG_K) return __builtin_bit_cast(bf16x8, slab[r * CPR + ((2 * st + kl) ^ key(r))]);
+      // two transposed reads of four rows of k each (see lds_read_tr16)
+      const int i16 = lane & 15, col = r0 + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
+      const char* p = reinterpret_cast<const char*>(slab);
+      s16x4_t part[2];
+#pragma unroll
+      for (int q = 0; q < 2; q++) {
+        const int k = 16 * st + 8 * kl + 4 * q + (i16 >> 2);
+        part[q] = lds_read_tr16(p + k * MN * 2 + (((col >> 3) ^ key_mn(k)) * 16) + (col & 4) * 2);
+      }
+      return __builtin_bit_cast(bf16x8, __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7));
     }
-    return v;
   }
 };
 
 // A tile: BM x BN outputs in GM x GN waves, slabs of BK values of k in a ring of
 // STAGES, KG groups of waves that share every slab's k.
-template <int BM_, int BN_, int BK_, int STAGES_, int GM_, int GN_, int KG_>
-struct F32Cfg {
+template <typename E, int BM_, int BN_, int BK_, int STAGES_, int GM_, int GN_, int KG_>
+struct RingCfg {
+  typedef E Elem;
   static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_, GM = GM_, GN = GN_, KG = KG_;
   static constexpr int WAVES = GM * GN * KG, THREADS = 64 * WAVES;
   static constexpr int TM = BM / GM / 32, TN = BN / GN / 32;  // 32 x 32 blocks of a wave
   static_assert(TM * GM * 32 == BM && TN * GN * 32 == BN, "whole blocks per wave");
-  static constexpr int SL = (BM + BN) * BK / 4;  // chunks per ring stage: A slab, then B slab
+  static constexpr int SL = (BM + BN) * BK / E::PER_CHUNK;  // chunks per stage: A slab, then B slab
   static constexpr int LDS_CHUNKS = STAGES * SL;
 };
+template <int... Shape>
+using F32Cfg = RingCfg<F32Elem, Shape...>;
+template <int... Shape>
+using Bf16Cfg = RingCfg<Bf16Elem, Shape...>;
 
 // Below this leading dimension a copy's byte offset in a slab (up to 255 rows) fits
 // 32 bits, and copies take a uniform base and that offset; longer rows are
@@ -134,29 +203,36 @@ constexpr int64_t kF32OffsetLd = (int64_t)1 << 22;
 
 // The operands' storage allows 16-byte copies: 16-byte aligned rows that are
 // whole chunks.
-__host__ __device__ inline bool f32_vec(const float* A, int64_t lda, const float* B, int64_t ldb,
-                                        int M, int N, int K, bool ta, bool tb) {
-  return ((uintptr_t)A & 15) == 0 && ((uintptr_t)B & 15) == 0 && lda % 4 == 0 && ldb % 4 == 0 &&
-         (ta ? M : K) % 4 == 0 && (tb ? K : N) % 4 == 0;
+template <typename V>
+__host__ __device__ inline bool whole_chunks(const V* A, int64_t lda, const V* B, int64_t ldb, int M,
+                                             int N, int K, bool ta, bool tb) {
+  constexpr int q = 16 / sizeof(V);
+  return ((uintptr_t)A & 15) == 0 && ((uintptr_t)B & 15) == 0 && lda % q == 0 && ldb % q == 0 &&
+         (ta ? M : K) % q == 0 && (tb ? K : N) % q == 0;
 }
 
 // C[m0:m0+BM, n0:n0+BN] = A B with the whole workgroup of T::THREADS: KG groups
 // of GM x GN waves, each group summing its share of every slab's k (the groups'
 // tiles are added at the end, group 0 first).  lds holds T::LDS_CHUNKS 16-byte
 // chunks.  No copy is in flight into lds when it returns.
-template <typename T, bool TA, bool TB, bool VEC>
-__device__ __forceinline__ void gemm_f32_tile(float* __restrict__ C, int64_t ldc,
-                                              const float* __restrict__ A, int64_t lda,
-                                              const float* __restrict__ B, int64_t ldb, int M,
-                                              int N, int K, int m0, int n0, f32x4* lds_base) {
+// KBLOCKED: both operands prepared K-blocked (K block b of row r holds BK values
+// at (b * rows + r) * BK, zero padded to whole tiles): lda and ldb are then the
+// operands' row counts.
+template <typename T, bool TA, bool TB, bool VEC, bool KBLOCKED = false,
+          typename V = typename T::Elem::Value>
+__device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ldc,
+                                               const V* __restrict__ A, int64_t lda,
+                                               const V* __restrict__ B, int64_t ldb, int M, int N,
+                                               int K, int m0, int n0, f32x4* lds_base) {
+  typedef typename T::Elem E;
   constexpr int BM = T::BM, BN = T::BN, BK = T::BK, STAGES = T::STAGES, KG = T::KG;
   constexpr int TM = T::TM, TN = T::TN, SL = T::SL, NW = T::WAVES;
-  using SA = AsyncSlab<BM, !TA, BK, VEC>;
-  using SB = AsyncSlab<BN, TB, BK, VEC>;
+  using SA = AsyncSlab<E, BM, !TA, BK, VEC>;
+  using SB = AsyncSlab<E, BN, TB, BK, VEC>;
   // copies of a slab, A's then B's; copy j of wave w is number j NW + w, or the
   // last one again where the waves do not share them evenly
   constexpr int COPIES = SA::COPIES + SB::COPIES, NCP = (COPIES + NW - 1) / NW;
-  static_assert(BK % (16 * KG) == 0, "the groups share the k evenly");
+  static_assert(BK % (2 * E::KSTEP * KG) == 0, "the groups share the k evenly, in even steps");
   static_assert(KG == 1 || (KG - 1) * BM * BN / 4 <= T::LDS_CHUNKS, "the groups' tiles fit the ring");
   static_assert(STAGES >= 2 && (STAGES - 1) * NCP < 64, "ring and its vmcnt");
   auto lds = reinterpret_cast<f32x4(*)[SL]>(lds_base);
@@ -170,6 +246,10 @@ __device__ __forceinline__ void gemm_f32_tile(float* __restrict__ C, int64_t ldc
   lda = async::uniform(lda);
   ldb = async::uniform(ldb);
   K = __builtin_amdgcn_readfirstlane(K);
+  static_assert(!KBLOCKED || (!TA && TB && VEC), "prepared operands are rows along k");
+  const int64_t step_a = TA || KBLOCKED ? (int64_t)BK * lda : BK;
+  const int64_t step_b = TB && !KBLOCKED ? BK : (int64_t)BK * ldb;
+  if (KBLOCKED) lda = ldb = BK;
   auto number = [&](int j) { return min(j * NW + wave, COPIES - 1); };
   auto is_a = [&](int j) {  // known at compile time where the waves share A's copies evenly
     return (j + 1) * NW <= SA::COPIES || (j * NW < SA::COPIES && number(j) < SA::COPIES);
@@ -182,42 +262,39 @@ __device__ __forceinline__ void gemm_f32_tile(float* __restrict__ C, int64_t ldc
 #pragma unroll
   for (int j = 0; j < NCP; j++) {
     int k;
-    off[j] = 4 * (uint32_t)index(j, lane, k);
+    off[j] = (uint32_t)sizeof(V) * (uint32_t)index(j, lane, k);
   }
-  const int64_t step_a = TA ? (int64_t)BK * lda : BK, step_b = TB ? BK : (int64_t)BK * ldb;
   const int nk = (K + BK - 1) / BK, krem = K - (nk - 1) * BK;
   const bool wide = lda >= kF32OffsetLd || ldb >= kF32OffsetLd;
   // the next slab to copy (its first value in the tile's first row or column);
   // past the last slab the last one is copied again, into a stage nothing reads
-  const float* pa = async::uniform(A + (TA ? m0 : (int64_t)m0 * lda));
-  const float* pb = async::uniform(B + (TB ? (int64_t)n0 * ldb : n0));
-  int next = 0, stage = 0;  // that slab and its ring stage
-  auto copies = [&](auto from, auto to) {  // copies from .. to - 1 of that slab by this wave
-    char* dst = reinterpret_cast<char*>(&lds[stage][0]);
-    if (wide || (next >= nk - 1 && krem < BK)) {
+  const V* pa = async::uniform(A + (TA ? m0 : (int64_t)m0 * lda));
+  const V* pb = async::uniform(B + (TB ? (int64_t)n0 * ldb : n0));
+  constexpr uint32_t STAGE_BYTES = SL * 16;
+  const uint32_t lds0 = async::lds_address(lds_base);
+  int next = 0;      // that slab
+  uint32_t put = 0;  // and the byte offset of its ring stage
+  // copy j of that slab.  careful: it may be the last slab of a ragged K, or rows
+  // may be too long for 32-bit offsets
+  auto copy = [&](int j, auto careful) {
+    const uint32_t to = lds0 + put + (COPIES % NW == 0 ? j * NW + wave : number(j)) * SA::COPY_BYTES;
+    if (decltype(careful)::value && (wide || (next >= nk - 1 && krem < BK))) {
       const int kend = next >= nk - 1 ? krem : BK;
-      int ln = lane;  // opaque: what this computes stays out of the loop's registers
+      int ln = lane, k;  // opaque: what this computes stays out of the loop's registers
       asm volatile("" : "+v"(ln));
-#pragma unroll
-      for (int j = from; j < to; j++) {
-        int k;
-        const int64_t at = index(j, ln, k);
-        SA::copy_any((is_a(j) ? pa : pb) + at, k < kend, dst + number(j) * SA::COPY_BYTES);
-      }
-      return;
+      const int64_t at = index(j, ln, k);
+      SA::copy_any((is_a(j) ? pa : pb) + at, k < kend, to);
+    } else if (is_a(j)) {  // wave-uniform
+      SA::copy(pa, off[j], to);
+    } else {
+      SB::copy(pb, off[j], to);
     }
-#pragma unroll
-    for (int j = from; j < to; j++)
-      if (is_a(j))  // wave-uniform
-        SA::copy(pa, off[j], dst + number(j) * SA::COPY_BYTES);
-      else
-        SB::copy(pb, off[j], dst + number(j) * SB::COPY_BYTES);
   };
   auto advance = [&] {
     pa += next < nk - 1 ? step_a : 0;
     pb += next < nk - 1 ? step_b : 0;
     next++;
-    stage = stage == STAGES - 1 ? 0 : stage + 1;
+    put = put == (STAGES - 1) * STAGE_BYTES ? 0 : put + STAGE_BYTES;
   };
 
   f32x16 acc[TM][TN];
@@ -229,69 +306,82 @@ __device__ __forceinline__ void gemm_f32_tile(float* __restrict__ C, int64_t ldc
       for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
 
   const int kl = lane >> 5, il = lane & 31;
-  // A group's share of a slab is NS steps of 8 k.  A step's fragments are read
+  // A group's share of a slab is NS steps.  A step's fragments are read
   // while the step before runs its MFMAs, across slabs too: the barrier that
-  // publishes slab kt + 1 stands before the last step of slab kt, whose
+  // publishes slab kt + 1 stands in the last step of slab kt, whose
   // fragments are in registers by then, so it also frees the stage of slab kt for
   // the copies of slab kt + STAGES, which the next slab's steps issue.  (With
   // the barrier at the start of a slab every wave waited out an LDS latency
-  // there: 64 x 64 tiles took 1700 cycles for the 1024 of a slab's MFMAs.)
-  constexpr int NS = BK / 8 / KG;
-  static_assert(NS % 2 == 0, "the fragment sets alternate by step");
-  f32x4 a[2][TM], b[2][TN];
+  // there: FP32 64 x 64 tiles took 1700 cycles for the 1024 of a slab's MFMAs.)
+  // Reads and copies are placed one by one between the MFMAs: a wave issues in
+  // order, and as a block in front of a step's MFMAs they left the matrix cores
+  // idle for about as long as the MFMAs run.
+  constexpr int NS = BK / E::KSTEP / KG;  // even: the fragment sets alternate by step
+  typename E::Frag a[2][TM], b[2][TN];
   int buf = 0;
-  auto read = [&](int at, int st) {
-    const f32x4* As = &lds[at][0];
-    const f32x4* Bs = &lds[at][SA::CHUNKS];
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-      a[st & 1][i] = SA::frag(As, wm0 + 32 * i + il, kl, group * (NS / 2) + (st >> 1), st & 1);
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-      b[st & 1][j] = SB::frag(Bs, wn0 + 32 * j + il, kl, group * (NS / 2) + (st >> 1), st & 1);
+  // fragment r of step st of the slab in stage `at`, in the order the MFMAs need
+  // them: A's first, B's, the rest of A's
+  auto read = [&](int at, int st, int r) {
+    const f32x4* slab = &lds[at][0];
+    if (r == 0 || r > TN) {
+      const int i = r == 0 ? 0 : r - TN;
+      a[st & 1][i] = SA::frag(slab, wm0 + 32 * i, lane, group * NS + st);
+    } else {
+      b[st & 1][r - 1] = SB::frag(slab + SA::CHUNKS, wn0 + 32 * (r - 1), lane, group * NS + st);
+    }
   };
+  constexpr int NR = TM + TN;
   if (nk > 0) {
 #pragma unroll
-    for (int st = 0; st < STAGES; st++) {
-      copies(std::integral_constant<int, 0>{}, std::integral_constant<int, NCP>{});
+    for (int st = 0; st < STAGES - 1; st++) {
+#pragma unroll
+      for (int j = 0; j < NCP; j++) copy(j, std::true_type{});
       advance();
     }
-    async::wait_vmcnt<(STAGES - 1) * NCP>();  // slab 0 has landed
+    async::wait_vmcnt<(STAGES - 2) * NCP>();  // slab 0 has landed
     async::barrier();
-    read(0, 0);
+#pragma unroll
+    for (int r = 0; r < NR; r++) read(0, 0, r);
   }
-  for (int kt = 0; kt < nk; kt++) {
+  auto slab = [&](auto careful) {
     const int after = buf == STAGES - 1 ? 0 : buf + 1;
     auto steps = [&](auto self, auto st_tag) {
       constexpr int st = decltype(st_tag)::value;
       if constexpr (st < NS) {
-        if constexpr (st == NS - 1) {
-          async::wait_vmcnt<(STAGES - 2) * NCP>();  // this wave's copies of slab kt + 1 landed
-          async::wait_lgkmcnt0();                   // and it has read all of slab kt
-          async::barrier();
-          read(after, 0);
-        } else {
-          read(buf, st + 1);
-          if (kt > 0)
-            copies(std::integral_constant<int, NCP * st / (NS - 1)>{},
-                   std::integral_constant<int, NCP*(st + 1) / (NS - 1)>{});
-        }
-#pragma unroll
-        for (int s = 0; s < 4; s++)
-#pragma unroll
-          for (int i = 0; i < TM; i++)
-#pragma unroll
-            for (int j = 0; j < TN; j++)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[st & 1][i][s], b[st & 1][j][s],
-                                                               acc[i][j], 0, 0, 0);
+        constexpr bool last = st == NS - 1;
+        constexpr int c0 = last ? 0 : NCP * st / (NS - 1), c1 = last ? 0 : NCP * (st + 1) / (NS - 1);
+        constexpr int NM = E::SUBSTEPS * TM * TN, OPS = NR + c1 - c0;  // MFMAs, other operations
         __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < NM; m++) {
+          const int s = m / (TM * TN), i = m / TN % TM, j = m % TN;
+          acc[i][j] = E::mfma(a[st & 1][i], b[st & 1][j], acc[i][j], s);
+          __builtin_amdgcn_sched_barrier(0);
+          if (last && m == 0) {
+            async::wait_vmcnt<(STAGES - 2) * NCP>();  // this wave's copies of slab kt + 1 landed
+            async::wait_lgkmcnt0();                   // and it has read all of slab kt
+            async::barrier();
+          }
+#pragma unroll
+          for (int o = OPS * m / NM; o < OPS * (m + 1) / NM; o++) {
+            if (o < NR)
+              read(last ? after : buf, last ? 0 : st + 1, o);
+            else
+              copy(c0 + o - NR, careful);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
         self(self, std::integral_constant<int, st + 1>{});
       }
     };
     steps(steps, std::integral_constant<int, 0>{});
-    if (kt > 0) advance();
+    advance();
     buf = after;
-  }
+  };
+  int kt = 0;
+  if (!wide)
+    for (; kt < nk - STAGES; kt++) slab(std::false_type{});
+  for (; kt < nk; kt++) slab(std::true_type{});
   async::wait_vmcnt<0>();  // the copies past the last slab land before the exit
 
   if constexpr (KG > 1) {
@@ -338,7 +428,7 @@ __device__ __forceinline__ void gemm_f32_tile(float* __restrict__ C, int64_t ldc
 // and 16-byte aligned bases; K ragged in units of 8 (zero-filled chunks).
 // ===========================================================================
 template <int BM, int BN, int BK>
-struct Bf16Cfg {
+struct Bf16StagedCfg {
   static constexpr int CH = BK / 8;  // 16-byte chunks per slab row
   // B stored K x N sits in LDS as stored: BK rows of BN values, the row pitch
   // padded by 64 bytes so the four rows one transposed read touches fall in
@@ -348,23 +438,6 @@ struct Bf16Cfg {
   static constexpr int LDS_CHUNKS =
       2 * BM * CH + (2 * BN * CH > B_KN_CHUNKS ? 2 * BN * CH : B_KN_CHUNKS);
 };
-
-// Four bf16 values of one column from four consecutive LDS rows (gfx950
-// ds_read_b64_tr_b16).  Within each group of 16 lanes, lane s supplies the
-// address of 4 consecutive 16-bit values M[s][0..3] and lane i receives
-// M[4 j + i / 4][i % 4] as element j: with lane s = 4 j + q pointing at
-// columns c0 + 4 q .. c0 + 4 q + 3 of row r0 + j, lane i receives column
-// c0 + i of rows r0 .. r0 + 3.
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ s16x4_t lds_read_tr16(const void* p) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p);
-#else
-  (void)p;
-  return s16x4_t{0, 0, 0, 0};
-#endif
-}
 
 // row r, 16-byte chunk c -> LDS chunk index; the XOR key changes every 16/CH rows
 // so 16 consecutive rows at one logical chunk hit distinct slots of a 256-byte
@@ -380,7 +453,7 @@ __device__ __forceinline__ void gemm_bf16_tile(float* __restrict__ C, int64_t ld
                                                const uint16_t* __restrict__ A, int64_t lda,
                                                const uint16_t* __restrict__ B, int64_t ldb, int M,
                                                int N, int K, int m0, int n0, i32x4* lds) {
-  using T = Bf16Cfg<BM, BN, BK>;
+  using T = Bf16StagedCfg<BM, BN, BK>;
   constexpr int CH = T::CH;
   constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
   constexpr int LA = BM * CH / kThreads;                // A chunks per thread

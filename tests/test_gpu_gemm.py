@@ -241,6 +241,39 @@ def test_f32_long_rows_integer_exact(rise, trans):
         assert np.array_equal(host(C), exact), tile
 
 
+@pytest.mark.parametrize("ops", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (64, 96, 64), (72, 40, 136), (264, 136, 200),
+                                   (129, 65, 100), (24, 264, 1032)])
+def test_bf16_stored_tile_edges_integer_exact(rise, ops, off, M, N, K):
+    # every BF16 tile at, below and above its edges and slab lengths on bf16-stored
+    # operands: rows of whole 16-byte chunks are read in place, others (off = 1, or
+    # odd sizes) through the preparation; integer inputs make every order exact
+    import torch
+
+    g = ri.rng(M + 5 * N + 11 * K + off)
+    A, B = ri.integer_matrix(g, M, K, bound=2), ri.integer_matrix(g, K, N, bound=2)
+    exact = (A.astype(np.int64) @ B.astype(np.int64)).astype(np.float32)
+
+    def placed(x, t):  # rows of 8-multiples, NaN around them, shifted by off values
+        x = np.ascontiguousarray(x.T) if t else x
+        ld = (x.shape[1] + 7) // 8 * 8 + 8 + off
+        buf = torch.full((x.shape[0] * ld + 8,), float("nan"), device="cuda", dtype=torch.bfloat16)
+        v = buf[off:off + x.shape[0] * ld].view(x.shape[0], ld)
+        v[:, :x.shape[1]] = dev(x)
+        return v, ld
+
+    (dA, lda), (dB, ldb) = placed(A, ops[0]), placed(B, ops[1])
+    for tile in rise.rise_gemm_tiles("bf16"):
+        print(f"gemm bf16 edges {M}x{N}x{K} ops={ops} off={off} tile={tile}", flush=True)
+        ws = torch.empty(rise.rise_gemm_workspace(M, N, K, "bf16", tile), device="cuda",
+                         dtype=torch.uint8)
+        C = torch.full((M, N), float("nan"), device="cuda")
+        rise.rise_gemm(C, dA, dB, M, N, K, lda=lda, ldb=ldb, ldc=N, opA=int(ops[0]),
+                       opB=int(ops[1]), mode="bf16", tile=tile, ws=ws)
+        assert np.array_equal(host(C), exact), tile
+
+
 @pytest.mark.parametrize("mode", list(MODES))
 def test_modes_integer_exact(rise, mode):
     g = ri.rng(21)
