@@ -6,16 +6,17 @@
 // is bound by HBM bandwidth (0.5 flop per byte), not by arithmetic: the kernels
 // are organised around coalesced 16-byte loads and enough loads in flight.
 //
-//   A row-major (the paper's layout, RISE_OP_N): a wavefront owns 4 rows at a
-//     time (map over rows -> waves, as the generated kernel's work-items own
-//     rows); its lanes stride along the rows in 16-byte chunks (split of the
-//     row into lane-sized pieces), each chunk of x is loaded once for the 4
-//     rows, and the per-lane partial sums are combined across the wavefront
-//     (the reduce, as a tree over the 64 lanes);
-//   A read through transpose (RISE_OP_T, A stored K x M): a thread owns 4
+//   A row-major (the paper's layout, RISE_OP_N): a wavefront owns rows (map over
+//     rows -> waves, as the generated kernel's work-items own rows), four at a
+//     time when there are plenty; its lanes stride along the rows in 16-byte chunks
+//     (split of the row into lane-sized pieces), and the per-lane partial sums are
+//     combined across the wavefront (the reduce, as a tree over the 64 lanes).
+//     With few rows several waves share a row;
+//   A read through transpose (RISE_OP_T, A stored K x M): a lane owns 4
 //     consecutive outputs and sweeps rows of the stored A with 16-byte loads;
-//     K is split over workgroups when there are too few column blocks to fill
-//     the GPU, and a second kernel sums the split-K partials in a fixed order.
+//     K is split over waves and workgroups when there are too few column blocks
+//     to fill the GPU, and a second kernel sums the split-K partials in a fixed
+//     order.
 #include <stdint.h>
 
 #include <algorithm>
@@ -28,8 +29,7 @@ namespace rise {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kRowsPerWave = 4;
-constexpr int kColsPerBlock = kThreads * 4;  // outputs per workgroup (RISE_OP_T)
+constexpr int kCols = 256, kWideCols = 1024;  // outputs per workgroup (RISE_OP_T)
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -37,169 +37,194 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(kThreads) void gemv_rows(float* __restrict__ y,
-                                                      const float* __restrict__ A, int64_t lda,
-                                                      const float* __restrict__ x, int M, int K,
-                                                      int64_t row_groups) {
-  const int lane = threadIdx.x & 63;
-  const int64_t nwaves = (int64_t)gridDim.x * (kThreads / 64);
-  for (int64_t g = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); g < row_groups;
-       g += nwaves) {
-    const int r0 = (int)(g * kRowsPerWave);
-    const float* rows[kRowsPerWave];
+// a 16-byte load from any 4-byte boundary (gfx950 runs global memory in
+// unaligned-access mode)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// RPW rows per wave; WAVES waves of a workgroup share a row group's K (1: a wave
+// owns its rows), each taking every WAVES-th run of UN 16-byte chunks per lane.
+template <int RPW, int WAVES, int UN>
+__global__ __launch_bounds__(WAVES == 1 ? kThreads : 64 * WAVES) void gemv_rows(
+    float* __restrict__ y, const float* __restrict__ A, int64_t lda, const float* __restrict__ x,
+    int M, int K, int64_t row_groups) {
+  __shared__ float part[WAVES][RPW];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t step = WAVES == 1 ? (int64_t)gridDim.x * (kThreads / 64) : gridDim.x;
+  for (int64_t g = WAVES == 1 ? (int64_t)blockIdx.x * (kThreads / 64) + wave : blockIdx.x;
+       g < row_groups; g += step) {
+    const int r0 = (int)(g * RPW);
+    const float* rows[RPW];
 #pragma unroll
-    for (int j = 0; j < kRowsPerWave; j++)  // rows past M repeat the last row; never stored
+    for (int j = 0; j < RPW; j++)  // rows past M repeat the last row; never stored
       rows[j] = A + (int64_t)min(r0 + j, M - 1) * lda;
-    float acc[kRowsPerWave] = {0.f, 0.f, 0.f, 0.f};
-    int k_done = 0;
-    if (VEC) {
-      const int nchunk = K / 4;
-      f32x4 a4[kRowsPerWave];
+    f32x4 a4[RPW];
 #pragma unroll
-      for (int j = 0; j < kRowsPerWave; j++) a4[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-      int c = lane;
-      // two chunks per lane per iteration keep more loads in flight
-      for (; c + 64 < nchunk; c += 128) {
-        const f32x4 x0 = reinterpret_cast<const f32x4*>(x)[c];
-        const f32x4 x1 = reinterpret_cast<const f32x4*>(x)[c + 64];
-        f32x4 v0[kRowsPerWave], v1[kRowsPerWave];
+    for (int j = 0; j < RPW; j++) a4[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nchunk = K / 4, kw = WAVES == 1 ? 0 : wave;
+    auto fma4 = [&](f32x4& acc, const f32x4& v, const f32x4& w) {
+      acc.x = fmaf(v.x, w.x, acc.x);
+      acc.y = fmaf(v.y, w.y, acc.y);
+      acc.z = fmaf(v.z, w.z, acc.z);
+      acc.w = fmaf(v.w, w.w, acc.w);
+    };
+    int c = 64 * UN * kw + lane;
+    for (; c + 64 * (UN - 1) < nchunk; c += 64 * UN * WAVES) {  // all loads of a run in flight
+      f32x4 xv[UN], v[UN][RPW];
 #pragma unroll
-        for (int j = 0; j < kRowsPerWave; j++) {
-          v0[j] = reinterpret_cast<const f32x4*>(rows[j])[c];
-          v1[j] = reinterpret_cast<const f32x4*>(rows[j])[c + 64];
-        }
+      for (int u = 0; u < UN; u++) {
+        xv[u] = reinterpret_cast<const f32x4u*>(x)[c + 64 * u];
 #pragma unroll
-        for (int j = 0; j < kRowsPerWave; j++) {
-          a4[j].x = fmaf(v0[j].x, x0.x, a4[j].x);
-          a4[j].y = fmaf(v0[j].y, x0.y, a4[j].y);
-          a4[j].z = fmaf(v0[j].z, x0.z, a4[j].z);
-          a4[j].w = fmaf(v0[j].w, x0.w, a4[j].w);
-          a4[j].x = fmaf(v1[j].x, x1.x, a4[j].x);
-          a4[j].y = fmaf(v1[j].y, x1.y, a4[j].y);
-          a4[j].z = fmaf(v1[j].z, x1.z, a4[j].z);
-          a4[j].w = fmaf(v1[j].w, x1.w, a4[j].w);
-        }
-      }
-      for (; c < nchunk; c += 64) {
-        const f32x4 x0 = reinterpret_cast<const f32x4*>(x)[c];
-#pragma unroll
-        for (int j = 0; j < kRowsPerWave; j++) {
-          const f32x4 v = reinterpret_cast<const f32x4*>(rows[j])[c];
-          a4[j].x = fmaf(v.x, x0.x, a4[j].x);
-          a4[j].y = fmaf(v.y, x0.y, a4[j].y);
-          a4[j].z = fmaf(v.z, x0.z, a4[j].z);
-          a4[j].w = fmaf(v.w, x0.w, a4[j].w);
-        }
+        for (int j = 0; j < RPW; j++) v[u][j] = reinterpret_cast<const f32x4u*>(rows[j])[c + 64 * u];
       }
 #pragma unroll
-      for (int j = 0; j < kRowsPerWave; j++) acc[j] = (a4[j].x + a4[j].y) + (a4[j].z + a4[j].w);
-      k_done = nchunk * 4;
-    }
-    for (int k = k_done + lane; k < K; k += 64) {  // scalar path / ragged tail
-      const float xv = x[k];
+      for (int u = 0; u < UN; u++)
 #pragma unroll
-      for (int j = 0; j < kRowsPerWave; j++) acc[j] = fmaf(rows[j][k], xv, acc[j]);
+        for (int j = 0; j < RPW; j++) fma4(a4[j], v[u][j], xv[u]);
     }
 #pragma unroll
-    for (int j = 0; j < kRowsPerWave; j++) {
+    for (int u = 0; u < UN; u++)  // this lane's chunks of the last, shorter run
+      if (c + 64 * u < nchunk) {
+        const f32x4 xv = reinterpret_cast<const f32x4u*>(x)[c + 64 * u];
+#pragma unroll
+        for (int j = 0; j < RPW; j++)
+          fma4(a4[j], f32x4(reinterpret_cast<const f32x4u*>(rows[j])[c + 64 * u]), xv);
+      }
+    float acc[RPW];
+#pragma unroll
+    for (int j = 0; j < RPW; j++) acc[j] = (a4[j].x + a4[j].y) + (a4[j].z + a4[j].w);
+    if (kw == 0 && nchunk * 4 + lane < K) {  // up to 3 values past the last chunk
+      const int k = nchunk * 4 + lane;
+#pragma unroll
+      for (int j = 0; j < RPW; j++) acc[j] = fmaf(rows[j][k], x[k], acc[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < RPW; j++) {
       const float s = wave_sum(acc[j]);
-      if (lane == 0 && r0 + j < M) y[r0 + j] = s;
+      if (WAVES == 1) {
+        if (lane == 0 && r0 + j < M) y[r0 + j] = s;
+      } else if (lane == 0) {
+        part[wave][j] = s;
+      }
+    }
+    if (WAVES > 1) {
+      __syncthreads();
+      if (threadIdx.x < RPW && r0 + (int)threadIdx.x < M) {
+        float s = part[0][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < WAVES; w++) s += part[w][threadIdx.x];
+        y[r0 + threadIdx.x] = s;
+      }
+      __syncthreads();
     }
   }
 }
 
-// out[kc * ldo + m] = sum over k in chunk kc of A[k][m] * x[k], added in k order.
-// DEEP keeps four rows of loads in flight per thread instead of two (for grids
-// too small to hide the latency with more waves); the sums are the same.
-template <bool VEC, bool DEEP>
+// out[kc * ldo + m] = sum over k in chunk kc of A[k][m] * x[k].  A lane owns four
+// columns; KS of the workgroup's four waves share the chunk's rows (their sums are
+// added in wave order), the others stand side by side, and 16-byte loads of UN
+// rows are in flight per lane.
+//   KS = 4, UN = 8: 256 columns a workgroup.  The split over waves inside the
+//     workgroup quarters the partial sums that a split over workgroups alone
+//     writes for the same number of waves (4096^2 with the reduction: 18.5 -> 15.3
+//     us, 512 x 16384 19.5 -> 10.3 us).
+//   KS = 1, UN = 2: 1024 columns a workgroup, for wide matrices, where one row
+//     of a workgroup is 4 KB of consecutive memory (16384^2: 171 us against 198).
+// Lanes at the right edge load the last four columns instead (their sums are
+// written by column, so nothing is counted twice).
+template <int KS, int UN>
 __global__ __launch_bounds__(kThreads) void gemv_cols(float* __restrict__ out, int64_t ldo,
                                                       const float* __restrict__ A, int64_t lda,
                                                       const float* __restrict__ x, int M, int K,
                                                       int mblocks, int kchunk) {
+  constexpr int COLS = kThreads * 4 / KS;
+  __shared__ float part[KS][COLS];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int side = wave % (4 / KS), kw = wave / (4 / KS);
   const int mb = blockIdx.x % mblocks, kc = blockIdx.x / mblocks;
-  const int m = mb * kColsPerBlock + threadIdx.x * 4;
-  const int k0 = kc * kchunk, k1 = min(K, k0 + kchunk);
-  if (m >= M) return;  // no barriers in this kernel
+  const int m0 = mb * COLS, m = min(m0 + 256 * side + 4 * lane, M - 4);
+  const int c0 = kc * kchunk, c1 = min(K, c0 + kchunk), share = (c1 - c0 + KS - 1) / KS;
+  int k = c0 + kw * share;
+  const int k1 = min(c1, k + share);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  if (VEC && m + 3 < M) {
-    int k = k0;
-    if (DEEP) {
-      for (; k + 3 < k1; k += 4) {
-        const f32x4 a0 = *reinterpret_cast<const f32x4*>(A + (int64_t)k * lda + m);
-        const f32x4 a1 = *reinterpret_cast<const f32x4*>(A + (int64_t)(k + 1) * lda + m);
-        const f32x4 a2 = *reinterpret_cast<const f32x4*>(A + (int64_t)(k + 2) * lda + m);
-        const f32x4 a3 = *reinterpret_cast<const f32x4*>(A + (int64_t)(k + 3) * lda + m);
-        const float x0 = x[k], x1 = x[k + 1], x2 = x[k + 2], x3 = x[k + 3];
-        acc.x = fmaf(a0.x, x0, acc.x); acc.y = fmaf(a0.y, x0, acc.y);
-        acc.z = fmaf(a0.z, x0, acc.z); acc.w = fmaf(a0.w, x0, acc.w);
-        acc.x = fmaf(a1.x, x1, acc.x); acc.y = fmaf(a1.y, x1, acc.y);
-        acc.z = fmaf(a1.z, x1, acc.z); acc.w = fmaf(a1.w, x1, acc.w);
-        acc.x = fmaf(a2.x, x2, acc.x); acc.y = fmaf(a2.y, x2, acc.y);
-        acc.z = fmaf(a2.z, x2, acc.z); acc.w = fmaf(a2.w, x2, acc.w);
-        acc.x = fmaf(a3.x, x3, acc.x); acc.y = fmaf(a3.y, x3, acc.y);
-        acc.z = fmaf(a3.z, x3, acc.z); acc.w = fmaf(a3.w, x3, acc.w);
+  if (M >= 4) {
+    const float* p = A + (int64_t)k * lda + m;
+    for (; k + UN <= k1; k += UN, p += UN * lda) {
+      f32x4 v[UN];
+#pragma unroll
+      for (int u = 0; u < UN; u++) v[u] = *reinterpret_cast<const f32x4u*>(p + u * lda);
+#pragma unroll
+      for (int u = 0; u < UN; u++) {
+        const float xv = x[k + u];
+        acc.x = fmaf(v[u].x, xv, acc.x); acc.y = fmaf(v[u].y, xv, acc.y);
+        acc.z = fmaf(v[u].z, xv, acc.z); acc.w = fmaf(v[u].w, xv, acc.w);
       }
     }
-    for (; k + 1 < k1; k += 2) {
-      const f32x4 a0 = *reinterpret_cast<const f32x4*>(A + (int64_t)k * lda + m);
-      const f32x4 a1 = *reinterpret_cast<const f32x4*>(A + (int64_t)(k + 1) * lda + m);
-      const float x0 = x[k], x1 = x[k + 1];
-      acc.x = fmaf(a0.x, x0, acc.x); acc.y = fmaf(a0.y, x0, acc.y);
-      acc.z = fmaf(a0.z, x0, acc.z); acc.w = fmaf(a0.w, x0, acc.w);
-      acc.x = fmaf(a1.x, x1, acc.x); acc.y = fmaf(a1.y, x1, acc.y);
-      acc.z = fmaf(a1.z, x1, acc.z); acc.w = fmaf(a1.w, x1, acc.w);
+    for (; k < k1; k++, p += lda) {
+      const f32x4 v = *reinterpret_cast<const f32x4u*>(p);
+      const float xv = x[k];
+      acc.x = fmaf(v.x, xv, acc.x); acc.y = fmaf(v.y, xv, acc.y);
+      acc.z = fmaf(v.z, xv, acc.z); acc.w = fmaf(v.w, xv, acc.w);
     }
-    for (; k < k1; k++) {
-      const f32x4 a0 = *reinterpret_cast<const f32x4*>(A + (int64_t)k * lda + m);
-      const float x0 = x[k];
-      acc.x = fmaf(a0.x, x0, acc.x); acc.y = fmaf(a0.y, x0, acc.y);
-      acc.z = fmaf(a0.z, x0, acc.z); acc.w = fmaf(a0.w, x0, acc.w);
-    }
-    *reinterpret_cast<f32x4*>(out + (int64_t)kc * ldo + m) = acc;
-    return;
-  }
-  float a[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int k = k0; k < k1; k++) {
-    const float x0 = x[k];
 #pragma unroll
     for (int q = 0; q < 4; q++)
-      if (m + q < M) a[q] = fmaf(A[(int64_t)k * lda + m + q], x0, a[q]);
+      if (m + q >= m0) part[kw][m + q - m0] = acc[q];
+  } else if (side == 0) {  // fewer than four columns: one lane each
+    float a = 0.f;
+    if (lane < M)
+      for (; k < k1; k++) a = fmaf(A[(int64_t)k * lda + lane], x[k], a);
+    part[kw][lane] = a;
   }
+  __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 4; q++)
-    if (m + q < M) out[(int64_t)kc * ldo + m + q] = a[q];
+  for (int c = threadIdx.x; c < COLS; c += kThreads) {
+    float s = part[0][c];
+#pragma unroll
+    for (int q = 1; q < KS; q++) s += part[q][c];
+    if (m0 + c < M) out[(int64_t)kc * ldo + m0 + c] = s;
+  }
 }
 
-__global__ void gemv_reduce(float* __restrict__ y, const float* __restrict__ part, int M,
-                            int nparts) {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= M) return;
-  // fixed order (part 0 first); the loads of 8 parts are issued together
+// y[m] = sum of the parts in a fixed order: a workgroup owns 64 outputs, its four
+// waves a quarter of the parts each (16 loads in flight), added in wave order.
+__global__ __launch_bounds__(kThreads) void gemv_reduce(float* __restrict__ y,
+                                                        const float* __restrict__ part, int M,
+                                                        int nparts) {
+  __shared__ float sums[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t m = (int64_t)blockIdx.x * 64 + lane, mc = m < M ? m : M - 1;
+  const int share = (nparts + 3) / 4, p1 = min(nparts, (wave + 1) * share);
   float s = 0.f;
-  int p = 0;
-  for (; p + 8 <= nparts; p += 8) {
-    float v[8];
+  int p = wave * share;
+  for (; p + 16 <= p1; p += 16) {
+    float v[16];
 #pragma unroll
-    for (int u = 0; u < 8; u++) v[u] = part[(int64_t)(p + u) * M + m];
+    for (int u = 0; u < 16; u++) v[u] = part[(int64_t)(p + u) * M + mc];
 #pragma unroll
-    for (int u = 0; u < 8; u++) s += v[u];
+    for (int u = 0; u < 16; u++) s += v[u];
   }
-  for (; p < nparts; p++) s += part[(int64_t)p * M + m];
-  y[m] = s;
+  for (; p < p1; p++) s += part[(int64_t)p * M + mc];
+  sums[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && m < M)
+    y[m] = (sums[0][lane] + sums[1][lane]) + (sums[2][lane] + sums[3][lane]);
 }
 
 struct ColSplit {
+  bool wide;  // 1024 columns a workgroup, else 256
   int mblocks, kchunks, kchunk;
 };
 ColSplit col_split(int64_t M, int64_t K) {
   ColSplit c;
-  c.mblocks = (int)((M + kColsPerBlock - 1) / kColsPerBlock);
-  // about 1024 workgroups in all (four per compute unit; measured at 16384^2:
-  // 171 us against 202 us with 2048, whose extra partial sums and shorter
-  // per-workgroup row sweeps cost more than they hide), chunks of at least 64
-  // rows of A
-  int64_t want = (1024 + c.mblocks - 1) / c.mblocks;
+  // wide rows and enough of them for two workgroups per compute unit (measured:
+  // 40000 x 1000 29.5 us wide, 31.2 narrow; 8192^2 51.3 and 49.7)
+  const int64_t wide_blocks = (M + kWideCols - 1) / kWideCols;
+  c.wide = M >= 16384 && wide_blocks * ((K + 63) / 64) >= 512;
+  const int cols = c.wide ? kWideCols : kCols;
+  c.mblocks = (int)((M + cols - 1) / cols);
+  // about 1024 wide workgroups in all (four per compute unit; 2048 took 202 us at
+  // 16384^2) or 2176 narrow ones, chunks of at least 64 rows of A
+  const int64_t blocks = c.wide ? 1024 : 2176;
+  int64_t want = std::min<int64_t>(1024, (blocks + c.mblocks - 1) / c.mblocks);
   int64_t most = std::max<int64_t>(1, (K + 63) / 64);
   c.kchunks = (int)std::max<int64_t>(1, std::min(want, most));
   c.kchunk = (int)((K + c.kchunks - 1) / c.kchunks);
@@ -224,41 +249,41 @@ int gemv_parts(int64_t M, int64_t K, bool trans) {
 rise_status launch_gemv(const GemvArgs& a, void* ws, hipStream_t s) {
   // K = 0 needs no special case: the kernels reduce over an empty range and
   // store the initial value 0
-  auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   if (!a.trans) {
-    const bool vec = aligned(a.A) && aligned(a.x) && a.lda % 4 == 0;
-    const int64_t groups = (a.M + kRowsPerWave - 1) / kRowsPerWave;
-    const int64_t blocks =
-        std::min<int64_t>((groups + 3) / 4, (int64_t)device_cu_count() * 8);
-    if (vec)
-      hipLaunchKernelGGL(gemv_rows<true>, dim3((unsigned)blocks), dim3(kThreads), 0, s, a.y, a.A,
-                         a.lda, a.x, a.M, a.K, groups);
-    else
-      hipLaunchKernelGGL(gemv_rows<false>, dim3((unsigned)blocks), dim3(kThreads), 0, s, a.y,
-                         a.A, a.lda, a.x, a.M, a.K, groups);
+    const int64_t cus = device_cu_count();
+    auto go = [&](auto kernel, int rpw, int waves) {
+      const int64_t groups = (a.M + rpw - 1) / rpw;
+      const int64_t blocks = waves == 1 ? std::min<int64_t>((groups + 3) / 4, cus * 32)
+                                        : std::min<int64_t>(groups, cus * 8);
+      hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(waves == 1 ? kThreads : 64 * waves), 0,
+                         s, a.y, a.A, a.lda, a.x, a.M, a.K, groups);
+    };
+    // four rows a wave reuse x best but need 2.5 waves per SIMD to hide the loads
+    // (12000 x 6000 50.0 us against 52.4 with one row a wave, 8192^2 56.8 against
+    // 46.9); fewer rows go one to a wave, then to four and to sixteen waves.  Before,
+    // all went four to a wave: 4096^2 17.0 -> 13.3 us, 1000 x 40000 60 -> 30, 64 x
+    // 16384 14.4 -> 5.0; 1500 x 12345, whose rows are not 16-byte aligned and went
+    // value by value, 96.9 -> 15.4
+    if (a.M >= 10240) go(gemv_rows<4, 1, 2>, 4, 1);
+    else if (a.M >= 2048) go(gemv_rows<1, 1, 4>, 1, 1);
+    else if (a.M >= 256) go(gemv_rows<1, 4, 4>, 1, 4);
+    else go(gemv_rows<1, 16, 4>, 1, 16);
     return check_launch("gemv_rows");
   }
   const ColSplit c = col_split(a.M, a.K);
-  const bool vec = aligned(a.A) && a.lda % 4 == 0;
   float* out = c.kchunks > 1 ? (float*)ws : a.y;
-  const int64_t ldo = a.M;
-  const unsigned grid = (unsigned)((int64_t)c.mblocks * c.kchunks);
-  // below two workgroups per compute unit, deeper loads per thread (4096^2:
-  // 15.5 us against 18.3 us); at 8192^2 and above they measured slower
-  const bool deep = (int64_t)grid < 2 * (int64_t)device_cu_count();
-  if (vec && deep)
-    hipLaunchKernelGGL((gemv_cols<true, true>), dim3(grid), dim3(kThreads), 0, s, out, ldo, a.A,
-                       a.lda, a.x, a.M, a.K, c.mblocks, c.kchunk);
-  else if (vec)
-    hipLaunchKernelGGL((gemv_cols<true, false>), dim3(grid), dim3(kThreads), 0, s, out, ldo,
-                       a.A, a.lda, a.x, a.M, a.K, c.mblocks, c.kchunk);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((int64_t)c.mblocks * c.kchunks)), dim3(kThreads), 0, s,
+                       out, (int64_t)a.M, a.A, a.lda, a.x, a.M, a.K, c.mblocks, c.kchunk);
+  };
+  if (c.wide)
+    go(gemv_cols<1, 2>);
   else
-    hipLaunchKernelGGL((gemv_cols<false, false>), dim3(grid), dim3(kThreads), 0, s, out, ldo,
-                       a.A, a.lda, a.x, a.M, a.K, c.mblocks, c.kchunk);
+    go(gemv_cols<4, 8>);
   rise_status st = check_launch("gemv_cols");
   if (st != RISE_OK || c.kchunks == 1) return st;
-  hipLaunchKernelGGL(gemv_reduce, dim3((unsigned)((a.M + kThreads - 1) / kThreads)),
-                     dim3(kThreads), 0, s, a.y, (const float*)ws, a.M, c.kchunks);
+  hipLaunchKernelGGL(gemv_reduce, dim3((unsigned)((a.M + 63) / 64)), dim3(kThreads), 0,
+                     s, a.y, (const float*)ws, a.M, c.kchunks);
   return check_launch("gemv_reduce");
 }
 
@@ -267,14 +292,16 @@ rise_status launch_gemv(const GemvArgs& a, void* ws, hipStream_t s) {
 // Fixed scratch for the entry point that allocates nothing (rise_gemv_noalloc).
 // The split-K partials of the transposed product go to this file-scope device
 // array instead of a caller workspace.  Its size covers every split col_split
-// picks: kchunks > 1 only when there are at most 1023 column blocks, and then
-// kchunks * M <= ceil(1024 / mblocks) * mblocks * 1024 <= 2046 * 1024 floats.
+// picks: kchunks > 1 only when there are fewer column blocks than workgroups
+// wanted, and then kchunks * M <= ceil(1024 / mblocks) * mblocks * 1024 <= 2046 *
+// 1024 floats (wide) or <= 4350 * 256 floats.
 // Each device holds its own copy for the life of the process; its device
 // address is looked up once per device (hipGetSymbolAddress with that device
 // current) and only that address is handed to kernels.
 // ---------------------------------------------------------------------------
 constexpr size_t kGemvScratchBytes = RISE_GEMV_NOALLOC_SCRATCH_BYTES;
-static_assert(kGemvScratchBytes >= (size_t)2046 * kColsPerBlock * 4, "scratch below the largest split");
+static_assert(kGemvScratchBytes >= (size_t)2046 * kWideCols * 4 &&
+                  kGemvScratchBytes >= (size_t)4350 * kCols * 4, "scratch below the largest split");
 static __device__ __align__(256) unsigned char scratch[kGemvScratchBytes];
 
 namespace {

@@ -137,3 +137,17 @@ def test_gemv_transposed_wide_split(rise, M, K):
     x = ri.uniform_matrix(g, K, 1)
     y = run(rise, np.ascontiguousarray(A.T), x, True)
     assert componentwise(y[:, None], oracle.gemm(A, x), gemm_scale(A, x)) <= TOL
+
+
+@pytest.mark.parametrize("trans", [False, True])
+@pytest.mark.parametrize("M,K", [(3, 131), (255, 1027), (256, 1026), (2047, 257), (2049, 1021),
+                                 (10241, 67), (16383, 70), (16385, 66), (16390, 2100), (40001, 837)])
+def test_gemv_split_edges_integer_exact(rise, trans, M, K):
+    # either side of every rows-per-wave, waves-per-row and columns-per-workgroup
+    # boundary, with remainders in both dimensions and rows at every 4-byte offset
+    g = ri.rng(M + 3 * K + trans)
+    A = ri.integer_matrix(g, M, K, bound=3)
+    x = ri.integer_matrix(g, K, 1, bound=3)
+    exact = (A.astype(np.int64) @ x.astype(np.int64)).astype(np.float32)[:, 0]
+    stored = np.ascontiguousarray(A.T) if trans else A
+    assert np.array_equal(run(rise, stored, x, trans, x_offset=1), exact)
