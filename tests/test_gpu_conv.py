@@ -243,3 +243,40 @@ def test_autograd_layer(rise):
     check_out(decode(tx.grad), rin, sin)
     err = np.abs(host(tw.grad).astype(np.float64) - rw)
     assert np.all(err <= 1e-5 * sw + 1e-30)
+
+
+@pytest.mark.parametrize("Cin,Cout", [(16, 32), (32, 32), (32, 64), (64, 32), (64, 64)])
+@pytest.mark.parametrize("pad", ["zero", "clamp"])
+@pytest.mark.parametrize("B,H,W", [(1, 1, 1), (2, 2, 65), (1, 7, 128), (3, 37, 130), (1, 150, 63),
+                                   (181, 5, 129)])
+def test_row_segments_integer_exact(rise, Cin, Cout, pad, B, H, W):
+    # strips cut into segments of every remainder of three rows, one row to many,
+    # and (181 images) more segments than workgroups; small integers with at most
+    # 28 nonzero weights per sum of the layer, so all results are exact (the
+    # reference is torch's convolution of the same integers on the CPU)
+    import torch
+    import torch.nn.functional as F
+
+    g = ri.rng(B * 1000 + H * 10 + W + Cin + Cout)
+    x = torch.from_numpy(g.integers(-1, 2, size=(B, H, W, Cin)).astype(np.float32))
+    d = torch.from_numpy(g.integers(-1, 2, size=(B, H, W, Cout)).astype(np.float32))
+    w = torch.zeros(Cout, Cin, 9)
+    for k in range(3):
+        w[np.arange(Cout), np.arange(Cout) * (k + 1) % Cin, g.integers(0, 9, Cout)] = 1 - k % 2 * 2.0
+    w = w.reshape(Cout, Cin, 3, 3)
+    assert w.abs().sum((1, 2, 3)).max() <= 28 and w.abs().sum((0, 2, 3)).max() <= 28
+    xp = F.pad(x.permute(0, 3, 1, 2), (1, 1, 1, 1), mode="replicate" if pad == "clamp" else "constant")
+    wr = w.clone().requires_grad_()
+    out = F.conv2d(xp, wr)
+    out.backward(d.permute(0, 3, 1, 2))
+    print(f"conv segments B={B} {H}x{W} {Cin}->{Cout} pad={pad}", flush=True)
+    xb, db = x.to(torch.bfloat16).cuda(), d.to(torch.bfloat16).cuda()
+    got = rise.conv2d(xb, w.cuda(), pad=pad).float().cpu()
+    assert torch.equal(got, out.detach().permute(0, 2, 3, 1))
+    if Cin == 16:
+        return
+    dIn, dW = rise.conv2d_backward(db, xb, w.cuda(), pad=pad, need_din=pad == "zero")
+    assert torch.equal(dW.cpu(), wr.grad)
+    if pad == "zero":
+        ref = F.conv_transpose2d(d.permute(0, 3, 1, 2), w, padding=1).permute(0, 2, 3, 1)
+        assert torch.equal(dIn.float().cpu(), ref)
