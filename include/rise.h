@@ -462,11 +462,11 @@ typedef struct {
 } rise_stencil_problem;
 
 /* A plan owns the device copy of the problem descriptors, the work-item list
- * (every output tile of every problem, GEMM tiles largest estimated cost first)
- * and a HIP graph of  [reset the work counter] -> [one persistent GEMM kernel,
- * whose workgroups take tiles from the counter until none are left] -> [one
+ * (every output tile of every problem) and a HIP graph of  [reset the work
+ * counters] -> [one persistent GEMM kernel, whose workgroups take tiles, largest
+ * estimated cost first, from one queue per XCD until all are empty] -> [one
  * stencil kernel per window side and load width, one workgroup per tile].
- * Launches of one plan share its work counter, so they must not overlap:
+ * Launches of one plan share its work counters, so they must not overlap:
  * issue them on one stream, or order them with events.  The batch is the
  * outer map of the patterns: its items write distinct outputs, so any order
  * is correct (distinct output acceptors, paper Sec. V-C).  GEMM tile shapes

@@ -740,8 +740,8 @@ rise_status rise_autotune_batched(const char* table_path, void* stream) {
     return fail(RISE_ERR_UNSUPPORTED, "rise_autotune_batched: cannot write the table");
   }
   rise_status st = RISE_OK;
-  // time one plan (graph launches) and return the cost of one item slot in us:
-  // total time x concurrent workgroups / items
+  // time one plan (graph launches) and return the cost of one item in us: of a
+  // product total time x CUs / items, of a stencil x workgroups
   auto measure = [&](const rise_gemm_problem* g, const rise_stencil_problem* sp, int kind,
                      double* per_item) -> rise_status {
     PlanImpl* p = nullptr;
@@ -755,7 +755,8 @@ rise_status rise_autotune_batched(const char* table_path, void* stream) {
     hipEventSynchronize(e1);
     float ms = 0.f;
     hipEventElapsedTime(&ms, e0, e1);
-    *per_item = (double)ms * 1e3 / reps * plan_grid(p) / std::max(1, plan_items(p));
+    const int slots = g ? (int)device_cu_count() : plan_grid(p);
+    *per_item = (double)ms * 1e3 / reps * slots / std::max(1, plan_items(p));
     rise_plan_free(p);
     return RISE_OK;
   };

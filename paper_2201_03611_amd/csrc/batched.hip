@@ -6,13 +6,13 @@
 // descriptors and the work items, picks a tile shape for every GEMM from a
 // measured cost table, and captures one graph of persistent kernels, one per
 // class of tile, each with the registers and occupancy its tile needs:
-//   [reset counter] -> [GEMM tiles] -> [stencil tiles, one kernel per window
+//   [reset counters] -> [GEMM tiles] -> [stencil tiles, one kernel per window
 //   side and load width present]
-// In the GEMM kernel every workgroup repeatedly takes the next item (largest
-// estimated cost first) with one atomic add and runs the matching tile function
-// (tiles.h); the stencil tiles of one class cost the same, so the stencil
-// kernels walk their item list round-robin without a counter.  A batch costs
-// one graph launch instead of one launch per problem.
+// In the GEMM kernel every workgroup repeatedly takes the next item of its XCD's
+// queue (largest estimated cost first) with one atomic add and runs the matching
+// tile function (tiles.h); the stencil tiles of one class cost the same, so the
+// stencil kernels walk their item list round-robin without a counter.  A batch
+// costs one graph launch instead of one launch per problem.
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -47,7 +47,6 @@ struct KindShape {
 // windows up to 5 x 5 and 16 rows for 7 x 7, the one-problem kernel's choice.
 constexpr int kF32BK = 16;
 constexpr int kBf16BK = 64;  // bf16 slab depth: 64 k per barrier
-constexpr int kGemmOccupancy = 2;
 constexpr int stencil_rows(int k) { return k <= 5 ? 8 : 16; }
 const KindShape kShape[NUM_KINDS] = {
     {64, 64, kF32BK}, {64, 64, kF32BK}, {128, 64, kF32BK}, {128, 64, kF32BK},
@@ -74,14 +73,23 @@ struct Item {
 };
 
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
-// FP32 tiles: 2 x 2 waves, a ring of three slabs
+// FP32 tiles: four waves (2 x 2, or side by side along the longer dimension of a
+// tile of an odd number of 32s), a ring of three slabs
 template <int BM, int BN>
-using F32Tile = tiles::F32Cfg<BM, BN, kF32BK, 3, 2, 2, 1>;
-// the largest GEMM tile of any kind
+using F32Tile = tiles::F32Cfg<BM, BN, kF32BK, 3, BM % 64 == 0 && BN % 64 == 0 ? 2 : BM == 128 ? 4 : 1,
+                              BM % 64 == 0 && BN % 64 == 0 ? 2 : BM == 128 ? 1 : 4, 1>;
+// the largest GEMM tile of FP32 and of any kind
+constexpr int kF32LdsBytes = 16 * F32Tile<128, 128>::LDS_CHUNKS;
 constexpr int kGemmLdsBytes =
-    cmax(16 * F32Tile<128, 128>::LDS_CHUNKS,
-         16 * tiles::Bf16StagedCfg<128, 128, kBf16BK>::LDS_CHUNKS);
-static_assert(kGemmLdsBytes * kGemmOccupancy <= 160 * 1024, "LDS of the resident workgroups");
+    cmax(kF32LdsBytes, 16 * tiles::Bf16StagedCfg<128, 128, kBf16BK>::LDS_CHUNKS);
+// element types of a plan's products: a kernel holds the registers and LDS of the
+// largest tile it can run, so each set has its own.  FP32 alone fits three
+// workgroups per CU (512 products of 64 .. 1024: 1555 us with two, 1518 with three)
+enum { SET_F32 = 1, SET_BF16 = 2, SET_BOTH = 3 };
+constexpr int gemm_occupancy(int set) { return set == SET_F32 ? 3 : 2; }
+static_assert(kF32LdsBytes * gemm_occupancy(SET_F32) <= 160 * 1024 &&
+                  kGemmLdsBytes * gemm_occupancy(SET_BOTH) <= 160 * 1024,
+              "LDS of the resident workgroups");
 
 // A descriptor address as a pointer into global memory: built from the integer
 // through the global address space, so the compiler uses global (not flat)
@@ -91,70 +99,126 @@ __device__ __forceinline__ T* gptr(uint64_t v) {
   return (T*)((__attribute__((address_space(1))) T*)v);
 }
 
-template <int BM, int BN, bool TB>
-__device__ __noinline__ void item_f32(const Desc& d, int tm, int tn, char* lds) {
+template <int SET, int BM, int BN, bool TB>
+__device__ __noinline__ void item_f32(const Desc& d, int m0, int n0, char* lds) {
   const float* A = gptr<const float>(d.a);
   const float* B = gptr<const float>(d.b);
   float* C = gptr<float>(d.out);
   if (tiles::whole_chunks(A, d.lda, B, d.ldb, d.M, d.N, d.K, false, TB))
-    tiles::gemm_ring_tile<F32Tile<BM, BN>, false, TB, true>(
-        C, d.ldc, A, d.lda, B, d.ldb, d.M, d.N, d.K, tm * BM, tn * BN,
-        reinterpret_cast<f32x4*>(lds));
+    tiles::gemm_ring_tile<F32Tile<BM, BN>, false, TB, true>(C, d.ldc, A, d.lda, B, d.ldb, d.M, d.N,
+                                                            d.K, m0, n0,
+                                                            reinterpret_cast<f32x4*>(lds));
   else
-    tiles::gemm_ring_tile<F32Tile<BM, BN>, false, TB, false>(
-        C, d.ldc, A, d.lda, B, d.ldb, d.M, d.N, d.K, tm * BM, tn * BN,
-        reinterpret_cast<f32x4*>(lds));
+    tiles::gemm_ring_tile<F32Tile<BM, BN>, false, TB, false>(C, d.ldc, A, d.lda, B, d.ldb, d.M, d.N,
+                                                             d.K, m0, n0,
+                                                             reinterpret_cast<f32x4*>(lds));
 }
-template <int BM, int BN, bool TB>
-__device__ __noinline__ void item_bf16(const Desc& d, int tm, int tn, char* lds) {
+// A tile of a product cut into 128 x 128: the tiles of the last row and column are as
+// many 32s high and wide as the product has left (the corner tiles at least as
+// many).  Sizes of 64 .. 1024 in steps of 32 in whole 128 x 128 tiles are 18 %
+// padding, in the best of the whole tiles 14 % (512 products: 1518 -> 1475 us).
+template <int SET, bool TB>
+__device__ __forceinline__ void item_f32_128(const Desc& d, int m0, int n0, char* lds) {
+  const int r = min(4, (d.M - m0 + 31) / 32), c = min(4, (d.N - n0 + 31) / 32);
+  if (r > 2 && c > 2) {
+    if (c == 4) return r == 4 ? item_f32<SET, 128, 128, TB>(d, m0, n0, lds)
+                              : item_f32<SET, 96, 128, TB>(d, m0, n0, lds);
+    return item_f32<SET, 128, 96, TB>(d, m0, n0, lds);
+  }
+  if (r > 2) return c == 2 ? item_f32<SET, 128, 64, TB>(d, m0, n0, lds)
+                           : item_f32<SET, 128, 32, TB>(d, m0, n0, lds);
+  if (c > 2) return r == 2 ? item_f32<SET, 64, 128, TB>(d, m0, n0, lds)
+                           : item_f32<SET, 32, 128, TB>(d, m0, n0, lds);
+  return item_f32<SET, 64, 64, TB>(d, m0, n0, lds);
+}
+template <int SET, int BM, int BN, bool TB>
+__device__ __noinline__ void item_bf16(const Desc& d, int m0, int n0, char* lds) {
   tiles::gemm_bf16_tile<BM, BN, kBf16BK, TB>(gptr<float>(d.out), d.ldc, gptr<const uint16_t>(d.a),
                                         d.lda, gptr<const uint16_t>(d.b), d.ldb, d.M, d.N, d.K,
-                                        tm * BM, tn * BN, reinterpret_cast<i32x4*>(lds));
+                                        m0, n0, reinterpret_cast<i32x4*>(lds));
 }
+template <int SET>
 __device__ __forceinline__ void run_gemm_item(const Desc& d, int tile, char* lds) {
   const int tm = tile / d.tiles_n, tn = tile - tm * d.tiles_n;
-  switch (d.kind) {
-    case F32_64x64_N: item_f32<64, 64, false>(d, tm, tn, lds); break;
-    case F32_64x64_T: item_f32<64, 64, true>(d, tm, tn, lds); break;
-    case F32_128x64_N: item_f32<128, 64, false>(d, tm, tn, lds); break;
-    case F32_128x64_T: item_f32<128, 64, true>(d, tm, tn, lds); break;
-    case F32_64x128_N: item_f32<64, 128, false>(d, tm, tn, lds); break;
-    case F32_64x128_T: item_f32<64, 128, true>(d, tm, tn, lds); break;
-    case F32_128x128_N: item_f32<128, 128, false>(d, tm, tn, lds); break;
-    case F32_128x128_T: item_f32<128, 128, true>(d, tm, tn, lds); break;
-    case BF16_64x64_N: item_bf16<64, 64, false>(d, tm, tn, lds); break;
-    case BF16_64x64_T: item_bf16<64, 64, true>(d, tm, tn, lds); break;
-    case BF16_128x128_N: item_bf16<128, 128, false>(d, tm, tn, lds); break;
-    case BF16_128x128_T: item_bf16<128, 128, true>(d, tm, tn, lds); break;
-    default: break;
-  }
+  if constexpr (SET & SET_F32) switch (d.kind) {
+      case F32_64x64_N: return item_f32<SET, 64, 64, false>(d, 64 * tm, 64 * tn, lds);
+      case F32_64x64_T: return item_f32<SET, 64, 64, true>(d, 64 * tm, 64 * tn, lds);
+      case F32_128x64_N: return item_f32<SET, 128, 64, false>(d, 128 * tm, 64 * tn, lds);
+      case F32_128x64_T: return item_f32<SET, 128, 64, true>(d, 128 * tm, 64 * tn, lds);
+      case F32_64x128_N: return item_f32<SET, 64, 128, false>(d, 64 * tm, 128 * tn, lds);
+      case F32_64x128_T: return item_f32<SET, 64, 128, true>(d, 64 * tm, 128 * tn, lds);
+      case F32_128x128_N: return item_f32_128<SET, false>(d, 128 * tm, 128 * tn, lds);
+      case F32_128x128_T: return item_f32_128<SET, true>(d, 128 * tm, 128 * tn, lds);
+      default: break;
+    }
+  if constexpr (SET & SET_BF16) switch (d.kind) {
+      case BF16_64x64_N: return item_bf16<SET, 64, 64, false>(d, 64 * tm, 64 * tn, lds);
+      case BF16_64x64_T: return item_bf16<SET, 64, 64, true>(d, 64 * tm, 64 * tn, lds);
+      case BF16_128x128_N: return item_bf16<SET, 128, 128, false>(d, 128 * tm, 128 * tn, lds);
+      case BF16_128x128_T: return item_bf16<SET, 128, 128, true>(d, 128 * tm, 128 * tn, lds);
+      default: break;
+    }
 }
+
+// The GEMM items lie in one queue per XCD; workgroups of an XCD (b % 8) take from
+// its queue until it is empty, then from the others'.  A queue holds whole
+// problems, so a problem's rows and columns are read through one L2 instead of
+// all eight (512 FP32 products of 64 .. 1024: 1605 -> 1555 us, bf16 557 -> 524).
+struct Queues {
+  int first[kNumXcd], count[kNumXcd];
+};
+constexpr int kCounterStride = 32;  // a 128-byte line per queue's counter
 
 __global__ void reset_counter(int* counter) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0;
+  if (threadIdx.x < kNumXcd) counter[threadIdx.x * kCounterStride] = 0;
 }
 
-// Every workgroup takes items until the list is exhausted; the exit condition
-// (item >= n_items) is reached by every workgroup because the counter only grows.
-// The index of the following item is requested (thread 0, one atomic) while the
-// current item runs, so the atomic's round trip is off the critical path.
-__global__ __launch_bounds__(kThreads, kGemmOccupancy) void batched_gemm_kernel(
-    const Desc* __restrict__ descs, const Item* __restrict__ items, int n_items, int* counter) {
-  __shared__ __attribute__((aligned(16))) char lds[kGemmLdsBytes];
+// Every workgroup takes items until the queues are exhausted; the exit condition
+// (eight empty queues) is reached by every workgroup because the counters only
+// grow.  The index of the following item is requested (thread 0, one atomic) while
+// the current item runs, so the atomic's round trip is off the critical path; but
+// not when fewer than two items per workgroup are left: a workgroup holding two
+// of the last ones leaves others idle (2048^2 x 1024 in 256 tiles: 160 us, not so 88).
+// Between items the workgroup waits for its LDS reads alone: the stores of an
+// item drain while the next one loads.
+template <int SET>
+__global__ __launch_bounds__(kThreads, gemm_occupancy(SET)) void batched_gemm_kernel(
+    const Desc* __restrict__ descs, const Item* __restrict__ items, Queues queues, int* counter) {
+  __shared__ __attribute__((aligned(16))) char lds[SET == SET_F32 ? kF32LdsBytes : kGemmLdsBytes];
   __shared__ int next;
-  if (threadIdx.x == 0) next = atomicAdd(counter, 1);
+  // thread 0's queue, its ticket there, and the queues not yet empty
+  int queue = blockIdx.x % kNumXcd, ticket = 0, left = kNumXcd;
+  auto draw = [&] { return atomicAdd(counter + queue * kCounterStride, 1); };
+  // the item of the ticket drawn last, or of the first ticket another queue gives; -1
+  // when all are empty
+  auto item_of_ticket = [&] {
+    while (ticket >= queues.count[queue]) {
+      if (--left == 0) return -1;
+      queue = (queue + 1) % kNumXcd;
+      ticket = draw();
+    }
+    return queues.first[queue] + ticket;
+  };
+  if (threadIdx.x == 0) {
+    ticket = draw();
+    next = item_of_ticket();
+  }
   __syncthreads();
   int it = next;
-  for (;;) {
-    __syncthreads();  // every thread has read `next` before it is overwritten
-    if (it >= n_items) break;
-    int pre = 0;
-    if (threadIdx.x == 0) pre = atomicAdd(counter, 1);  // the following item
+  while (it >= 0) {
+    async::barrier();  // every thread has read `next` before it is overwritten
+    const bool early = ticket + 2 * (int)(gridDim.x / kNumXcd) < queues.count[queue];
+    if (threadIdx.x == 0 && early) ticket = draw();
     const Item item = items[it];
-    run_gemm_item(descs[item.desc], item.tile, lds);
-    if (threadIdx.x == 0) next = pre;
-    __syncthreads();  // the LDS buffer is free for the next item; `next` is visible
+    run_gemm_item<SET>(descs[item.desc], item.tile, lds);
+    if (threadIdx.x == 0) {
+      if (!early) ticket = draw();
+      next = item_of_ticket();
+    }
+    async::wait_lgkmcnt0();
+    async::barrier();  // the LDS buffer is free for the next item; `next` is visible
     it = next;
+    async::wait_lgkmcnt0();
   }
 }
 
@@ -213,13 +277,13 @@ const void* stencil_class_kernel(int c) {
 
 // Cost model of one tile: a + b * K microseconds (GEMM), a (stencil); measured
 // per kind by rise_autotune_batched and read from its table.  The built-in
-// values below were measured on an MI355X with that routine.
+// values below are relative ones, from batches of 16 .. 512 products on an MI355X.
 struct Cost {
   double a, b;
 };
 Cost g_default_cost[NUM_KINDS] = {
-    {1.0, 0.0040}, {1.0, 0.0042}, {1.2, 0.0068}, {1.2, 0.0070}, {1.2, 0.0068}, {1.2, 0.0070},
-    {1.5, 0.0125}, {1.5, 0.0128}, {1.0, 0.0014}, {1.0, 0.0016}, {1.5, 0.0040}, {1.5, 0.0044},
+    {0.4, 0.0033}, {0.4, 0.0033}, {0.7, 0.0064}, {0.7, 0.0064}, {0.7, 0.0064}, {0.7, 0.0064},
+    {1.5, 0.0125}, {1.5, 0.0125}, {1.0, 0.0014}, {1.0, 0.0016}, {1.5, 0.0040}, {1.5, 0.0044},
     {1.0, 0.0},    {1.5, 0.0},    {2.0, 0.0},    {2.5, 0.0},
     {1.5, 0.0},    {2.0, 0.0},    {2.5, 0.0},    {3.0, 0.0}};
 
@@ -246,12 +310,29 @@ bool load_costs(const char* path, Cost* cost) {
 
 int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
+// Estimated microseconds of tile (tm, tn).  The edge tiles of 128 x 128 FP32 kinds
+// are smaller: three hundredths of a whole tile's time per k do not shrink with the
+// area (the table's 64 x 64 against its 128 x 128 kind).
+double tile_cost(const Cost* cost, int kind, int M, int N, int K, int tm, int tn) {
+  double part = 1.0;
+  if (kind == F32_128x128_N || kind == F32_128x128_T) {
+    const int r = std::min(4, ceil_div(M - 128 * tm, 32));
+    const int c = std::min(4, ceil_div(N - 128 * tn, 32));
+    part = 0.03 + 0.97 * r * c / 16.0;
+  }
+  return cost[kind].a + cost[kind].b * K * part;
+}
 double gemm_cost(const Cost* cost, int kind, int M, int N, int K) {
-  const KindShape& s = kShape[kind];
-  return (double)ceil_div(M, s.bm) * ceil_div(N, s.bn) * (cost[kind].a + cost[kind].b * K);
+  // the four classes of tile: inner, last row, last column, corner
+  const int tm = ceil_div(M, kShape[kind].bm), tn = ceil_div(N, kShape[kind].bn);
+  if (tm == 0 || tn == 0) return 0;
+  auto at = [&](int i, int j) { return tile_cost(cost, kind, M, N, K, i, j); };
+  return (double)(tm - 1) * (tn - 1) * at(0, 0) + (tn - 1) * at(tm - 1, 0) +
+         (tm - 1) * at(0, tn - 1) + at(tm - 1, tn - 1);
 }
 
-int pick_gemm_kind(const Cost* cost, int dtype, int opB, int M, int N, int K, int forced) {
+int pick_gemm_kind(const Cost* cost, int dtype, int opB, int M, int N, int K, int forced,
+                   int most_area) {
   if (forced >= 0) return forced;
   const int t = opB == RISE_OP_T ? 1 : 0;
   int best = -1;
@@ -259,8 +340,37 @@ int pick_gemm_kind(const Cost* cost, int dtype, int opB, int M, int N, int K, in
   const int first = dtype == RISE_F32 ? F32_64x64_N : BF16_64x64_N;
   const int last = dtype == RISE_F32 ? F32_128x128_T : BF16_128x128_T;
   for (int k = first + t; k <= last; k += 2) {
+    if (kShape[k].bm * kShape[k].bn > most_area) continue;
     double c = gemm_cost(cost, k, M, N, K);
     if (best < 0 || c < best_c) best = k, best_c = c;
+  }
+  return best;
+}
+
+// The tile kind of every product: the cheapest for itself among tiles of at most
+// 128 x 128, 128 x 64 or 64 x 64, whichever of these lets the whole batch end first:
+// a CU's share of the work, and most of the largest tile for the uneven end.
+// FP32 products of 64 .. 1024: 16 of them (400 tiles of 128 x 128) take 125, 101 and
+// 96 us, 128 of them 395, 370 and 380, 512 of them 1399, 1436 and 1501.
+std::vector<int> pick_gemm_kinds(const Cost* cost, const rise_gemm_problem* g, int ng, int forced,
+                                 int cus) {
+  std::vector<int> best;
+  double best_end = 0;
+  for (int area : {128 * 128, 128 * 64, 64 * 64}) {
+    std::vector<int> kinds(ng);
+    for (int i = 0; i < ng; i++)
+      kinds[i] = pick_gemm_kind(cost, g[i].dtype, g[i].opB, (int)g[i].M, (int)g[i].N, (int)g[i].K,
+                                forced, area);
+    if (forced >= 0 || ng == 0) return kinds;
+    double sum = 0, largest = 0;
+    for (int i = 0; i < ng; i++) {
+      sum += gemm_cost(cost, kinds[i], (int)g[i].M, (int)g[i].N, (int)g[i].K);
+      if (g[i].M > 0 && g[i].N > 0)
+        largest = std::max(largest, tile_cost(cost, kinds[i], (int)g[i].M, (int)g[i].N,
+                                              (int)g[i].K, 0, 0));
+    }
+    const double end = sum / cus + 0.8 * largest;
+    if (best.empty() || end < best_end) best = kinds, best_end = end;
   }
   return best;
 }
@@ -320,8 +430,9 @@ rise_status check_stencil_problem(const rise_stencil_problem& p, int i) {
 
 }  // namespace
 
-// one kernel of a plan: items [first, first + count) of the item list;
-// cls = -1 is the GEMM kernel, else the stencil class (kind - STENCIL_1)
+// one kernel of a plan: cls = -1 is the GEMM kernel, which takes its items from
+// the plan's queues, else the stencil class (kind - STENCIL_1), items [first,
+// first + count) of the item list
 struct Launch {
   int cls, first, count, grid;
 };
@@ -331,6 +442,8 @@ struct PlanImpl {
   Item* d_items = nullptr;
   int* d_counter = nullptr;
   int n_items = 0;
+  int gemm_set = 0;  // element types of the products
+  Queues queues = {};
   std::vector<Launch> launches;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -339,7 +452,7 @@ struct PlanImpl {
 };
 
 namespace {
-// [reset counter] -> the plan's kernels, in order on one stream; the first
+// [reset counters] -> the plan's kernels, in order on one stream; the first
 // launch error, if any
 hipError_t enqueue(const PlanImpl* p, hipStream_t s) {
   hipLaunchKernelGGL(reset_counter, dim3(1), dim3(64), 0, s, p->d_counter);
@@ -348,8 +461,11 @@ hipError_t enqueue(const PlanImpl* p, hipStream_t s) {
     if (e != hipSuccess) break;
     const Item* items = p->d_items + l.first;
     if (l.cls < 0) {
-      hipLaunchKernelGGL(batched_gemm_kernel, dim3(l.grid), dim3(kThreads), 0, s, p->d_desc, items,
-                         l.count, p->d_counter);
+      auto kernel = p->gemm_set == SET_F32    ? batched_gemm_kernel<SET_F32>
+                    : p->gemm_set == SET_BF16 ? batched_gemm_kernel<SET_BF16>
+                                              : batched_gemm_kernel<SET_BOTH>;
+      hipLaunchKernelGGL(kernel, dim3(l.grid), dim3(kThreads), 0, s, p->d_desc, items, p->queues,
+                         p->d_counter);
       e = hipGetLastError();
     } else {
       void* args[] = {(void*)&p->d_desc, (void*)&items, (void*)&l.count};
@@ -381,16 +497,20 @@ rise_status plan_build(PlanImpl** out, const rise_gemm_problem* g, int ng,
   std::vector<double> unit;  // estimated microseconds per tile of each problem
   std::vector<int> ntile;
   auto plan = new PlanImpl();
+  int dev = 0, cus = 256;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+    cus = 256;
+  plan->kinds = pick_gemm_kinds(cost, g, ng, forced_kind, cus);
   for (int i = 0; i < ng; i++) {
     const rise_gemm_problem& p = g[i];
-    const int kind = pick_gemm_kind(cost, p.dtype, p.opB, (int)p.M, (int)p.N, (int)p.K,
-                                    forced_kind);
-    plan->kinds.push_back(kind);
+    const int kind = plan->kinds[i];
     const KindShape& s = kShape[kind];
     Desc d{(uint64_t)(uintptr_t)p.C, (uint64_t)(uintptr_t)p.A, (uint64_t)(uintptr_t)p.B, p.lda,
            p.ldb, p.ldc, (int)p.M, (int)p.N, (int)p.K, kind, ceil_div(p.N, s.bn), 0, 0};
     descs.push_back(d);
     ntile.push_back((p.M == 0 || p.N == 0) ? 0 : ceil_div(p.M, s.bm) * d.tiles_n);
+    plan->gemm_set |= kind < BF16_64x64_N ? SET_F32 : SET_BF16;
     unit.push_back(cost[kind].a + cost[kind].b * p.K);
   }
   for (int i = 0; i < ns; i++) {
@@ -413,11 +533,33 @@ rise_status plan_build(PlanImpl** out, const rise_gemm_problem* g, int ng,
   std::vector<int> order(descs.size());
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return unit[x] > unit[y]; });
-  std::vector<Item> items;
+  // A problem goes to the queue with the least estimated cost so far; one of more
+  // than a quarter of a queue's share is dealt over all of them tile by tile.
+  std::vector<Item> items, queue[kNumXcd];
+  double load[kNumXcd] = {}, gemm_us = 0;
+  std::vector<double> whole_cost(descs.size());
+  for (size_t i = 0; i < descs.size(); i++) {
+    const Desc& d = descs[i];
+    const bool gemm = d.kind < STENCIL_1;
+    whole_cost[i] = gemm ? gemm_cost(cost, d.kind, d.M, d.N, d.K) : unit[i] * ntile[i];
+    plan->est_us += whole_cost[i];
+    if (gemm) gemm_us += whole_cost[i];
+  }
   for (int d : order) {
-    plan->est_us += unit[d] * ntile[d];
-    if (descs[d].kind < STENCIL_1)
-      for (int t = 0; t < ntile[d]; t++) items.push_back(Item{d, t});
+    const Desc& g = descs[d];
+    if (g.kind >= STENCIL_1) continue;
+    const bool whole = whole_cost[d] <= gemm_us / kNumXcd / 4;
+    int q = (int)(std::min_element(load, load + kNumXcd) - load);
+    for (int t = 0; t < ntile[d]; t++) {
+      if (!whole && t) q = (q + 1) % kNumXcd;
+      queue[q].push_back(Item{d, t});
+      load[q] += tile_cost(cost, g.kind, g.M, g.N, g.K, t / g.tiles_n, t % g.tiles_n);
+    }
+  }
+  for (int q = 0; q < kNumXcd; q++) {
+    plan->queues.first[q] = (int)items.size();
+    plan->queues.count[q] = (int)queue[q].size();
+    items.insert(items.end(), queue[q].begin(), queue[q].end());
   }
   const int n_gemm_items = (int)items.size();
   int stencil_first[kStencilClasses], stencil_count[kStencilClasses];
@@ -430,13 +572,9 @@ rise_status plan_build(PlanImpl** out, const rise_gemm_problem* g, int ng,
   }
   plan->n_items = (int)items.size();
 
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-    cus = 256;
   if (n_gemm_items > 0)
     plan->launches.push_back(
-        Launch{-1, 0, n_gemm_items, std::max(1, std::min(n_gemm_items, kGemmOccupancy * cus))});
+        Launch{-1, 0, n_gemm_items, std::max(1, std::min(n_gemm_items, gemm_occupancy(plan->gemm_set) * cus))});
   for (int c = 0; c < kStencilClasses; c++)
     if (stencil_count[c] > 0)  // one workgroup per item
       plan->launches.push_back(Launch{c, stencil_first[c], stencil_count[c], stencil_count[c]});
@@ -445,7 +583,7 @@ rise_status plan_build(PlanImpl** out, const rise_gemm_problem* g, int ng,
   const size_t nd = std::max<size_t>(descs.size(), 1), ni = std::max<size_t>(items.size(), 1);
   if ((e = hipMalloc(&plan->d_desc, nd * sizeof(Desc))) != hipSuccess ||
       (e = hipMalloc(&plan->d_items, ni * sizeof(Item))) != hipSuccess ||
-      (e = hipMalloc(&plan->d_counter, 256)) != hipSuccess) {
+      (e = hipMalloc(&plan->d_counter, kNumXcd * kCounterStride * sizeof(int))) != hipSuccess) {
     rise_plan_free(plan);
     return fail(RISE_ERR_HIP, std::string("rise_plan_create: ") + hipGetErrorString(e));
   }

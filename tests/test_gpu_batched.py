@@ -301,3 +301,33 @@ def test_stencils_with_aligned_rows_and_ragged_width(rise):
         o = host(out)
         assert np.all(np.isnan(o[:, W:]))
         assert componentwise(o[:, :W], oracle.stencil2d(img, w, p), stencil_scale(img, w, p)) <= TOL
+
+
+@pytest.mark.parametrize("opB", [0, 1])
+@pytest.mark.parametrize("whole", [False, True])
+def test_f32_edge_tiles_integer_exact(rise, tmp_path, opB, whole):
+    # every remainder of 128 in steps of 32, and ragged ones, in both dimensions: the
+    # last row and column of 128 x 128 tiles (made the cheapest by a cost table) run
+    # smaller tiles; without the table small tiles are chosen.  Small integers: exact
+    import torch
+
+    table = tmp_path / "table.txt"
+    table.write_text("f32_128x128_N 0.1 0.001\nf32_128x128_T 0.1 0.001\n")
+    g = ri.rng(50 + opB)
+    side = [32, 64, 96, 128, 132, 160, 200, 224, 256, 292]
+    sizes = [(m, n, 20 + 4 * i) for i, m in enumerate(side) for n in side]
+    gemms = [dict(M=M, N=N, K=K, opB=opB, A=ri.integer_matrix(g, M, K, bound=3),
+                  B=ri.integer_matrix(g, K, N, bound=3), bf16=False) for M, N, K in sizes]
+    gp, sp, keep = to_device(rise, gemms, [])
+    plan = rise.Plan(gp, len(gemms), sp, 0, tune_table=str(table) if whole else None)
+    print(f"batch: {len(gemms)} f32 gemms, {plan.items()} items, opB={opB}", flush=True)
+    if whole:
+        assert {plan.tile(i)[:2] for i in range(len(gemms))} == {(128, 128)}
+    for p in gemms:
+        p["dC"].fill_(float("nan"))
+    plan.launch()
+    torch.cuda.synchronize()
+    for p in gemms:
+        exact = (p["A"].astype(np.int64) @ p["B"].astype(np.int64)).astype(np.float32)
+        assert np.array_equal(host(p["dC"]), exact), (p["M"], p["N"], p["K"])
+    plan.destroy()
