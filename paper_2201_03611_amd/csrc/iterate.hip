@@ -148,18 +148,19 @@ __device__ __forceinline__ void load_group(float (&v)[N], const float* p) {
   }
 }
 
-// Fan-ins 3 to 8, passes of at least one round: the first round runs in
+// Fan-ins 3 to 16, passes of at least one round: the first round runs in
 // registers straight from the loads, each thread folding whole groups of N
 // neighbours, so LDS holds one value per group (never the raw chunk) and the
 // later rounds run there as in iterate_sum_pass.  With an aligned chunk a
 // thread loads a unit of the fewest consecutive groups that stays 16-byte
-// aligned (one group for N = 4 and 8, two for 6, four for odd N) with 16-byte
-// loads; the groups past the last whole unit, unaligned chunks and every chunk
-// for N = 6 (whose two-group units measured slower) load group by group in
+// aligned (one group for N a multiple of 4, four for odd N) with 16-byte loads;
+// the groups past the last whole unit, unaligned chunks and every chunk for N =
+// 4 i + 2 (whose two-group units measured slower) load group by group in
 // 4-byte-aligned loads of up to 16 bytes.  The LDS tile is a sixth of
 // iterate_sum_pass's or less, so eight workgroups share a CU instead of three
 // and their loads overlap the other workgroups' LDS rounds.  The sums are the
-// same left folds from 0, in the same order.
+// same left folds from 0, in the same order.  (In iterate_sum_pass: 16^5 * 64
+// values 91 us, here 57; 9^7 * 12 79 and 43; 16^3 * 16 7.3 and 4.9.)
 template <int N>
 __global__ __launch_bounds__(kThreads) void iterate_sum_pass_first(
     float* __restrict__ dst, const float* __restrict__ src, int64_t len_out, int L, int G, int q,
@@ -318,6 +319,27 @@ __global__ __launch_bounds__(kThreads) void iterate_sum_pass_bin(
   if (lane < cnt && (lane & ((1 << r) - 1)) == 0) dst[g0 + (lane >> r)] = w;
 }
 
+// The kernel for fan-in n, if it has its own.
+decltype(&iterate_sum_pass_first<3>) pass_first(int64_t n) {
+  switch (n) {
+    case 3: return iterate_sum_pass_first<3>;
+    case 4: return iterate_sum_pass_first<4>;
+    case 5: return iterate_sum_pass_first<5>;
+    case 6: return iterate_sum_pass_first<6>;
+    case 7: return iterate_sum_pass_first<7>;
+    case 8: return iterate_sum_pass_first<8>;
+    case 9: return iterate_sum_pass_first<9>;
+    case 10: return iterate_sum_pass_first<10>;
+    case 11: return iterate_sum_pass_first<11>;
+    case 12: return iterate_sum_pass_first<12>;
+    case 13: return iterate_sum_pass_first<13>;
+    case 14: return iterate_sum_pass_first<14>;
+    case 15: return iterate_sum_pass_first<15>;
+    case 16: return iterate_sum_pass_first<16>;
+    default: return nullptr;
+  }
+}
+
 struct Pass {
   int L, G, q, a, R;
   int64_t len_in, len_out, blocks;
@@ -404,24 +426,10 @@ rise_status launch_iterate_sum(float* out, const float* in, int64_t n, int64_t m
     else if (p.L < 1)  // k = 0: a copy
       hipLaunchKernelGGL(iterate_sum_pass, grid, block, 0, s, dst, src, p.len_out, (int)n, p.L,
                          p.G, p.q, a, R, v);
-    else if (n == 3)
-      hipLaunchKernelGGL(iterate_sum_pass_first<3>, grid, block, 0, s, dst, src, p.len_out, p.L,
-                         p.G, p.q, v);
-    else if (n == 4)
-      hipLaunchKernelGGL(iterate_sum_pass_first<4>, grid, block, 0, s, dst, src, p.len_out, p.L,
-                         p.G, p.q, v);
-    else if (n == 5)
-      hipLaunchKernelGGL(iterate_sum_pass_first<5>, grid, block, 0, s, dst, src, p.len_out, p.L,
-                         p.G, p.q, v);
-    else if (n == 6)  // a group per 16 + 8-byte load pair beats units of two groups
-      hipLaunchKernelGGL(iterate_sum_pass_first<6>, grid, block, 0, s, dst, src, p.len_out, p.L,
-                         p.G, p.q, 0);
-    else if (n == 7)
-      hipLaunchKernelGGL(iterate_sum_pass_first<7>, grid, block, 0, s, dst, src, p.len_out, p.L,
-                         p.G, p.q, v);
-    else if (n == 8)
-      hipLaunchKernelGGL(iterate_sum_pass_first<8>, grid, block, 0, s, dst, src, p.len_out, p.L,
-                         p.G, p.q, v);
+    else if (auto first = pass_first(n))
+      hipLaunchKernelGGL(first, grid, block, 0, s, dst, src, p.len_out, p.L, p.G, p.q,
+                         // two groups per 16-byte-aligned unit lose to a group per thread
+                         n % 4 == 2 ? 0 : v);
     else
       hipLaunchKernelGGL(iterate_sum_pass, dim3((unsigned)p.blocks), dim3(kThreads), 0, s, dst,
                          src, p.len_out, (int)n, p.L, p.G, p.q, a, R, vec ? 1 : 0);

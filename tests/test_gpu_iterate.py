@@ -169,3 +169,13 @@ def test_convenience_wrapper(rise):
     y = rise.iterate_sum(x, 4, 5)
     G = 4 ** 5
     assert host(y).tolist() == [G * (2 * j * G + G - 1) / 2 for j in range(3)]
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2])
+@pytest.mark.parametrize("n", range(9, 18))
+def test_wide_fan_ins(rise, n, offset):
+    # fan-ins with a first round in registers (up to 16) and the first without, one
+    # round and two passes, whole and ragged last workgroups, at three alignments
+    for m, k in [(1, 1), (3, 2), (1001, 1), (8192 // n * 4, 1), (5, 4), (16, 3)]:
+        x = ri.uniform_matrix(ri.rng(9300 + n * 7 + m), m, n ** k).reshape(-1)
+        check(rise, x, n, m, k, offset=offset)
