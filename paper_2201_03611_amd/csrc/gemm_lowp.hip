@@ -622,15 +622,17 @@ __global__ __launch_bounds__(kThreads, 1) void packed_kblock_kernel(
 // replaced the register-staged kernel (1156 us with preparation) and, for bf16,
 // the K-blocked one (1.77 M cycles).  The clock falls to 1.4-1.75 GHz under this
 // load, so time no longer follows cycles one for one.
-template <typename T, bool TA, bool TB, bool KBLOCKED = false>
+template <typename T, bool TA, bool TB, bool KBLOCKED = false, int PARTS = 1>
 __global__ __launch_bounds__(T::THREADS, T::WAVES / 4) void gemm_bf16_kernel(
     float* __restrict__ C, int64_t ldc, const uint16_t* __restrict__ A, int64_t lda,
-    const uint16_t* __restrict__ B, int64_t ldb, int M, int N, int K, int tiles_m, int tiles_n) {
+    const uint16_t* __restrict__ B, int64_t ldb, int M, int N, int K, int tiles_m, int tiles_n,
+    int64_t plane_a, int64_t plane_b) {
   __shared__ f32x4 lds[T::LDS_CHUNKS];
   int tm, tn;
   grouped_tile(xcd_contiguous(blockIdx.x, gridDim.x), tiles_m, tiles_n, 4, tm, tn);
-  tiles::gemm_ring_tile<T, TA, TB, true, KBLOCKED>(C, ldc, A, lda, B, ldb, M, N, K, tm * T::BM,
-                                                   tn * T::BN, lds);
+  tiles::gemm_ring_tile<T, TA, TB, true, KBLOCKED, PARTS>(C, ldc, A, lda, B, ldb, M, N, K,
+                                                          tm * T::BM, tn * T::BN, lds, plane_a,
+                                                          plane_b);
 }
 
 template <typename T>
@@ -639,10 +641,11 @@ rise_status launch_ring(const GemmLowpArgs& a, bool kblocked, hipStream_t s) {
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n), dim3(T::THREADS), 0, s, a.C, a.ldc,
                        (const uint16_t*)a.A, a.lda, (const uint16_t*)a.B, a.ldb, a.M, a.N, a.K,
-                       tiles_m, tiles_n);
+                       tiles_m, tiles_n, (int64_t)0, (int64_t)0);
   };
   if (kblocked) {
-    if constexpr (T::BM == 256 && T::BN == 256 && T::BK == 32) go(gemm_bf16_kernel<T, false, true, true>);
+    if constexpr (T::BM == 256 && T::BN == 256 && T::BK == 32)
+      go(gemm_bf16_kernel<T, false, true, true>);
   } else if (!a.ta && !a.tb) go(gemm_bf16_kernel<T, false, false>);
   else if (!a.ta) go(gemm_bf16_kernel<T, false, true>);
   else if (!a.tb) go(gemm_bf16_kernel<T, true, false>);
@@ -650,10 +653,29 @@ rise_status launch_ring(const GemmLowpArgs& a, bool kblocked, hipStream_t s) {
   return check_launch("gemm_bf16_kernel");
 }
 
+// Split bf16 operands on the same ring: a product of parts after the other, each over
+// all k.  The packed kernel multiplies all parts of a slab at once, so it reads each
+// part once, but needs 128 x 128 tiles and registers to stage them (with preparation,
+// bf16x3 and bf16x6: 512^3 21.7 -> 14.8 and 36 -> 19.5 us, 3000 x 700 x 5000 143 -> 120
+// and 329 -> 213, 2048 x 4096 x 4096 227 -> 202 and 500 -> 367).
+template <typename T, int PARTS>
+rise_status launch_ring_parts(const PackedGemm& g, hipStream_t s) {
+  const int tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
+  hipLaunchKernelGGL((gemm_bf16_kernel<T, false, true, false, PARTS>), dim3(tiles_m * tiles_n),
+                     dim3(T::THREADS), 0, s, g.C, g.ldc, (const uint16_t*)g.Ap, (int64_t)g.Kp,
+                     (const uint16_t*)g.Bp, (int64_t)g.Kp, g.M, g.N, g.Kp, tiles_m, tiles_n,
+                     (int64_t)g.Mp * g.Kp, (int64_t)g.Np * g.Kp);
+  return check_launch("gemm_bf16_kernel");
+}
+
 // The tiles; for BF16, nanoseconds per 64 x 64 outputs and k that one CU takes
 // on them (measured: 256 x 256 at 8192^3, 256 x 128 and 128 x 128 at 2048 x 4096 x
 // 4096, the smaller ones at 1024^3 and 512 x 2048 x 4096; the matrix cores alone
-// need 0.84 at 2.4 GHz), 0: only where asked for.
+// need 0.84 at 2.4 GHz), 0: only where asked for.  The split modes run the same tiles
+// a product of parts after the other, so their rows are BF16's; their K-blocked 256 x
+// 256 x 16 kernels count against these (4096^3: bf16x3 362 us against 385 in 256 x
+// 128, bf16x6 620 against 704; 2048 x 4096 x 4096, with half the CUs idle, 281
+// against 204 and 494 against 375).
 struct TileRow {
   rise_mode mode;
   rise_tile t;
@@ -664,12 +686,21 @@ const TileRow kTiles[] = {
     {RISE_MODE_BF16, {256, 256, 32}, 1.65}, {RISE_MODE_BF16, {256, 128, 64}, 1.68},
     {RISE_MODE_BF16, {128, 256, 64}, 1.68}, {RISE_MODE_BF16, {128, 64, 64}, 2.5},
     {RISE_MODE_BF16, {64, 64, 64}, 4.2},    {RISE_MODE_BF16, {64, 64, 128}, 3.2},
-    {RISE_MODE_BF16, {64, 32, 128}, 4.6},   {RISE_MODE_BF16X3, {256, 256, 16}},
-    {RISE_MODE_BF16X3, {256, 256, 32}},     {RISE_MODE_BF16X3, {128, 128, 32}},
-    {RISE_MODE_BF16X6, {256, 256, 16}},     {RISE_MODE_BF16X6, {128, 128, 16}},
+    {RISE_MODE_BF16, {64, 32, 128}, 4.6},
+    {RISE_MODE_BF16X3, {256, 256, 16}, 1.58}, {RISE_MODE_BF16X3, {256, 256, 32}},
+    {RISE_MODE_BF16X3, {128, 128, 32}},       {RISE_MODE_BF16X3, {256, 128, 64}, 1.68},
+    {RISE_MODE_BF16X3, {128, 256, 64}, 1.68}, {RISE_MODE_BF16X3, {128, 128, 64}, 1.9},
+    {RISE_MODE_BF16X3, {128, 64, 64}, 2.5},   {RISE_MODE_BF16X3, {64, 64, 64}, 4.2},
+    {RISE_MODE_BF16X3, {64, 64, 128}, 3.2},   {RISE_MODE_BF16X3, {64, 32, 128}, 4.6},
+    {RISE_MODE_BF16X6, {256, 256, 16}, 1.48}, {RISE_MODE_BF16X6, {128, 128, 16}},
+    {RISE_MODE_BF16X6, {256, 128, 64}, 1.68}, {RISE_MODE_BF16X6, {128, 256, 64}, 1.68},
+    {RISE_MODE_BF16X6, {128, 128, 64}, 1.9},  {RISE_MODE_BF16X6, {128, 64, 64}, 2.5},
+    {RISE_MODE_BF16X6, {64, 64, 64}, 4.2},    {RISE_MODE_BF16X6, {64, 64, 128}, 3.2},
+    {RISE_MODE_BF16X6, {64, 32, 128}, 4.6},
     {RISE_MODE_FP8, {256, 256, 128}},       {RISE_MODE_FP8, {128, 128, 128}},
 };
-constexpr int kLongK = 2048;  // from here 64 x 64 x 128 beats 64 x 64 x 64 (4096: 17.5 against 21 us)
+// k of all products from which 64 x 64 x 128 beats 64 x 64 x 64 (4096: 17.5 against 21 us)
+constexpr int kLongK = 2048;
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
@@ -721,14 +752,15 @@ bool gemm_lowp_tile_supported(rise_mode mode, const rise_tile& t) {
 }
 
 rise_tile gemm_lowp_default_tile(rise_mode mode, int M, int N, int K) {
-  if (mode == RISE_MODE_BF16) {
+  if (mode != RISE_MODE_FP8) {
     // the shortest time for the CU that gets the most tiles (as for FP32: what the
     // shapes differ in is mainly how evenly they cover 256 CUs)
+    const int64_t k = (int64_t)K * (mode == RISE_MODE_BF16 ? 1 : mode == RISE_MODE_BF16X3 ? 3 : 6);
     rise_tile best{128, 128, 64};
     double least = 0;
     for (const auto& r : kTiles) {
       if (r.mode != mode || r.ns == 0) continue;
-      if (r.t.bm == 64 && r.t.bn == 64 && (r.t.bk == 128) != (K > kLongK)) continue;
+      if (r.t.bm == 64 && r.t.bn == 64 && (r.t.bk == 128) != (k > kLongK)) continue;
       const int64_t tiles =
           (((int64_t)M + r.t.bm - 1) / r.t.bm) * (((int64_t)N + r.t.bn - 1) / r.t.bn);
       const double t = (double)((tiles + 255) / 256) * r.t.bm * r.t.bn * r.ns;
@@ -736,18 +768,10 @@ rise_tile gemm_lowp_default_tile(rise_mode mode, int M, int N, int K) {
     }
     return best;
   }
-  // 256 x 256 when it still gives every CU a tile, else 128 x 128; at 256 x
-  // 256 the K-blocked kernel where it is the faster one (measured at 8192^3
-  // with preparation: bf16x3 2.71-2.91 against 3.12-3.18 ms for 256 x 256
-  // x 32, bf16x6 5.06 against 6.78 ms for the row-major 256 x 256 x 16 tile,
-  // fp8 0.62 against 0.83 ms for 128 x 128)
-  long tiles_big = (long)((M + 255) / 256) * ((N + 255) / 256);
-  const bool big = tiles_big >= 256;
-  switch (mode) {
-    case RISE_MODE_BF16X3: return big ? rise_tile{256, 256, 16} : rise_tile{128, 128, 32};
-    case RISE_MODE_BF16X6: return big ? rise_tile{256, 256, 16} : rise_tile{128, 128, 16};
-    default: return big ? rise_tile{256, 256, 128} : rise_tile{128, 128, 128};
-  }
+  // 256 x 256, K-blocked, when it still gives every CU a tile, else 128 x 128
+  // (8192^3 with preparation 0.62 against 0.83 ms)
+  const int64_t big = ((int64_t)(M + 255) / 256) * ((N + 255) / 256);
+  return big >= 256 ? rise_tile{256, 256, 128} : rise_tile{128, 128, 128};
 }
 
 size_t gemm_lowp_workspace(int M, int N, int K, rise_mode mode, const rise_tile& t) {
@@ -766,15 +790,54 @@ int packed_kblock(rise_mode mode, const rise_tile& t) {
   return 0;
 }
 
+namespace {
+// calls go(RingCfg<...>) with the ring configuration of a tile
+template <typename Go>
+rise_status with_ring_tile(const rise_tile& t, Go go) {
+#define RISE_BF16_TILE(BM, BN, BK, ...)       \
+  if (t.bm == BM && t.bn == BN && t.bk == BK) \
+    return go(static_cast<tiles::Bf16Cfg<BM, BN, BK, __VA_ARGS__>*>(nullptr));
+  RISE_BF16_TILE(256, 128, 64, 3, 4, 2, 1)
+  RISE_BF16_TILE(128, 256, 64, 3, 2, 4, 1)
+  RISE_BF16_TILE(128, 128, 64, 3, 4, 2, 1)
+  RISE_BF16_TILE(128, 64, 64, 3, 2, 2, 2)
+  RISE_BF16_TILE(64, 64, 64, 3, 2, 2, 2)
+  RISE_BF16_TILE(64, 64, 128, 3, 2, 2, 4)
+  RISE_BF16_TILE(64, 32, 128, 3, 2, 1, 4)
+  RISE_BF16_TILE(256, 256, 64, 2, 2, 4, 1)
+  RISE_BF16_TILE(256, 256, 32, 4, 2, 4, 1)
+#undef RISE_BF16_TILE
+  return fail(RISE_ERR_UNSUPPORTED, "gemm_bf16: unsupported tile");
+}
+rise_status launch_bf16_tile(const GemmLowpArgs& a, const rise_tile& t, bool kblocked,
+                             hipStream_t s) {
+  return with_ring_tile(t, [&](auto* cfg) {
+    return launch_ring<std::remove_pointer_t<decltype(cfg)>>(a, kblocked, s);
+  });
+}
+template <int PARTS>
+rise_status launch_parts_tile(const PackedGemm& g, const rise_tile& t, hipStream_t s) {
+  return with_ring_tile(t, [&](auto* cfg) {
+    using T = std::remove_pointer_t<decltype(cfg)>;
+    if constexpr (T::BM == 256 && T::BN == 256)
+      return fail(RISE_ERR_UNSUPPORTED, "packed gemm: tile");
+    else
+      return launch_ring_parts<T, PARTS>(g, s);
+  });
+}
+}  // namespace
+
 rise_status launch_packed_gemm(const PackedGemm& g, const rise_tile& t, hipStream_t s) {
   if (g.kblock != packed_kblock(g.mode, t))
     return fail(RISE_ERR_UNSUPPORTED, "packed gemm: operand layout does not match the tile");
   switch (g.mode) {
     case RISE_MODE_BF16X3:
+      if (t.bk >= 64) return launch_parts_tile<2>(g, t, s);
       if (t.bm == 256 && t.bk == 16) return launch_kblock<RISE_MODE_BF16X3>(g, s);
       if (t.bm == 256) return launch_bf16<256, 256, 32, RISE_MODE_BF16X3>(g, s);
       return launch_bf16<128, 128, 32, RISE_MODE_BF16X3>(g, s);
     case RISE_MODE_BF16X6:
+      if (t.bk >= 64) return launch_parts_tile<3>(g, t, s);
       if (t.bm == 256) return launch_kblock<RISE_MODE_BF16X6>(g, s);
       return launch_bf16<128, 128, 16, RISE_MODE_BF16X6>(g, s);
     case RISE_MODE_FP8:
@@ -784,26 +847,6 @@ rise_status launch_packed_gemm(const PackedGemm& g, const rise_tile& t, hipStrea
       return fail(RISE_ERR_UNSUPPORTED, "packed gemm: mode");
   }
 }
-
-namespace {
-rise_status launch_bf16_tile(const GemmLowpArgs& a, const rise_tile& t, bool kblocked,
-                             hipStream_t s) {
-#define RISE_BF16_TILE(BM, BN, BK, ...)               \
-  if (t.bm == BM && t.bn == BN && t.bk == BK)         \
-    return launch_ring<tiles::Bf16Cfg<BM, BN, BK, __VA_ARGS__>>(a, kblocked, s);
-  RISE_BF16_TILE(256, 256, 64, 2, 2, 4, 1)
-  RISE_BF16_TILE(256, 256, 32, 4, 2, 4, 1)
-  RISE_BF16_TILE(256, 128, 64, 3, 4, 2, 1)
-  RISE_BF16_TILE(128, 256, 64, 3, 2, 4, 1)
-  RISE_BF16_TILE(128, 128, 64, 3, 4, 2, 1)
-  RISE_BF16_TILE(128, 64, 64, 3, 2, 2, 2)
-  RISE_BF16_TILE(64, 64, 64, 3, 2, 2, 2)
-  RISE_BF16_TILE(64, 64, 128, 3, 2, 2, 4)
-  RISE_BF16_TILE(64, 32, 128, 3, 2, 1, 4)
-#undef RISE_BF16_TILE
-  return fail(RISE_ERR_UNSUPPORTED, "gemm_bf16: unsupported tile");
-}
-}  // namespace
 
 rise_status launch_gemm_lowp(const GemmLowpArgs& a, const rise_tile& t, void* ws, hipStream_t s) {
   // bf16 operands whose rows are whole 16-byte chunks are read where they are (a

@@ -218,12 +218,16 @@ __host__ __device__ inline bool whole_chunks(const V* A, int64_t lda, const V* B
 // KBLOCKED: both operands prepared K-blocked (K block b of row r holds BK values
 // at (b * rows + r) * BK, zero padded to whole tiles): lda and ldb are then the
 // operands' row counts.
-template <typename T, bool TA, bool TB, bool VEC, bool KBLOCKED = false,
+// PARTS > 1: the operands are prepared as that many planes (plane_a and plane_b values
+// apart, K whole slabs) whose sum they are, and C is the sum of the products of parts
+// i, j with i + j < PARTS, each over all k, small products first.
+template <typename T, bool TA, bool TB, bool VEC, bool KBLOCKED = false, int PARTS = 1,
           typename V = typename T::Elem::Value>
 __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ldc,
                                                const V* __restrict__ A, int64_t lda,
                                                const V* __restrict__ B, int64_t ldb, int M, int N,
-                                               int K, int m0, int n0, f32x4* lds_base) {
+                                               int K, int m0, int n0, f32x4* lds_base,
+                                               int64_t plane_a = 0, int64_t plane_b = 0) {
   typedef typename T::Elem E;
   constexpr int BM = T::BM, BN = T::BN, BK = T::BK, STAGES = T::STAGES, KG = T::KG;
   constexpr int TM = T::TM, TN = T::TN, SL = T::SL, NW = T::WAVES;
@@ -264,7 +268,9 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
     int k;
     off[j] = (uint32_t)sizeof(V) * (uint32_t)index(j, lane, k);
   }
-  const int nk = (K + BK - 1) / BK, krem = K - (nk - 1) * BK;
+  constexpr int PRODUCTS = PARTS * (PARTS + 1) / 2;
+  static_assert(PARTS == 1 || (!TA && TB && VEC && !KBLOCKED && PARTS <= 3), "prepared planes");
+  const int nk1 = (K + BK - 1) / BK, krem = K - (nk1 - 1) * BK, nk = PRODUCTS * nk1;
   const bool wide = lda >= kF32OffsetLd || ldb >= kF32OffsetLd;
   // the next slab to copy (its first value in the tile's first row or column);
   // past the last slab the last one is copied again, into a stage nothing reads
@@ -272,6 +278,15 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
   const V* pb = async::uniform(B + (TB ? (int64_t)n0 * ldb : n0));
   constexpr uint32_t STAGE_BYTES = SL * 16;
   const uint32_t lds0 = async::lds_address(lds_base);
+  // parts of product q (as in the packed kernels), two bits each
+  constexpr uint32_t PART_A = 2 << 10 | 1 << 8 | 0 << 6 | 1 << 4 | 0 << 2 | 0;
+  constexpr uint32_t PART_B = 0 << 10 | 1 << 8 | 2 << 6 | 0 << 4 | 1 << 2 | 0;
+  const V *pa0 = pa, *pb0 = pb;
+  int product = PRODUCTS - 1, left = nk1;  // (PARTS > 1) the slab's product, its slabs to come
+  if (PARTS > 1) {
+    pa += (PART_A >> 2 * product & 3) * plane_a;
+    pb += (PART_B >> 2 * product & 3) * plane_b;
+  }
   int next = 0;      // that slab
   uint32_t put = 0;  // and the byte offset of its ring stage
   // copy j of that slab.  careful: it may be the last slab of a ragged K, or rows
@@ -291,8 +306,15 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
     }
   };
   auto advance = [&] {
-    pa += next < nk - 1 ? step_a : 0;
-    pb += next < nk - 1 ? step_b : 0;
+    if (PARTS > 1 && --left == 0 && product > 0) {
+      product--;
+      left = nk1;
+      pa = pa0 + (PART_A >> 2 * product & 3) * plane_a;
+      pb = pb0 + (PART_B >> 2 * product & 3) * plane_b;
+    } else {
+      pa += next < nk - 1 ? step_a : 0;
+      pb += next < nk - 1 ? step_b : 0;
+    }
     next++;
     put = put == (STAGES - 1) * STAGE_BYTES ? 0 : put + STAGE_BYTES;
   };

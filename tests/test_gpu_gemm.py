@@ -382,3 +382,22 @@ def test_precision_config_sampled(rise):
     print("componentwise error vs exact product:", errs, flush=True)
     assert errs["f32"] <= TOL_F32 and errs["bf16x3"] <= TOL_F32 and errs["bf16x6"] <= TOL_F32
     assert errs["bf16"] <= 2.0 ** -7 and errs["fp8"] <= 2.0 ** -3
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (65, 31, 64), (130, 257, 63), (70, 129, 65),
+                                   (300, 70, 129)])
+@pytest.mark.parametrize("mode,bits", [("bf16x3", 15), ("bf16x6", 17)])
+@pytest.mark.parametrize("wide_b", [False, True])
+def test_split_parts_integer_exact(rise, mode, bits, M, N, K, wide_b):
+    # one operand of integers that need all parts (signed, 15 or 17 bits), the other of
+    # -1, 0, 1: every product and sum is below 2^24, so the kept products of parts
+    # add up exactly; one, two and three slabs per product, every tile
+    g = ri.rng(60 + M + K + bits)
+    wide, small = (lambda r, c: ri.integer_matrix(g, r, c, bound=2 ** bits - 1),
+                   lambda r, c: ri.integer_matrix(g, r, c, bound=1))
+    A, B = (small(M, K), wide(K, N)) if wide_b else (wide(M, K), small(K, N))
+    exact = A.astype(np.int64) @ B.astype(np.int64)
+    assert (np.abs(A.astype(np.int64)) @ np.abs(B.astype(np.int64))).max() < 2 ** 24
+    for tile in rise.rise_gemm_tiles(mode):
+        C = run(rise, A, B, mode=mode, tile=tile)
+        assert np.array_equal(C, exact.astype(np.float32)), tile
