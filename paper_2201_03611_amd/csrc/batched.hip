@@ -78,10 +78,15 @@ constexpr int cmax(int a, int b) { return a > b ? a : b; }
 template <int BM, int BN>
 using F32Tile = tiles::F32Cfg<BM, BN, kF32BK, 3, BM % 64 == 0 && BN % 64 == 0 ? 2 : BM == 128 ? 4 : 1,
                               BM % 64 == 0 && BN % 64 == 0 ? 2 : BM == 128 ? 1 : 4, 1>;
+// bf16 tiles: two slabs of the 128 x 128 ring for two workgroups a CU (512 products of
+// 64 .. 1024: staged through registers 494 us, so 457; three workgroups with slabs
+// of 32 k, whose rows are half lines, 497)
+template <int BM, int BN>
+using Bf16Tile = tiles::Bf16Cfg<BM, BN, kBf16BK, BM == 128 ? 2 : 3, 2, 2, 1>;
 // the largest GEMM tile of FP32 and of any kind
 constexpr int kF32LdsBytes = 16 * F32Tile<128, 128>::LDS_CHUNKS;
 constexpr int kGemmLdsBytes =
-    cmax(kF32LdsBytes, 16 * tiles::Bf16StagedCfg<128, 128, kBf16BK>::LDS_CHUNKS);
+    cmax(kF32LdsBytes, 16 * Bf16Tile<128, 128>::LDS_CHUNKS);
 // element types of a plan's products: a kernel holds the registers and LDS of the
 // largest tile it can run, so each set has its own.  FP32 alone fits three
 // workgroups per CU (512 products of 64 .. 1024: 1555 us with two, 1518 with three)
@@ -133,9 +138,9 @@ __device__ __forceinline__ void item_f32_128(const Desc& d, int m0, int n0, char
 }
 template <int SET, int BM, int BN, bool TB>
 __device__ __noinline__ void item_bf16(const Desc& d, int m0, int n0, char* lds) {
-  tiles::gemm_bf16_tile<BM, BN, kBf16BK, TB>(gptr<float>(d.out), d.ldc, gptr<const uint16_t>(d.a),
-                                        d.lda, gptr<const uint16_t>(d.b), d.ldb, d.M, d.N, d.K,
-                                        m0, n0, reinterpret_cast<i32x4*>(lds));
+  tiles::gemm_ring_tile<Bf16Tile<BM, BN>, false, TB, true>(
+      gptr<float>(d.out), d.ldc, gptr<const uint16_t>(d.a), d.lda, gptr<const uint16_t>(d.b), d.ldb,
+      d.M, d.N, d.K, m0, n0, reinterpret_cast<f32x4*>(lds));
 }
 template <int SET>
 __device__ __forceinline__ void run_gemm_item(const Desc& d, int tile, char* lds) {

@@ -443,161 +443,6 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
 }
 
 // ===========================================================================
-// BF16 GEMM tile for bf16-stored operands (v_mfma_f32_32x32x16_bf16, FP32
-// accumulation): A is M x K row-major; B is either N x K (TB, K contiguous, read
-// directly) or K x N (read through transpose: each 8-element chunk along N is
-// scattered into the K-contiguous LDS layout).  Requires lda, ldb multiples of 8
-// and 16-byte aligned bases; K ragged in units of 8 (zero-filled chunks).
-// ===========================================================================
-template <int BM, int BN, int BK>
-struct Bf16StagedCfg {
-  static constexpr int CH = BK / 8;  // 16-byte chunks per slab row
-  // B stored K x N sits in LDS as stored: BK rows of BN values, the row pitch
-  // padded by 64 bytes so the four rows one transposed read touches fall in
-  // four different quarters of a 256-byte bank line
-  static constexpr int BPITCH = BN * 2 + 64;  // bytes
-  static constexpr int B_KN_CHUNKS = 2 * BK * BPITCH / 16;
-  static constexpr int LDS_CHUNKS =
-      2 * BM * CH + (2 * BN * CH > B_KN_CHUNKS ? 2 * BN * CH : B_KN_CHUNKS);
-};
-
-// row r, 16-byte chunk c -> LDS chunk index; the XOR key changes every 16/CH rows
-// so 16 consecutive rows at one logical chunk hit distinct slots of a 256-byte
-// (64-bank) line
-template <int CH>
-__device__ __forceinline__ int swz16(int r, int c) {
-  constexpr int per = 16 / CH;  // rows sharing one 256-byte bank line
-  return r * CH + (c ^ ((r / per) % CH));
-}
-
-template <int BM, int BN, int BK, bool TB>
-__device__ __forceinline__ void gemm_bf16_tile(float* __restrict__ C, int64_t ldc,
-                                               const uint16_t* __restrict__ A, int64_t lda,
-                                               const uint16_t* __restrict__ B, int64_t ldb, int M,
-                                               int N, int K, int m0, int n0, i32x4* lds) {
-  using T = Bf16StagedCfg<BM, BN, BK>;
-  constexpr int CH = T::CH;
-  constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
-  constexpr int LA = BM * CH / kThreads;                // A chunks per thread
-  constexpr int LB = BN * CH / kThreads;                // B chunks per thread (both layouts)
-  static_assert(LA >= 1 && LB >= 1 && TM >= 1 && TN >= 1, "tile");
-  i32x4* As = lds;
-  i32x4* Bs = lds + 2 * BM * CH;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm0 = (wave >> 1) * WM, wn0 = (wave & 1) * WN;
-  const int il = lane & 31, kh = lane >> 5;
-
-  i32x4 ra[LA], rb[LB];
-  auto fetch = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < LA; q++) {
-      const int c = tid + kThreads * q, r = c / CH, ch = c % CH;
-      const int k = k0 + ch * 8;
-      ra[q] = (m0 + r < M && k < K)
-                  ? *reinterpret_cast<const i32x4*>(A + (int64_t)(m0 + r) * lda + k)
-                  : i32x4{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int q = 0; q < LB; q++) {
-      const int c = tid + kThreads * q;
-      if (TB) {  // B stored N x K
-        const int r = c / CH, ch = c % CH, k = k0 + ch * 8;
-        rb[q] = (n0 + r < N && k < K)
-                    ? *reinterpret_cast<const i32x4*>(B + (int64_t)(n0 + r) * ldb + k)
-                    : i32x4{0, 0, 0, 0};
-      } else {  // B stored K x N: chunk = 8 consecutive n at one k
-        const int k = c / (BN / 8), nc = (c % (BN / 8)) * 8;
-        rb[q] = (k0 + k < K && n0 + nc < N)
-                    ? *reinterpret_cast<const i32x4*>(B + (int64_t)(k0 + k) * ldb + n0 + nc)
-                    : i32x4{0, 0, 0, 0};
-      }
-    }
-  };
-  auto stash = [&](int buf) {
-#pragma unroll
-    for (int q = 0; q < LA; q++) {
-      const int c = tid + kThreads * q;
-      As[buf * BM * CH + swz16<CH>(c / CH, c % CH)] = ra[q];
-    }
-#pragma unroll
-    for (int q = 0; q < LB; q++) {
-      const int c = tid + kThreads * q;
-      if (TB) {
-        Bs[buf * BN * CH + swz16<CH>(c / CH, c % CH)] = rb[q];
-      } else {  // 8 consecutive n of row k, stored as they are
-        const int k = c / (BN / 8), nc = (c % (BN / 8)) * 8;
-        Bs[(buf * BK * T::BPITCH + k * T::BPITCH + nc * 2) / 16] = rb[q];
-      }
-    }
-  };
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; i++)
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
-
-  const int nk = (K + BK - 1) / BK;
-  if (nk > 0) {
-    fetch(0);
-    stash(0);
-    __syncthreads();
-  }
-  for (int kt = 0; kt < nk; kt++) {
-    const int cur = kt & 1;
-    const bool more = kt + 1 < nk;
-    if (more) fetch((kt + 1) * BK);
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ks++) {
-      const int c = 2 * ks + kh;
-      bf16x8 a[TM], b[TN];
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-        a[i] = __builtin_bit_cast(bf16x8, As[cur * BM * CH + swz16<CH>(wm0 + 32 * i + il, c)]);
-      if (TB) {
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-          b[j] = __builtin_bit_cast(bf16x8, Bs[cur * BN * CH + swz16<CH>(wn0 + 32 * j + il, c)]);
-      } else {
-        // lane (il, kh) needs column wn0 + 32 j + il at k = 16 ks + 8 kh .. + 7:
-        // two transposed reads of four rows each (see lds_read_tr16)
-        const int i16 = lane & 15, g16 = (lane >> 4) & 1;
-        const char* bsb = reinterpret_cast<const char*>(Bs) + cur * BK * T::BPITCH;
-        const int row = 16 * ks + 8 * kh + i16 / 4;
-#pragma unroll
-        for (int j = 0; j < TN; j++) {
-          const int col = wn0 + 32 * j + 16 * g16 + 4 * (i16 % 4);
-          const s16x4_t lo = lds_read_tr16(bsb + row * T::BPITCH + col * 2);
-          const s16x4_t hi = lds_read_tr16(bsb + (row + 4) * T::BPITCH + col * 2);
-          b[j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    if (more) stash(cur ^ 1);
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < TM; i++)
-#pragma unroll
-    for (int j = 0; j < TN; j++) {
-      const int col = n0 + wn0 + j * 32 + il;
-      if (col >= N) continue;
-#pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const int row = m0 + wm0 + i * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
-        if (row < M) C[(int64_t)row * ldc + col] = acc[i][j][r];
-      }
-    }
-}
-
-// ===========================================================================
 // Stencil tile, LDS halo schedule: out rows [y0, y0+TY) x columns [x0, x0+256)
 //   pad2D (clamp/zero)     -> index remapping while the halo tile is fetched;
 //   slide2D                -> one (TY + 2R) x (256 + 8) halo tile staged in LDS
