@@ -7,20 +7,9 @@
 // step, ping-ponging between two images in the caller's workspace; the first
 // launch reads the input and the last writes the output.
 //
-// fuse = T > 1 runs T steps per launch (temporal blocking).  A workgroup loads
-// a 128-column region of the image with a halo of T*r rows and columns, with
-// pad2D applied, and keeps the steps in LDS, which is itself a double buffer:
-// step t reads one LDS image and writes the other, on a region that shrinks
-// by r per side and step, until the last step leaves the output tile
-// (128 - 2rT columns by 32 rows), which goes to HBM.  HBM then carries the
-// image once per T steps instead of once per step, at the price of the halo
-// recomputation.
-//
-// Padding inside the fused steps: every LDS image holds, at positions outside
-// the image, what pad2D would read there (the nearest edge value for clamp, 0
-// for zero), so a step is the same unguarded weighted sum everywhere.  After
-// each intermediate step, tiles that reach past the image rewrite those
-// positions from the freshly computed edge (clamp) or with zeros.
+// fuse = T > 1 runs T steps per launch (temporal blocking), in registers: a wave
+// walks down a strip of 128 columns, two to a lane, and every row it loads passes
+// through the T steps at once.  HBM then carries the image once per T steps.
 //
 // Every output is the sum over dy (outer) and dx (inner) of fma(x, w, acc)
 // from 0, the order of the single-step kernels, so fused and unfused
@@ -28,6 +17,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -35,224 +25,233 @@ namespace rise {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kItW = 128;   // LDS region width: 64 lanes x 2 columns
-constexpr int kItTH = 32;   // output rows per tile
 constexpr int kItTMax = 4;  // most steps per launch
 
-template <int K>
+// Strips and segments of the fused kernel: a strip has C columns to a lane, of which
+// HALO on each side are only read, and a segment `rows` output rows; one wave each.
+// (Four columns to a lane halve the share of the halo but also the waves: as fast at
+// 4096^2, 10 to 40 % slower below 1500^2.)
+constexpr int C = 2;
+template <int K, int T>
 struct ItCfg {
   static constexpr int R = (K - 1) / 2;
-  static constexpr int PITCH = kItW + 2 * R;  // R spare columns each side
-  static constexpr int ROWS = kItTH + 2 * R * kItTMax;
-  static constexpr int BUF = ROWS * PITCH;
+  static constexpr int HALO = (R * T + C - 1) / C * C;
+  static constexpr int USE = 64 * C - 2 * HALO;
+  static_assert(C >= R, "windows reach into the neighbouring lanes only");
+  static constexpr int PF = K;  // rows loaded ahead (a multiple of K)
 };
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// Input region of one tile, one thread's share: column tid % 128 of rows
-// tid / 128, tid / 128 + 2, ...  Every load reads a clamped, always valid
-// address (no branches, so the loads stay in flight until the values are
-// written to LDS); bit j of `zero` marks values that zero padding replaces.
-template <int K>
-struct ItRegs {
-  static constexpr int N = ItCfg<K>::ROWS / 2;
-  static_assert(N <= 32, "zero mask bits");
-  float v[N];
-  uint32_t zero;
-};
+typedef float V __attribute__((ext_vector_type(C)));
+typedef float VU __attribute__((ext_vector_type(C), aligned(4)));
 
-template <int K>
-__device__ __forceinline__ void it_fetch(ItRegs<K>& st, const float* __restrict__ in,
-                                         int64_t ld_in, int H, int W, int zero_pad, int gy0,
-                                         int gx0) {
-  const int c = threadIdx.x & (kItW - 1), r0 = threadIdx.x >> 7;
-  const int gx = gx0 + c, gxc = clampi(gx, 0, W - 1);
-  const bool col_in = gx >= 0 && gx < W;
-  uint32_t z = 0;
-#pragma unroll
-  for (int j = 0; j < ItRegs<K>::N; j++) {
-    const int gy = gy0 + r0 + 2 * j;
-    st.v[j] = in[(int64_t)clampi(gy, 0, H - 1) * ld_in + gxc];
-    if (zero_pad && !(col_in && gy >= 0 && gy < H)) z |= 1u << j;
-  }
-  st.zero = z;
+// the value of the lane before (UP) or after, by a DPP move over the whole wave
+template <bool UP>
+__device__ __forceinline__ float neighbour(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v),
+                                                            UP ? 0x138 : 0x130, 0xf, 0xf, true));
 }
 
-template <int K>
-__device__ __forceinline__ void it_stash(const ItRegs<K>& st, float* img, int rows) {
-  constexpr int R = ItCfg<K>::R, P = ItCfg<K>::PITCH;
-  const int c = threadIdx.x & (kItW - 1), r0 = threadIdx.x >> 7;
+// One wave's segment.  Level t holds the image after t steps.  In every tick the next
+// row of level 0 is loaded, and level t = 1 .. T finishes row i - R t: a row that
+// arrives at a level is added to the K output rows of the next level whose windows
+// it is in (dy = 0 opens an accumulator, dy = K - 1 closes one), so each level keeps
+// K accumulators per column and no rows.
+// EX, EY (a strip or a segment that reaches past the image): a level's columns and
+// rows outside the image are what pad2D reads there, the level's own edge (clamp) or
+// zeros.  Outside columns are rewritten in each finished row.  Rows above row 0 are
+// not processed; when row 0 arrives, it is first added for the rows above it.  Past
+// the last row the row before arrives again.
+template <int K, int T, bool EX, bool EY>
+__device__ __forceinline__ void iterate_segment(float* __restrict__ out, int64_t ld_out,
+                                                const float* __restrict__ in, int64_t ld_in, int H,
+                                                int W, const float (&wt)[K][K], int zero_pad,
+                                                int xs, int y0, int y1, int keep_out) {
+  using Cfg = ItCfg<K, T>;
+  constexpr int R = Cfg::R, PF = Cfg::PF, HALO = Cfg::HALO;
+  const int lane = threadIdx.x & 63, x = xs + C * lane;
+  const int first = y0 - R * T, ticks = y1 - y0 + 2 * R * T;
+  auto load = [&](int i) {  // row first + i, inside the image
+    const float* row = in + (int64_t)clampi(first + i, 0, H - 1) * ld_in;
+    if (!EX) return V(*reinterpret_cast<const VU*>(row + x));
+    V v;
 #pragma unroll
-  for (int j = 0; j < ItRegs<K>::N; j++)
-    if (r0 + 2 * j < rows) img[(r0 + 2 * j) * P + R + c] = (st.zero >> j) & 1u ? 0.f : st.v[j];
+    for (int q = 0; q < C; q++) v[q] = row[clampi(x + q, 0, W - 1)];
+    return v;
+  };
+  // columns of a level's row outside the image; the column W - 1 is lane `le`'s
+  // element `ee` (when the strip reaches past it)
+  const int cr = W - 1 - xs, le = cr / C & 63, ee = cr % C;
+  const bool left = xs < 0, right = xs + 64 * C > W;
+  auto pad_columns = [&](V& v) {
+    if (left) {
+      const float e = __builtin_bit_cast(
+          float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v.x), HALO / C));
+#pragma unroll
+      for (int q = 0; q < C; q++) v[q] = x < 0 ? (zero_pad ? 0.f : e) : v[q];
+    }
+    if (right) {
+      float pick = v[0];
+#pragma unroll
+      for (int q = 1; q < C; q++) pick = ee == q ? v[q] : pick;
+      const float e =
+          __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, pick), le));
+#pragma unroll
+      for (int q = 0; q < C; q++) v[q] = x + q >= W ? (zero_pad ? 0.f : e) : v[q];
+    }
+  };
+
+  float acc[T][K][C] = {};  // [level - 1][output row modulo K][column]
+  V last[EY ? T : 1] = {};
+  V ahead[PF];
+#pragma unroll
+  for (int i = 0; i < PF; i++) ahead[i] = load(i);
+
+  auto tick = [&](auto phase, int i) {
+    constexpr int P = decltype(phase)::value;
+    V v = ahead[P];
+    ahead[P] = load(min(i + PF, ticks - 1));
+#pragma unroll
+    for (int t = 0; t < T; t++) {  // v: row y of level t, which makes one of level t + 1
+      const int y = first + i - R * t;
+      if (EY && y < 0) return;  // (the next levels are further up still)
+      if (EX) pad_columns(v);
+      if (EY) {
+        if (y >= H) v = zero_pad ? V(0.f) : last[t];
+        last[t] = v;
+      }
+      float win[C + 2 * R];
+#pragma unroll
+      for (int q = 0; q < R; q++) {
+        win[q] = neighbour<true>(v[C - R + q]);
+        win[C + R + q] = neighbour<false>(v[q]);
+      }
+#pragma unroll
+      for (int q = 0; q < C; q++) win[R + q] = v[q];
+      auto add = [&](float (&a)[C], int dy, bool pad_row) {
+#pragma unroll
+        for (int q = 0; q < C; q++)
+#pragma unroll
+          for (int dx = 0; dx < K; dx++)
+            a[q] = fmaf(pad_row && zero_pad ? 0.f : win[q + dx], wt[dy][dx], a[q]);
+      };
+      if (EY && y == 0) {  // output rows j < R start with the rows above the image
+#pragma unroll
+        for (int j = 0; j < R; j++) {
+          float(&a)[C] = acc[t][(P + K - (R - j)) % K];
+#pragma unroll
+          for (int q = 0; q < C; q++) a[q] = 0.f;
+#pragma unroll
+          for (int dy = 0; dy < R - j; dy++) add(a, dy, true);
+        }
+      }
+#pragma unroll
+      for (int dy = K - 1; dy >= 0; dy--) {
+        float(&a)[C] = acc[t][(P + K - dy) % K];
+        if (dy == 0) {
+#pragma unroll
+          for (int q = 0; q < C; q++) a[q] = 0.f;
+        }
+        add(a, dy, false);
+      }
+#pragma unroll
+      for (int q = 0; q < C; q++) v[q] = acc[t][(P + 1) % K][q];
+    }
+    const int y = first + i - R * T;
+    if (y < y0) return;
+    // (rows y0 .. y1 - 1, columns HALO .. of the strip inside the image)
+    if (lane >= HALO / C && lane < 64 - HALO / C) {
+      float* dst = out + (int64_t)y * ld_out + x;
+      if (!EX || x + C <= W) {
+        if (keep_out)  // the next launch reads it: leave it in the caches
+          *reinterpret_cast<VU*>(dst) = VU(v);
+        else
+          __builtin_nontemporal_store(VU(v), reinterpret_cast<VU*>(dst));
+      } else {
+#pragma unroll
+        for (int q = 0; q < C; q++)
+          if (x + q < W) dst[q] = v[q];
+      }
+    }
+  };
+  auto ticks_from = [&](auto self, auto phase, int i) {
+    constexpr int P = decltype(phase)::value;
+    if constexpr (P < PF) {
+      if (i + P >= ticks) return;
+      tick(phase, i + P);
+      self(self, std::integral_constant<int, P + 1>{}, i);
+    }
+  };
+  for (int i = 0; i < ticks; i += PF) ticks_from(ticks_from, std::integral_constant<int, 0>{}, i);
 }
 
-// A resident grid: the row-major tile raster is cut into 8 contiguous bands,
-// one per XCD (workgroup b runs on XCD b % 8), and workgroup j of an XCD takes
-// tiles j, j + per, ... of its band.  While a workgroup runs the steps of one
-// tile, the input region of its next tile is already on its way into
-// registers.
-template <int K>
+// Bound by the FMAs (T K^2 per column and row of a strip, with HALO columns and 2 R T
+// rows of every strip and segment computed again) where there are several waves to a
+// SIMD, and by a wave's own latency on small images.  It replaced LDS tiles of 32
+// rows by 128 columns, which read 96 bytes of LDS per eight outputs and step: 4096^2,
+// 3 x 3, four steps a launch 18.5 -> 9.9 us per step, 256^2 3.9 -> 1.9; 5 x 5 35.5 ->
+// 24 and 5.0 -> 4.0.
+template <int K, int T>
 __global__ __launch_bounds__(kThreads) void stencil_iter_fused(
     float* __restrict__ out, int64_t ld_out, const float* __restrict__ in, int64_t ld_in, int H,
-    int W, const float* __restrict__ w, int zero_pad, int steps, int tiles_x, int ntiles,
-    int per, int keep_out) {
-  using Cfg = ItCfg<K>;
-  constexpr int R = Cfg::R, P = Cfg::PITCH;
-  __shared__ float lds[2 * Cfg::BUF];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int xcd = blockIdx.x % kNumXcd, jx = blockIdx.x / kNumXcd;
-  const int band_end = (int)((int64_t)ntiles * (xcd + 1) / kNumXcd);
-  int tile = (int)((int64_t)ntiles * xcd / kNumXcd) + jx;
-  if (tile >= band_end) return;  // the whole workgroup leaves before any barrier
-  const int RT = R * steps, TW = kItW - 2 * RT, ROWS = kItTH + 2 * RT;
-
+    int W, const float* __restrict__ w, int zero_pad, int strips, int rows, int segments,
+    int keep_out) {
+  using Cfg = ItCfg<K, T>;
+  const int64_t g =
+      (int64_t)blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (g >= (int64_t)strips * segments) return;
+  const int seg = (int)(g / strips), strip = (int)(g - (int64_t)seg * strips);
+  const int xs = strip * Cfg::USE - Cfg::HALO, y0 = seg * rows, y1 = min(H, y0 + rows);
   float wt[K][K];
 #pragma unroll
   for (int dy = 0; dy < K; dy++)
 #pragma unroll
     for (int dx = 0; dx < K; dx++) wt[dy][dx] = w[dy * K + dx];
-
-  ItRegs<K> st;
-  int y0 = (tile / tiles_x) * kItTH, x0 = (tile % tiles_x) * TW;
-  it_fetch<K>(st, in, ld_in, H, W, zero_pad, y0 - RT, x0 - RT);
-  while (true) {
-    const int gy0 = y0 - RT, gx0 = x0 - RT;  // image position of LDS row 0, column 0
-    __syncthreads();  // every wave is done reading the previous tile's last image
-    // step 0: the input region with pad2D applied (column c at LDS index R + c)
-    it_stash<K>(st, lds, ROWS);
-    const int next = tile + per;
-    const bool more = next < band_end;
-    const int ny0 = (next / tiles_x) * kItTH, nx0 = (next % tiles_x) * TW;
-    if (more) it_fetch<K>(st, in, ld_in, H, W, zero_pad, ny0 - RT, nx0 - RT);
-    const bool border = gy0 < 0 || gy0 + ROWS > H || gx0 < 0 || gx0 + kItW > W;
-
-    int cur = 0;
-    for (int t = 1; t <= steps; t++) {
-      __syncthreads();
-      const float* src = lds + cur * Cfg::BUF;
-      float* dst = lds + (cur ^ 1) * Cfg::BUF;
-      // rows [R t, ROWS - R t) in blocks of 4; the last block is moved up so
-      // that no block leaves the region (overlapping rows are recomputed with
-      // the same result).  Every lane computes columns 2 lane, 2 lane + 1 over
-      // the full width; columns outside the region come out as garbage that
-      // no later step inside the region reads.
-      const int lo = R * t, hi = ROWS - R * t, nb = (hi - lo + 3) >> 2;
-      for (int b = wave; b < nb; b += kThreads / 64) {
-        const int r0 = min(lo + 4 * b, hi - 4);
-        float acc[4][2];
-#pragma unroll
-        for (int o = 0; o < 4; o++) acc[o][0] = acc[o][1] = 0.f;
-#pragma unroll
-        for (int j = 0; j < 4 + 2 * R; j++) {
-          // data columns 2 lane - R .. 2 lane + 1 + R sit at LDS 2 lane .. 2 lane + K
-          const float* row = src + (r0 - R + j) * P + 2 * lane;
-          float v[K + 1];
-#pragma unroll
-          for (int e = 0; e < K + 1; e += 2) {
-            const float2 p2 = *reinterpret_cast<const float2*>(row + e);
-            v[e] = p2.x;
-            v[e + 1] = p2.y;
-          }
-#pragma unroll
-          for (int o = 0; o < 4; o++) {
-            const int dy = j - o;
-            if (dy >= 0 && dy < K) {
-#pragma unroll
-              for (int q = 0; q < 2; q++)
-#pragma unroll
-                for (int dx = 0; dx < K; dx++)
-                  acc[o][q] = fmaf(v[q + dx], wt[dy][dx], acc[o][q]);
-            }
-          }
-        }
-#pragma unroll
-        for (int o = 0; o < 4; o++) {
-          float* d = dst + (r0 + o) * P + R + 2 * lane;
-          d[0] = acc[o][0];
-          d[1] = acc[o][1];
-        }
-      }
-      cur ^= 1;
-      if (t < steps && border) {
-        // restore pad2D's values outside the image inside the new region
-        __syncthreads();
-        float* img = lds + cur * Cfg::BUF;
-        const int n = (hi - lo) * kItW;
-        if (zero_pad) {
-          for (int i = tid; i < n; i += kThreads) {
-            const int r = lo + (i >> 7), c = i & (kItW - 1);
-            const int gy = gy0 + r, gx = gx0 + c;
-            if (c >= lo && c < kItW - lo && (gy < 0 || gy >= H || gx < 0 || gx >= W))
-              img[r * P + R + c] = 0.f;
-          }
-        } else {
-          // columns first (rows inside the image), then whole rows, so corners
-          // take the corner value
-          for (int i = tid; i < n; i += kThreads) {
-            const int r = lo + (i >> 7), c = i & (kItW - 1);
-            const int gy = gy0 + r, gx = gx0 + c;
-            if (c >= lo && c < kItW - lo && gy >= 0 && gy < H && (gx < 0 || gx >= W))
-              img[r * P + R + c] = img[r * P + R + clampi(gx, 0, W - 1) - gx0];
-          }
-          __syncthreads();
-          for (int i = tid; i < n; i += kThreads) {
-            const int r = lo + (i >> 7), c = i & (kItW - 1);
-            const int gy = gy0 + r;
-            if (c >= lo && c < kItW - lo && (gy < 0 || gy >= H))
-              img[r * P + R + c] = img[(clampi(gy, 0, H - 1) - gy0) * P + R + c];
-          }
-        }
-      }
-    }
-    __syncthreads();
-    // the output tile: rows RT .. RT + 32, columns RT .. RT + TW of the last image
-    const float* img = lds + cur * Cfg::BUF;
-    {
-      const int c = tid & (kItW - 1), x = x0 + c;
-      if (c < TW && x < W) {
-#pragma unroll 4
-        for (int r = tid >> 7; r < kItTH; r += 2) {
-          const int y = y0 + r;
-          if (y < H) {
-            const float v = img[(RT + r) * P + R + RT + c];
-            if (keep_out)  // the next launch reads it: leave it in the caches
-              out[(int64_t)y * ld_out + x] = v;
-            else
-              __builtin_nontemporal_store(v, out + (int64_t)y * ld_out + x);
-          }
-        }
-      }
-    }
-    if (!more) break;
-    tile = next;
-    y0 = ny0;
-    x0 = nx0;
-  }
+  constexpr int RT = Cfg::R * T;
+  const bool inside_x = xs >= 0 && xs + 64 * C <= W, inside_y = y0 >= RT && y1 + RT <= H;
+  auto run = [&](auto ex, auto ey) {
+    iterate_segment<K, T, decltype(ex)::value, decltype(ey)::value>(
+        out, ld_out, in, ld_in, H, W, wt, zero_pad, xs, y0, y1, keep_out);
+  };
+  if (!inside_y)
+    run(std::true_type{}, std::true_type{});
+  else if (!inside_x)
+    run(std::true_type{}, std::false_type{});
+  else
+    run(std::false_type{}, std::false_type{});
 }
 
+template <int K, int T>
+rise_status launch_fused_steps(const StencilArgs& a, hipStream_t s) {
+  using Cfg = ItCfg<K, T>;
+  const int64_t strips = ((int64_t)a.W + Cfg::USE - 1) / Cfg::USE;
+  const int64_t simds = 4 * (int64_t)device_cu_count();
+  // rows of a segment: the least time of the SIMD that gets the most waves.  A row of
+  // four 3 x 3 steps takes one wave 0.61 us and two 0.59, six 1.18, eight 1.42; of
+  // 5 x 5 steps one wave 0.7, two 1.1, three 1.4, nine 3.3
+  double least = 0;
+  int rows = 0;
+  for (int r = 2; r <= 256; r += 1 + r / 16) {
+    const int64_t per = (strips * (((int64_t)a.H + r - 1) / r) + simds - 1) / simds;
+    const double cost =
+        (K == 3 ? std::max(3.5, per + 1.2) : per + 1.4) * (r + 2 * Cfg::R * T);
+    if (least == 0 || cost < least) least = cost, rows = r;
+  }
+  const int64_t segments = ((int64_t)a.H + rows - 1) / rows, blocks = (strips * segments + 3) / 4;
+  if (blocks > INT32_MAX) return fail(RISE_ERR_SHAPE, "rise_stencil2d_iterate: too many tiles");
+  hipLaunchKernelGGL((stencil_iter_fused<K, T>), dim3((unsigned)blocks), dim3(kThreads), 0, s,
+                     a.out, a.ld_out, a.in, a.ld_in, a.H, a.W, a.w, (int)(a.pad == RISE_PAD_ZERO),
+                     (int)strips, rows, (int)segments, (int)a.keep_out);
+  return check_launch("stencil_iter_fused");
+}
 template <int K>
 rise_status launch_fused(const StencilArgs& a, int steps, hipStream_t s) {
-  const int TW = kItW - 2 * ItCfg<K>::R * steps;
-  const int tiles_x = (a.W + TW - 1) / TW, tiles_y = (a.H + kItTH - 1) / kItTH;
-  const int64_t ntiles = (int64_t)tiles_x * tiles_y;
-  if (ntiles > INT32_MAX) return fail(RISE_ERR_SHAPE, "rise_stencil2d_iterate: too many tiles");
-  static const int occ = [] {
-    int o = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, stencil_iter_fused<K>, kThreads, 0) !=
-            hipSuccess || o < 1)
-      o = 1;
-    return o;
-  }();
-  // workgroups per XCD: as many as stay resident, evened out over the band
-  const int64_t band = (ntiles + kNumXcd - 1) / kNumXcd;
-  const int64_t max_per = std::max<int64_t>(1, (int64_t)occ * device_cu_count() / kNumXcd);
-  const int64_t rounds = (band + max_per - 1) / max_per;
-  const int per = (int)std::max<int64_t>(1, (band + rounds - 1) / rounds);
-  hipLaunchKernelGGL(stencil_iter_fused<K>, dim3(kNumXcd * per), dim3(kThreads), 0, s, a.out,
-                     a.ld_out, a.in, a.ld_in, a.H, a.W, a.w, (int)(a.pad == RISE_PAD_ZERO), steps,
-                     tiles_x, (int)ntiles, per, (int)a.keep_out);
-  return check_launch("stencil_iter_fused");
+  switch (steps) {
+    case 2: return launch_fused_steps<K, 2>(a, s);
+    case 3: return launch_fused_steps<K, 3>(a, s);
+    default: return launch_fused_steps<K, kItTMax>(a, s);
+  }
 }
 
 int launches(int64_t steps, int fuse) { return (int)((steps + fuse - 1) / fuse); }
@@ -262,10 +261,9 @@ int launches(int64_t steps, int fuse) { return (int)((steps + fuse - 1) / fuse);
 bool stencil_iterate_fusable(int kh, int kw) { return kh == kw && (kh == 3 || kh == 5); }
 int stencil_iterate_max_fuse() { return kItTMax; }
 
-// Measured on MI355X at 4096^2: for 3x3 four fused steps beat one launch per
-// step (19 vs 21 us per step); for 5x5 the fused steps are bound by the FMA
-// rate (k*k FMAs per pixel and step plus the halo recomputation) and lose to
-// one launch per step, which is bound by HBM (36 vs 28 us per step).
+// Measured at 4096^2: for 3x3 four fused steps beat one launch per step (9.9 against
+// 21 us per step); for 5x5, bound by the FMA rate, they are even (24 and 24.5 us),
+// and below 1500^2 the single steps win (1000^2: 5.5 and 4.9 us).
 int stencil_iterate_default_fuse(int kh, int kw) {
   return kh == 3 && kw == 3 ? kItTMax : 1;
 }

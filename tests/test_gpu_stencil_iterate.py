@@ -159,3 +159,20 @@ def test_convenience_wrapper(rise):
     img, w = inputs(64, 64, 3, 7500)
     y = rise.stencil2d_iterate(torch.from_numpy(img).cuda(), torch.from_numpy(w), 3)
     check_oracle(host(y), img, w, 3, "clamp")
+
+
+@pytest.mark.parametrize("k", [3, 5])
+@pytest.mark.parametrize("pad", ["clamp", "zero"])
+@pytest.mark.parametrize("H,W", [(2, 3), (9, 119), (31, 120), (47, 121), (64, 127), (19, 129), (40, 241),
+                                 (300, 113), (1100, 1001)])
+def test_fused_strips_equal_single_steps(rise, k, pad, H, W):
+    # widths around the strips' useful columns (112 to 124 of 128) and images lower than
+    # the halo rows up to many segments, at an odd row length: every fusing gives
+    # the bits of one launch per step
+    img, w = inputs(H, W, k, 7300 + H + W + k)
+    img[H // 2, W // 2] = -0.0
+    w[0, 0] = -w[0, 0]
+    one = run(rise, img, w, 4, pad, 1, ld_in=W + 1, ld_out=W + 3, offset=1)
+    for fuse in (2, 3, 4):
+        got = run(rise, img, w, 4, pad, fuse, ld_in=W + 1, ld_out=W + 3, offset=1)
+        assert np.array_equal(got.view(np.uint32), one.view(np.uint32)), fuse
