@@ -37,7 +37,6 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES / 4) void gemm_f32_kernel(
 //   rows along m or n: a lane reads one value per k, 32 lanes 128 contiguous bytes.
 // Rows past the edge repeat the last one and feed outputs that are not stored;
 // k past the end reads as zero.
-constexpr int kSplitMaxK = 1024;  // longest K the library picks it for
 
 template <bool ALONG_K>
 struct SplitFrag {
@@ -187,15 +186,27 @@ rise_tile gemm_f32_default_tile(int M, int N, int K) {
   // 1.52 against 1.10 ms).
   // 32 x 32 tiles of a short K run gemm_f32_split_kernel, whose waves wait out
   // one memory latency per 32 k but need no ring to fill (128^3: 4.1 against 4.9
-  // us); of a long K the ring (64 x 64 x 4096: 22 against 38 us).
+  // us); of a long K the ring (64 x 64 x 4096: 22 against 38 us).  Where rows are
+  // not whole chunks the ring's copies go value by value and the crossing lies
+  // further out (130 x 333 x 1601 16.7 against 20.2 us, 555 x 85 x 3001 27.4 and
+  // 26.4), and so is the time of the split kernel lower beside them.
+  // Every round also pays for the stages a ring starts with and for the store of
+  // the tile, as K grows short most of its time: counted as three stages and 32 k
+  // (without them 1664 x 903 x 79 took 64 x 32 tiles, 23.9 us, 32 x 32 11.0; over
+  // 250 random shapes up to 3000 x 3000 x 1500 the choice was 8.2 % above the best
+  // tile, now 2.0).
   const bool chunks = M % 4 == 0 && N % 4 == 0 && K % 4 == 0;
+  const int split_max_k = chunks ? 1024 : 2560;
   rise_tile best{64, 64, 32};
   double least = 0;
   for (const auto& c : kTiles) {
     if (c.ns == 0 || (c.t.bm == 256 && !chunks)) continue;
-    if (c.t.bm == 32 && c.t.bn == 32 && (c.t.bk == 128) != (K > kSplitMaxK)) continue;
+    if (c.t.bm == 32 && c.t.bn == 32 && (c.t.bk == 128) != (K > split_max_k)) continue;
+    const bool split = c.t.bm == 32 && c.t.bn == 32 && c.t.bk == 32;
+    const double ns = split && !chunks ? 26.0 : c.ns;
+    const double k = (double)K + 32 + (split ? 0 : 3 * c.t.bk);
     const int64_t tiles = (((int64_t)M + c.t.bm - 1) / c.t.bm) * (((int64_t)N + c.t.bn - 1) / c.t.bn);
-    const double t = (double)((tiles + 255) / 256) * c.t.bm * c.t.bn * c.ns;
+    const double t = (double)((tiles + 255) / 256) * c.t.bm * c.t.bn * ns * k;
     if (least == 0 || t < least) least = t, best = c.t;
   }
   return best;
