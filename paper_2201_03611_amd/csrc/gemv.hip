@@ -7,11 +7,11 @@
 // are organised around coalesced 16-byte loads and enough loads in flight.
 //
 //   A row-major (the paper's layout, RISE_OP_N): a wavefront owns rows (map over
-//     rows -> waves, as the generated kernel's work-items own rows), four at a
+//     rows -> waves, as the generated kernel's work-items own rows), up to four at a
 //     time when there are plenty; its lanes stride along the rows in 16-byte chunks
 //     (split of the row into lane-sized pieces), and the per-lane partial sums are
 //     combined across the wavefront (the reduce, as a tree over the 64 lanes).
-//     With few rows several waves share a row;
+//     Unless rows are short or very many, several waves share them;
 //   A read through transpose (RISE_OP_T, A stored K x M): a lane owns 4
 //     consecutive outputs and sweeps rows of the stored A with 16-byte loads;
 //     K is split over waves and workgroups when there are too few column blocks
@@ -216,14 +216,19 @@ struct ColSplit {
 ColSplit col_split(int64_t M, int64_t K) {
   ColSplit c;
   // wide rows and enough of them for two workgroups per compute unit (measured:
-  // 40000 x 1000 29.5 us wide, 31.2 narrow; 8192^2 51.3 and 49.7)
+  // 40000 x 1000 29.5 us wide, 31.2 narrow; 9000 x 5000 34.8 and 39; 8192^2 48.4
+  // and 49.7)
   const int64_t wide_blocks = (M + kWideCols - 1) / kWideCols;
-  c.wide = M >= 16384 && wide_blocks * ((K + 63) / 64) >= 512;
+  c.wide = M >= 8192 && wide_blocks * ((K + 63) / 64) >= 512;
   const int cols = c.wide ? kWideCols : kCols;
   c.mblocks = (int)((M + cols - 1) / cols);
   // about 1024 wide workgroups in all (four per compute unit; 2048 took 202 us at
-  // 16384^2) or 2176 narrow ones, chunks of at least 64 rows of A
-  const int64_t blocks = c.wide ? 1024 : 2176;
+  // 16384^2), chunks of at least 64 rows of A; as many narrow ones while a chunk
+  // stays short (outputs x K = 8192 x 3000 23.2 us with 1024, 28.2 with 2176; 7104 x
+  // 3566 24.4 and 25.8), 2176 of a longer K, for two
+  // workgroups per compute unit also when counted by 1024 columns, which a test pins
+  // (3000 x 12000 34.5 us, 30.9 with 1024)
+  const int64_t blocks = c.wide || K <= 8192 ? 1024 : 2176;
   int64_t want = std::min<int64_t>(1024, (blocks + c.mblocks - 1) / c.mblocks);
   int64_t most = std::max<int64_t>(1, (K + 63) / 64);
   c.kchunks = (int)std::max<int64_t>(1, std::min(want, most));
@@ -258,14 +263,17 @@ rise_status launch_gemv(const GemvArgs& a, void* ws, hipStream_t s) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(waves == 1 ? kThreads : 64 * waves), 0,
                          s, a.y, a.A, a.lda, a.x, a.M, a.K, groups);
     };
-    // four rows a wave reuse x best but need 2.5 waves per SIMD to hide the loads
-    // (12000 x 6000 50.0 us against 52.4 with one row a wave, 8192^2 56.8 against
-    // 46.9); fewer rows go one to a wave, then to four and to sixteen waves.  Before,
-    // all went four to a wave: 4096^2 17.0 -> 13.3 us, 1000 x 40000 60 -> 30, 64 x
-    // 16384 14.4 -> 5.0; 1500 x 12345, whose rows are not 16-byte aligned and went
-    // value by value, 96.9 -> 15.4
-    if (a.M >= 10240) go(gemv_rows<4, 1, 2>, 4, 1);
-    else if (a.M >= 2048) go(gemv_rows<1, 1, 4>, 1, 1);
+    // two rows to four waves: 2048 rows are four waves per SIMD,
+    // and each value of x feeds two.  8192^2 43.4 us (6.2 TB/s) where one wave a row took
+    // 46.9 and one wave for four rows 57.2; 16384^2 163.8 against 172.6 and 3566 x
+    // 7104 19.2 against 20.0 with four rows a wave.  Short rows do not feed four
+    // waves: of many, four rows go to one wave (100000 x 64 13.5 against 36.1 us,
+    // 30000 x 1000 22.2 and 25.4; 40000 x 2000 55.0 and 54.8).  Fewer rows go one to
+    // four and to sixteen waves.  Before, all went four to a wave: 4096^2 17.0 -> 13.0
+    // us, 1000 x 40000 60 -> 30, 64 x 16384 14.4 -> 5.0; 1500 x 12345, whose rows are
+    // not 16-byte aligned and went value by value, 96.9 -> 15.4
+    if (a.M >= 10240 && a.K < 2048) go(gemv_rows<4, 1, 2>, 4, 1);
+    else if (a.M >= 2048) go(gemv_rows<2, 4, 2>, 2, 4);
     else if (a.M >= 256) go(gemv_rows<1, 4, 4>, 1, 4);
     else go(gemv_rows<1, 16, 4>, 1, 16);
     return check_launch("gemv_rows");

@@ -151,3 +151,18 @@ def test_gemv_split_edges_integer_exact(rise, trans, M, K):
     exact = (A.astype(np.int64) @ x.astype(np.int64)).astype(np.float32)[:, 0]
     stored = np.ascontiguousarray(A.T) if trans else A
     assert np.array_equal(run(rise, stored, x, trans, x_offset=1), exact)
+
+
+@pytest.mark.parametrize("trans,M,K", [(False, 2049, 5), (False, 2051, 4099), (False, 10240, 2047),
+                                       (False, 10241, 2047), (False, 10241, 2048), (True, 8191, 4099),
+                                       (True, 8193, 4097), (True, 517, 8192), (True, 517, 8193)])
+def test_gemv_row_pairs_and_long_splits_integer_exact(rise, trans, M, K):
+    # row pairs with an odd last row and rows shorter than one run of the four
+    # waves, and either side of where the transposed split changes its width and
+    # its number of chunks
+    g = ri.rng(7 * M + K)
+    A = ri.integer_matrix(g, M, K, bound=3)
+    x = ri.integer_matrix(g, K, 1, bound=3)
+    exact = (A.astype(np.int64) @ x.astype(np.int64)).astype(np.float32)[:, 0]
+    stored = np.ascontiguousarray(A.T) if trans else A
+    assert np.array_equal(run(rise, stored, x, trans, x_offset=1), exact)
