@@ -181,32 +181,36 @@ rise_tile gemm_f32_default_tile(int M, int N, int K) {
   // shapes differ in is mainly how evenly they cover 256 CUs (1000 x 1531: 384
   // tiles of 64 x 64, two on half of the CUs, 36 us; 256 of 64 x 96, one each, 31
   // us; 512 x 512 x 512: 64 of 64 x 64, 14 us, 256 of 32 x 32, 8 us).  256 x 128
-  // only where rows are whole 16-byte chunks whichever way they are stored:
-  // copied value by value it measured slower than 64 x 64 (4095 x 4097 x 4096:
-  // 1.52 against 1.10 ms).
+  // of a long K only where rows are whole 16-byte chunks whichever way they are
+  // stored: copied value by value it measured slower than 64 x 64 (4095 x 4097 x 4096:
+  // 1.52 against 1.10 ms; 5001 x 5003 x 101 114 against 125 us, x 301 207 and 198).
   // 32 x 32 tiles of a short K run gemm_f32_split_kernel, whose waves wait out
   // one memory latency per 32 k but need no ring to fill (128^3: 4.1 against 4.9
   // us); of a long K the ring (64 x 64 x 4096: 22 against 38 us).  Where rows are
   // not whole chunks the ring's copies go value by value and the crossing lies
   // further out (130 x 333 x 1601 16.7 against 20.2 us, 555 x 85 x 3001 27.4 and
   // 26.4), and so is the time of the split kernel lower beside them.
+  // That holds while the split kernel's tiles are few; many of them read each row
+  // of A and B too often (5755 x 6140 x 112: 216 us, 256 x 128 70).
   // Every round also pays for the stages a ring starts with and for the store of
-  // the tile, as K grows short most of its time: counted as three stages and 32 k
-  // (without them 1664 x 903 x 79 took 64 x 32 tiles, 23.9 us, 32 x 32 11.0; over
-  // 250 random shapes up to 3000 x 3000 x 1500 the choice was 8.2 % above the best
-  // tile, now 2.0).
+  // the tile, as K grows short most of its time: counted as four stages and 128 k,
+  // and a last round that is not full runs somewhat faster than a full one (without
+  // these 1664 x 903 x 79 took 64 x 32 tiles, 23.9 us, 32 x 32 11.0; over 900 random
+  // shapes up to 7000 x 7000 x 3000 the choice was 9.3 % above the best tile of
+  // each, 1.7 with them).
   const bool chunks = M % 4 == 0 && N % 4 == 0 && K % 4 == 0;
   const int split_max_k = chunks ? 1024 : 2560;
   rise_tile best{64, 64, 32};
   double least = 0;
   for (const auto& c : kTiles) {
-    if (c.ns == 0 || (c.t.bm == 256 && !chunks)) continue;
+    if (c.ns == 0 || (c.t.bm == 256 && !chunks && K > 512)) continue;
     if (c.t.bm == 32 && c.t.bn == 32 && (c.t.bk == 128) != (K > split_max_k)) continue;
     const bool split = c.t.bm == 32 && c.t.bn == 32 && c.t.bk == 32;
-    const double ns = split && !chunks ? 26.0 : c.ns;
-    const double k = (double)K + 32 + (split ? 0 : 3 * c.t.bk);
     const int64_t tiles = (((int64_t)M + c.t.bm - 1) / c.t.bm) * (((int64_t)N + c.t.bn - 1) / c.t.bn);
-    const double t = (double)((tiles + 255) / 256) * c.t.bm * c.t.bn * ns * k;
+    const double ns = split && !chunks && tiles <= 2048 ? 26.0 : c.ns;
+    const double k = (double)K + 128 + (split ? 0 : 4 * c.t.bk);
+    const double rounds = 0.85 * (double)((tiles + 255) / 256) + 0.15 * (double)tiles / 256;
+    const double t = rounds * c.t.bm * c.t.bn * ns * k;
     if (least == 0 || t < least) least = t, best = c.t;
   }
   return best;
