@@ -668,35 +668,35 @@ rise_status launch_ring_parts(const PackedGemm& g, hipStream_t s) {
   return check_launch("gemm_bf16_kernel");
 }
 
-// The tiles; for BF16, nanoseconds per 64 x 64 outputs and k that one CU takes
-// on them (measured: 256 x 256 at 8192^3, 256 x 128 and 128 x 128 at 2048 x 4096 x
-// 4096, the smaller ones at 1024^3 and 512 x 2048 x 4096; the matrix cores alone
-// need 0.84 at 2.4 GHz), 0: only where asked for.  The split modes run the same tiles
-// a product of parts after the other, so their rows are BF16's; their K-blocked 256 x
-// 256 x 16 kernels count against these (4096^3: bf16x3 362 us against 385 in 256 x
-// 128, bf16x6 620 against 704; 2048 x 4096 x 4096, with half the CUs idle, 281
-// against 204 and 494 against 375).
+// The tiles; nanoseconds per 64 x 64 outputs and k that one CU takes on them (the
+// matrix cores alone need 0.84 at 2.4 GHz), 0: only where asked for.  The split
+// modes run the same tiles a product of parts after the other, so their rows are
+// BF16's; their K-blocked 256 x 256 x 16 kernels count against these (4096^3: bf16x3
+// 362 us against 385 in 256 x 128, bf16x6 620 against 704; 2048 x 4096 x 4096, with
+// half the CUs idle, 281 against 204 and 494 against 375).  The figures are those
+// with which gemm_lowp_default_tile chose best over some 5000 random shapes from 100
+// to 7000 (K from 48 to 5000) of which every tile was timed.
 struct TileRow {
   rise_mode mode;
   rise_tile t;
   double ns = 0;
 };
 const TileRow kTiles[] = {
-    {RISE_MODE_BF16, {256, 256, 64}},       {RISE_MODE_BF16, {128, 128, 64}, 1.9},
-    {RISE_MODE_BF16, {256, 256, 32}, 1.65}, {RISE_MODE_BF16, {256, 128, 64}, 1.68},
-    {RISE_MODE_BF16, {128, 256, 64}, 1.68}, {RISE_MODE_BF16, {128, 64, 64}, 2.5},
-    {RISE_MODE_BF16, {64, 64, 64}, 4.2},    {RISE_MODE_BF16, {64, 64, 128}, 3.2},
-    {RISE_MODE_BF16, {64, 32, 128}, 4.6},
+    {RISE_MODE_BF16, {256, 256, 64}},       {RISE_MODE_BF16, {128, 128, 64}, 2.0},
+    {RISE_MODE_BF16, {256, 256, 32}, 1.52}, {RISE_MODE_BF16, {256, 128, 64}, 1.66},
+    {RISE_MODE_BF16, {128, 256, 64}, 1.68}, {RISE_MODE_BF16, {128, 64, 64}, 2.8},
+    {RISE_MODE_BF16, {64, 64, 64}, 3.65},    {RISE_MODE_BF16, {64, 64, 128}, 3.6},
+    {RISE_MODE_BF16, {64, 32, 128}, 4.7},
     {RISE_MODE_BF16X3, {256, 256, 16}, 1.58}, {RISE_MODE_BF16X3, {256, 256, 32}},
-    {RISE_MODE_BF16X3, {128, 128, 32}},       {RISE_MODE_BF16X3, {256, 128, 64}, 1.68},
-    {RISE_MODE_BF16X3, {128, 256, 64}, 1.68}, {RISE_MODE_BF16X3, {128, 128, 64}, 1.9},
-    {RISE_MODE_BF16X3, {128, 64, 64}, 2.5},   {RISE_MODE_BF16X3, {64, 64, 64}, 4.2},
-    {RISE_MODE_BF16X3, {64, 64, 128}, 3.2},   {RISE_MODE_BF16X3, {64, 32, 128}, 4.6},
-    {RISE_MODE_BF16X6, {256, 256, 16}, 1.48}, {RISE_MODE_BF16X6, {128, 128, 16}},
-    {RISE_MODE_BF16X6, {256, 128, 64}, 1.68}, {RISE_MODE_BF16X6, {128, 256, 64}, 1.68},
-    {RISE_MODE_BF16X6, {128, 128, 64}, 1.9},  {RISE_MODE_BF16X6, {128, 64, 64}, 2.5},
-    {RISE_MODE_BF16X6, {64, 64, 64}, 4.2},    {RISE_MODE_BF16X6, {64, 64, 128}, 3.2},
-    {RISE_MODE_BF16X6, {64, 32, 128}, 4.6},
+    {RISE_MODE_BF16X3, {128, 128, 32}},       {RISE_MODE_BF16X3, {256, 128, 64}, 1.66},
+    {RISE_MODE_BF16X3, {128, 256, 64}, 1.68}, {RISE_MODE_BF16X3, {128, 128, 64}, 2.0},
+    {RISE_MODE_BF16X3, {128, 64, 64}, 2.8},   {RISE_MODE_BF16X3, {64, 64, 64}, 3.65},
+    {RISE_MODE_BF16X3, {64, 64, 128}, 3.6},   {RISE_MODE_BF16X3, {64, 32, 128}, 4.7},
+    {RISE_MODE_BF16X6, {256, 256, 16}, 1.43}, {RISE_MODE_BF16X6, {128, 128, 16}},
+    {RISE_MODE_BF16X6, {256, 128, 64}, 1.66}, {RISE_MODE_BF16X6, {128, 256, 64}, 1.68},
+    {RISE_MODE_BF16X6, {128, 128, 64}, 2.0},  {RISE_MODE_BF16X6, {128, 64, 64}, 2.8},
+    {RISE_MODE_BF16X6, {64, 64, 64}, 3.65},    {RISE_MODE_BF16X6, {64, 64, 128}, 3.6},
+    {RISE_MODE_BF16X6, {64, 32, 128}, 4.7},
     {RISE_MODE_FP8, {256, 256, 128}},       {RISE_MODE_FP8, {128, 128, 128}},
 };
 // k of all products from which 64 x 64 x 128 beats 64 x 64 x 64 (4096: 17.5 against 21 us)
@@ -753,8 +753,14 @@ bool gemm_lowp_tile_supported(rise_mode mode, const rise_tile& t) {
 
 rise_tile gemm_lowp_default_tile(rise_mode mode, int M, int N, int K) {
   if (mode != RISE_MODE_FP8) {
-    // the shortest time for the CU that gets the most tiles (as for FP32: what the
-    // shapes differ in is mainly how evenly they cover 256 CUs)
+    // The shortest time, which is mainly that of the CU that gets the most tiles:
+    // what the shapes differ in is how evenly they cover 256 CUs.  A last round that
+    // is far from full still runs faster than a full one (more power and bandwidth
+    // for each CU), so the rounds count 0.7 whole and 0.3 as the mean over the CUs;
+    // and each fills its ring first, two stages.  Against the best tile of each of the
+    // random shapes the choice is 1.6 % (bf16), 0.7 (bf16x3) and 0.4 (bf16x6) slower;
+    // by whole rounds alone 2.2, 1.0 and 0.9, and up to twice as slow just past a full
+    // round.
     const int64_t k = (int64_t)K * (mode == RISE_MODE_BF16 ? 1 : mode == RISE_MODE_BF16X3 ? 3 : 6);
     rise_tile best{128, 128, 64};
     double least = 0;
@@ -763,7 +769,8 @@ rise_tile gemm_lowp_default_tile(rise_mode mode, int M, int N, int K) {
       if (r.t.bm == 64 && r.t.bn == 64 && (r.t.bk == 128) != (k > kLongK)) continue;
       const int64_t tiles =
           (((int64_t)M + r.t.bm - 1) / r.t.bm) * (((int64_t)N + r.t.bn - 1) / r.t.bn);
-      const double t = (double)((tiles + 255) / 256) * r.t.bm * r.t.bn * r.ns;
+      const double rounds = 0.7 * (double)((tiles + 255) / 256) + 0.3 * (double)tiles / 256;
+      const double t = rounds * r.t.bm * r.t.bn * r.ns * (double)(k + 2 * r.t.bk);
       if (least == 0 || t < least) least = t, best = r.t;
     }
     return best;
