@@ -215,11 +215,12 @@ struct ColSplit {
 };
 ColSplit col_split(int64_t M, int64_t K) {
   ColSplit c;
-  // wide rows and enough of them for two workgroups per compute unit (measured:
-  // 40000 x 1000 29.5 us wide, 31.2 narrow; 9000 x 5000 34.8 and 39; 8192^2 48.4
-  // and 49.7)
+  // wide rows and enough of them for a good two workgroups per compute unit
+  // (measured, outputs x K, wide and narrow: 6000^2 31.5 and 33.5 us, 7112 x 6144 36.4
+  // and 40.0, 5000 x 8000 34.9 and 36.6; below either line 10848 x 3184 32.1 and 30.0,
+  // 4416 x 5888 27.4 and 25.3, 2176 x 12720 27.1 and 24.3)
   const int64_t wide_blocks = (M + kWideCols - 1) / kWideCols;
-  c.wide = M >= 8192 && wide_blocks * ((K + 63) / 64) >= 512;
+  c.wide = M >= 4096 && wide_blocks * ((K + 63) / 64) >= 560;
   const int cols = c.wide ? kWideCols : kCols;
   c.mblocks = (int)((M + cols - 1) / cols);
   // about 1024 wide workgroups in all (four per compute unit; 2048 took 202 us at
