@@ -156,9 +156,7 @@ def main():
     sten_gbs = bytes_sten / (t_sten * 1e-3) / 1e9
     value = (flops_gemm + flops_sten) / (ms_step * 1e-3) / 1e12
 
-    # the 256 x 128 x 16 tile runs the asynchronous-ring kernel for these operands
-    # (contiguous, 16-byte aligned rows, K a multiple of 16); other tiles run the
-    # register-staged one
+    # every tile but 32 x 32 x 32 runs the asynchronous-ring kernel
     gt = rise.rise_gemm_default_tile(M, N, K, "f32")
     gemm_kernel = "gemm_f32_kernel"
     gemm_traffic = traffic_for(gemm_kernel, ["paper_2201_03611_amd/csrc/gemm_f32.hip",
@@ -200,9 +198,8 @@ def main():
                              "ms": round(t_sten, 5)},
     }
 
-    result["strategy"] = {"gemm": f"f32 tile {gt[0]}x{gt[1]}x{gt[2]}" + (
-                              ", slabs through a 3-slab asynchronous LDS ring"
-                              if gemm_kernel == "gemm_f32_async_kernel" else ""),
+    result["strategy"] = {"gemm": f"f32 tile {gt[0]}x{gt[1]}x{gt[2]}, slabs through a "
+                                  "3-slab asynchronous LDS ring",
                           "stencil": f"{sv} halo tile, {srows} output rows x 256 columns"}
 
     # measured ceilings of this GPU beside the spec peaks
@@ -514,7 +511,7 @@ def gemv_leg(rise, torch, dev, stream):
 def stencil_iterate_leg(rise, ri, torch, dev, stream):
     """16 steps of the 4096^2 5x5 Gaussian clamp stencil (iterate, Sec. VI): one
     launch per step through the double buffer of two images, and 4 steps per
-    launch in the LDS double buffer.  Pixel-steps per second; the fused schedule
+    launch in registers.  Pixel-steps per second; the fused schedule
     against the FP32 vector peak (k*k FMAs per pixel-step).  The per-step
     schedule's working set (input, two 64 MiB intermediates, output) fits the
     256 MB last-level cache, which serves most of its reads: its bytes per
