@@ -15,14 +15,19 @@ namespace {
 
 using tiles::kThreads;
 
-template <typename T, bool TA, bool TB, bool VEC>
+// How slabs reach LDS: 16-byte copies (rows of whole aligned chunks), through
+// registers, or 4-byte copies.
+enum Fill { CHUNKS, STAGED, VALUES };
+
+template <typename T, bool TA, bool TB, Fill FILL>
 __global__ __launch_bounds__(T::THREADS, T::WAVES / 4) void gemm_f32_kernel(
     float* __restrict__ C, int64_t ldc, const float* __restrict__ A, int64_t lda,
     const float* __restrict__ B, int64_t ldb, int M, int N, int K, int tiles_m, int tiles_n) {
   __shared__ f32x4 lds[T::LDS_CHUNKS];
   int tm, tn;
   grouped_tile(xcd_contiguous(blockIdx.x, gridDim.x), tiles_m, tiles_n, 8, tm, tn);
-  tiles::gemm_ring_tile<T, TA, TB, VEC>(C, ldc, A, lda, B, ldb, M, N, K, tm * T::BM, tn * T::BN, lds);
+  tiles::gemm_ring_tile<T, TA, TB, FILL != VALUES, false, 1, FILL == STAGED>(
+      C, ldc, A, lda, B, ldb, M, N, K, tm * T::BM, tn * T::BN, lds);
 }
 
 // Few output tiles: a workgroup of NW waves owns a 32 x 32 tile, and wave w sums
@@ -121,18 +126,34 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_split_kernel(
   }
 }
 
-template <typename T, bool VEC>
-rise_status launch_tile(const GemmF32Args& a, hipStream_t s) {
+template <typename T, Fill FILL>
+rise_status launch_fill(const GemmF32Args& a, hipStream_t s) {
   const int tiles_m = (a.M + T::BM - 1) / T::BM, tiles_n = (a.N + T::BN - 1) / T::BN;
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n), dim3(T::THREADS), 0, s, a.C, a.ldc, a.A,
                        a.lda, a.B, a.ldb, a.M, a.N, a.K, tiles_m, tiles_n);
   };
-  if (!a.ta && !a.tb) go(gemm_f32_kernel<T, false, false, VEC>);
-  else if (!a.ta) go(gemm_f32_kernel<T, false, true, VEC>);
-  else if (!a.tb) go(gemm_f32_kernel<T, true, false, VEC>);
-  else go(gemm_f32_kernel<T, true, true, VEC>);
+  if (!a.ta && !a.tb) go(gemm_f32_kernel<T, false, false, FILL>);
+  else if (!a.ta) go(gemm_f32_kernel<T, false, true, FILL>);
+  else if (!a.tb) go(gemm_f32_kernel<T, true, false, FILL>);
+  else go(gemm_f32_kernel<T, true, true, FILL>);
   return check_launch("gemm_f32_kernel");
+}
+
+// Rows that are not whole aligned chunks go through registers while K is short: a
+// ring fills with a quarter of the instructions, and its first three slabs in one
+// memory latency (64 x 64 tiles, by values and staged: 1664 x 903 x 79 14.2 and 11.8 us, 5001 x
+// 5003 x 101 125 and 100, x 301 198 and 190).  Over a longer K copies that need no
+// registers run further ahead (1000 x 1531 x 777 32.2 and 35.5 us, 3001^3 479 and
+// 516), and 256 x 128 tiles gain nothing.
+constexpr int kStagedMaxK = 320;
+
+template <typename T>
+rise_status launch_tile(const GemmF32Args& a, bool vec, hipStream_t s) {
+  if (vec) return launch_fill<T, CHUNKS>(a, s);
+  if constexpr (T::BM * T::BN < 128 * 128)
+    if (a.K <= kStagedMaxK) return launch_fill<T, STAGED>(a, s);
+  return launch_fill<T, VALUES>(a, s);
 }
 
 template <int NW>
@@ -221,7 +242,7 @@ rise_status launch_gemm_f32(const GemmF32Args& a, const rise_tile& t, hipStream_
 #define RISE_F32_TILE(BM, BN, BK, ...)                                         \
   if (t.bm == BM && t.bn == BN && t.bk == BK) {                                \
     using T = tiles::F32Cfg<BM, BN, BK, __VA_ARGS__>;                          \
-    return vec ? launch_tile<T, true>(a, s) : launch_tile<T, false>(a, s);     \
+    return launch_tile<T>(a, vec, s);                                          \
   }
   RISE_F32_TILE(256, 128, 16, 3, 2, 2, 1)
   RISE_F32_TILE(128, 128, 32, 3, 2, 2, 2)

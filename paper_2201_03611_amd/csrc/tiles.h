@@ -70,6 +70,8 @@ __device__ __forceinline__ s16x4_t lds_read_tr16(const void* p) {
 // fetches.  VEC copies move 16 bytes per lane and need 16-byte aligned rows of
 // whole chunks; otherwise each lane copies one value (4 bytes, any alignment)
 // to the same place: four times the copies and the same MFMAs and LDS reads.
+// FP32 slabs can also pass through registers (STAGED): unaligned 16-byte loads and
+// LDS writes to the same place, faster while K is a few slabs.
 // Register staging through guarded value-by-value loads, which such storage took
 // before, ran 1000 x 1531 x 777 in 58 us and 3001^3 in 1188 us, where an aligned
 // neighbour took 45 and 839.
@@ -134,6 +136,48 @@ struct AsyncSlab {
     k = ch / CPM;
     const int col = PC * ((ch % CPM) ^ key_mn(k)) + e;
     return k * ld + min(col, mn_total - mn0 - (VEC ? PC : 1));
+  }
+  // Staged through registers: the chunk of lane `lane` in wave copy i (its row or
+  // column in the tile and its first k), and where it is loaded from, any 4-byte
+  // alignment.  base_mn is the row or column that the slab's pointer stands at.  A
+  // chunk that would pass the end of a row along m or n is loaded `shift` values
+  // further left.
+  __device__ static void place(int i, int lane, int& mn, int& k) {
+    const int ch = i * 64 + lane;
+    if (ALONG_K) {
+      mn = ch / CPR;
+      k = PC * ((ch % CPR) ^ key(mn));
+    } else {
+      k = ch / CPM;
+      mn = PC * ((ch % CPM) ^ key_mn(k));
+    }
+  }
+  __device__ static int base_mn(int mn0, int mn_total) {
+    return ALONG_K ? mn0 : min(mn0, max(mn_total - PC, 0));
+  }
+  __device__ static int64_t staged_index(int64_t ld, int mn0, int mn_total, int i, int lane, int& shift) {
+    int mn, k;
+    place(i, lane, mn, k);
+    shift = 0;
+    if (ALONG_K) return min(mn, mn_total - 1 - mn0) * ld + k;
+    const int col = min(mn0 + mn, mn_total - PC);
+    shift = min(mn0 + mn - col, PC - 1);
+    return k * ld + (col - base_mn(mn0, mn_total));
+  }
+  // the same chunk value by value, zeros from k = kend on
+  __device__ static f32x4 staged_values(const float* base, int64_t ld, int mn0, int mn_total, int kend,
+                                        int i, int lane) {
+    int mn, k;
+    place(i, lane, mn, k);
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int ke = ALONG_K ? k + e : k;
+      const int64_t at = ALONG_K ? min(mn, mn_total - 1 - mn0) * ld + ke
+                                 : k * ld + (min(mn0 + mn + e, mn_total - 1) - base_mn(mn0, mn_total));
+      v[e] = ke < kend ? base[at] : 0.f;
+    }
+    return v;
   }
   __device__ static void copy(const Value* base, uint32_t off, uint32_t to) {
     if (VEC)
@@ -221,8 +265,11 @@ __host__ __device__ inline bool whole_chunks(const V* A, int64_t lda, const V* B
 // PARTS > 1: the operands are prepared as that many planes (plane_a and plane_b values
 // apart, K whole slabs) whose sum they are, and C is the sum of the products of parts
 // i, j with i + j < PARTS, each over all k, small products first.
+// STAGED (FP32, VEC's layout): rows of any alignment and length.  Slabs pass through
+// registers instead, a 16-byte load and an LDS write per chunk: what is loaded
+// during one slab is written during the next, a ring's length before it is read.
 template <typename T, bool TA, bool TB, bool VEC, bool KBLOCKED = false, int PARTS = 1,
-          typename V = typename T::Elem::Value>
+          bool STAGED = false, typename V = typename T::Elem::Value>
 __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ldc,
                                                const V* __restrict__ A, int64_t lda,
                                                const V* __restrict__ B, int64_t ldb, int M, int N,
@@ -262,20 +309,30 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
     return is_a(j) ? SA::index(lda, m0, M, number(j), ln, k)
                    : SB::index(ldb, n0, N, number(j) - SA::COPIES, ln, k);
   };
-  uint32_t off[NCP];
+  static_assert(!STAGED || (E::PER_CHUNK == 4 && VEC && !KBLOCKED && PARTS == 1 && NCP <= 16),
+                "staged slabs are FP32 operands as stored");
+  uint32_t off[NCP], shifts = 0;  // (STAGED) two bits a chunk
 #pragma unroll
   for (int j = 0; j < NCP; j++) {
     int k;
-    off[j] = (uint32_t)sizeof(V) * (uint32_t)index(j, lane, k);
+    if constexpr (STAGED) {
+      const int64_t at = is_a(j) ? SA::staged_index(lda, m0, M, number(j), lane, k)
+                                 : SB::staged_index(ldb, n0, N, number(j) - SA::COPIES, lane, k);
+      off[j] = 4 * (uint32_t)at;
+      shifts |= (uint32_t)k << 2 * j;
+    } else {
+      off[j] = (uint32_t)sizeof(V) * (uint32_t)index(j, lane, k);
+    }
   }
   constexpr int PRODUCTS = PARTS * (PARTS + 1) / 2;
   static_assert(PARTS == 1 || (!TA && TB && VEC && !KBLOCKED && PARTS <= 3), "prepared planes");
   const int nk1 = (K + BK - 1) / BK, krem = K - (nk1 - 1) * BK, nk = PRODUCTS * nk1;
-  const bool wide = lda >= kF32OffsetLd || ldb >= kF32OffsetLd;
+  const bool wide = lda >= kF32OffsetLd || ldb >= kF32OffsetLd ||
+                    (STAGED && ((TA && M < 4) || (!TB && N < 4)));
   // the next slab to copy (its first value in the tile's first row or column);
   // past the last slab the last one is copied again, into a stage nothing reads
-  const V* pa = async::uniform(A + (TA ? m0 : (int64_t)m0 * lda));
-  const V* pb = async::uniform(B + (TB ? (int64_t)n0 * ldb : n0));
+  const V* pa = async::uniform(A + (!TA ? (int64_t)m0 * lda : STAGED ? SA::base_mn(m0, M) : m0));
+  const V* pb = async::uniform(B + (TB ? (int64_t)n0 * ldb : STAGED ? SB::base_mn(n0, N) : n0));
   constexpr uint32_t STAGE_BYTES = SL * 16;
   const uint32_t lds0 = async::lds_address(lds_base);
   // parts of product q (as in the packed kernels), two bits each
@@ -304,6 +361,32 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
     } else {
       SB::copy(pb, off[j], to);
     }
+  };
+  // (STAGED) chunk j of the slab in flight, its load from slab `next` and its write
+  // to the stage at `put`
+  f32x4 held[STAGED ? NCP : 1];
+  const bool shifted = STAGED && ((TA && m0 + BM > M) || (!TB && n0 + BN > N));
+  auto load = [&](int j, auto careful) -> f32x4 {
+    if (decltype(careful)::value && (wide || (next >= nk - 1 && krem < BK))) {
+      const int kend = next >= nk - 1 ? krem : BK;
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      return is_a(j) ? SA::staged_values((const float*)pa, lda, m0, M, kend, number(j), ln)
+                     : SB::staged_values((const float*)pb, ldb, n0, N, kend, number(j) - SA::COPIES, ln);
+    }
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    const char* from = is_a(j) ? (const char*)pa : (const char*)pb;
+    return f32x4(*reinterpret_cast<const f32x4u*>(from + off[j]));
+  };
+  // careful: the slab may hold values put in place one by one
+  auto store = [&](int j, f32x4 v, uint32_t at, bool by_value) {
+    if (shifted && !by_value) {  // a shifted chunk's values move to their columns
+      const uint32_t sh = shifts >> 2 * j;
+      if (sh & 1) v = f32x4{v.y, v.z, v.w, v.w};
+      if (sh & 2) v = f32x4{v.z, v.w, v.w, v.w};
+    }
+    char* to = reinterpret_cast<char*>(lds_base) + at;
+    reinterpret_cast<f32x4*>(to)[number(j) * 64 + lane] = v;
   };
   auto advance = [&] {
     if (PARTS > 1 && --left == 0 && product > 0) {
@@ -353,7 +436,34 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
     }
   };
   constexpr int NR = TM + TN;
-  if (nk > 0) {
+  bool held_by_value = false;  // how the slab in flight was loaded
+  auto by_value = [&] { return wide || (next >= nk - 1 && krem < BK); };
+  if constexpr (STAGED) {
+    if (nk > 0) {
+      f32x4 first[STAGES - 1][NCP];
+      bool values[STAGES - 1];
+#pragma unroll
+      for (int st = 0; st < STAGES - 1; st++) {
+        values[st] = by_value();
+#pragma unroll
+        for (int j = 0; j < NCP; j++) first[st][j] = load(j, std::true_type{});
+        advance();
+      }
+#pragma unroll
+      for (int st = 0; st < STAGES - 1; st++)
+#pragma unroll
+        for (int j = 0; j < NCP; j++) store(j, first[st][j], st * STAGE_BYTES, values[st]);
+      held_by_value = by_value();
+#pragma unroll
+      for (int j = 0; j < NCP; j++) held[j] = load(j, std::true_type{});
+      advance();
+      put = (STAGES - 1) * STAGE_BYTES;
+      async::wait_lgkmcnt0();
+      async::barrier();
+#pragma unroll
+      for (int r = 0; r < NR; r++) read(0, 0, r);
+    }
+  } else if (nk > 0) {
 #pragma unroll
     for (int st = 0; st < STAGES - 1; st++) {
 #pragma unroll
@@ -380,15 +490,18 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
           acc[i][j] = E::mfma(a[st & 1][i], b[st & 1][j], acc[i][j], s);
           __builtin_amdgcn_sched_barrier(0);
           if (last && m == 0) {
-            async::wait_vmcnt<(STAGES - 2) * NCP>();  // this wave's copies of slab kt + 1 landed
-            async::wait_lgkmcnt0();                   // and it has read all of slab kt
+            if (!STAGED) async::wait_vmcnt<(STAGES - 2) * NCP>();  // copies of slab kt + 1 landed
+            async::wait_lgkmcnt0();  // and this wave has read all of slab kt (STAGED: written kt + 2)
             async::barrier();
           }
 #pragma unroll
           for (int o = OPS * m / NM; o < OPS * (m + 1) / NM; o++) {
             if (o < NR)
               read(last ? after : buf, last ? 0 : st + 1, o);
-            else
+            else if constexpr (STAGED) {
+              store(c0 + o - NR, held[c0 + o - NR], put, held_by_value);
+              held[c0 + o - NR] = load(c0 + o - NR, careful);
+            } else
               copy(c0 + o - NR, careful);
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -397,12 +510,13 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
       }
     };
     steps(steps, std::integral_constant<int, 0>{});
+    if (STAGED) held_by_value = by_value();
     advance();
     buf = after;
   };
   int kt = 0;
   if (!wide)
-    for (; kt < nk - STAGES; kt++) slab(std::false_type{});
+    for (; kt < nk - STAGES - STAGED; kt++) slab(std::false_type{});
   for (; kt < nk; kt++) slab(std::true_type{});
   async::wait_vmcnt<0>();  // the copies past the last slab land before the exit
 

@@ -401,3 +401,35 @@ def test_split_parts_integer_exact(rise, mode, bits, M, N, K, wide_b):
     for tile in rise.rise_gemm_tiles(mode):
         C = run(rise, A, B, mode=mode, tile=tile)
         assert np.array_equal(C, exact.astype(np.float32)), tile
+
+
+@pytest.mark.parametrize("ops", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("M,N,K", [(3, 2, 5), (5, 7, 64), (67, 99, 96), (131, 70, 97), (66, 130, 320),
+                                   (66, 130, 321), (257, 33, 31)])
+def test_f32_short_k_any_alignment_integer_exact(rise, ops, M, N, K):
+    # rows of odd length and offset, so no 16-byte chunk is aligned: fewer slabs than
+    # the ring, whole and ragged last slabs, edge tiles with one to three columns of a
+    # chunk left, fewer columns than a chunk, and either side of the longest K staged
+    # through registers; what lies around the operands is NaN
+    import torch
+
+    g = ri.rng(M + 5 * N + K)
+    A = ri.integer_matrix(g, M, K, bound=3)
+    B = ri.integer_matrix(g, K, N, bound=3)
+    exact = (A.astype(np.int64) @ B.astype(np.int64)).astype(np.float32)
+
+    def placed(x, trans):
+        x = np.ascontiguousarray(x.T if trans else x)
+        ld = x.shape[1] + 3 - x.shape[1] % 2  # odd
+        buf = torch.full((x.shape[0] * ld + 8,), float("nan"), device="cuda")
+        v = buf[1:1 + x.shape[0] * ld].view(x.shape[0], ld)
+        v[:, :x.shape[1]] = dev(x)
+        return v, ld
+
+    (dA, lda), (dB, ldb) = placed(A, ops[0]), placed(B, ops[1])
+    for tile in rise.rise_gemm_tiles("f32"):
+        print(f"gemm f32 short k {M}x{N}x{K} ops={ops} tile={tile}", flush=True)
+        C = torch.empty((M, N), device="cuda")
+        rise.rise_gemm(C, dA, dB, M, N, K, lda=lda, ldb=ldb, ldc=N, opA=int(ops[0]),
+                       opB=int(ops[1]), mode="f32", tile=tile)
+        assert np.array_equal(host(C), exact), tile
