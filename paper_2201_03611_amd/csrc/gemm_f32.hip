@@ -142,8 +142,8 @@ rise_status launch_fill(const GemmF32Args& a, hipStream_t s) {
 
 // Rows that are not whole aligned chunks go through registers while K is short: a
 // ring fills with a quarter of the instructions, and its first three slabs in one
-// memory latency (64 x 64 tiles, by values and staged: 1664 x 903 x 79 14.2 and 11.8 us, 5001 x
-// 5003 x 101 125 and 100, x 301 198 and 190).  Over a longer K copies that need no
+// memory latency (64 x 64 tiles, by values and staged: 1664 x 903 x 79 14.2 and 11.6 us, 5001 x
+// 5003 x 101 125 and 101, x 301 198 and 190).  Over a longer K copies that need no
 // registers run further ahead (1000 x 1531 x 777 32.2 and 35.5 us, 3001^3 479 and
 // 516), and 256 x 128 tiles gain nothing.
 constexpr int kStagedMaxK = 320;
@@ -204,7 +204,7 @@ rise_tile gemm_f32_default_tile(int M, int N, int K) {
   // us; 512 x 512 x 512: 64 of 64 x 64, 14 us, 256 of 32 x 32, 8 us).  256 x 128
   // of a long K only where rows are whole 16-byte chunks whichever way they are
   // stored: copied value by value it measured slower than 64 x 64 (4095 x 4097 x 4096:
-  // 1.52 against 1.10 ms; 5001 x 5003 x 101 114 against 125 us, x 301 207 and 198).
+  // 1.52 against 1.10 ms; 5001 x 5003 x 101 113 and 101 us, 5642 x 2784 x 139 66 and 75).
   // 32 x 32 tiles of a short K run gemm_f32_split_kernel, whose waves wait out
   // one memory latency per 32 k but need no ring to fill (128^3: 4.1 against 4.9
   // us); of a long K the ring (64 x 64 x 4096: 22 against 38 us).  Where rows are

@@ -164,7 +164,31 @@ struct AsyncSlab {
     shift = min(mn0 + mn - col, PC - 1);
     return k * ld + (col - base_mn(mn0, mn_total));
   }
-  // the same chunk value by value, zeros from k = kend on
+  // a 16-byte load from any 4-byte boundary (gfx950 runs global memory in
+  // unaligned-access mode)
+  __device__ static f32x4 load_any(const void* from) {
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    return f32x4(*reinterpret_cast<const f32x4u*>(from));
+  }
+  // a chunk of the last slab, zeros from k = kend on (and of any slab, by 64-bit
+  // address).  A chunk along k that would pass kend is loaded further left, from the
+  // slab before where this one is shorter than a chunk, and shifted.
+  __device__ static f32x4 staged_tail(const float* base, int64_t ld, int mn0, int mn_total, int kend,
+                                      int i, int lane) {
+    int mn, k;
+    place(i, lane, mn, k);
+    if (ALONG_K) {
+      const int from = min(k, kend - 4), s = k - from;
+      f32x4 v = load_any(base + (min(mn, mn_total - 1 - mn0) * ld + from));
+      if (s & 1) v = f32x4{v.y, v.z, v.w, 0.f};
+      if (s & 2) v = f32x4{v.z, v.w, 0.f, 0.f};
+      return s >= 4 ? f32x4{0.f, 0.f, 0.f, 0.f} : v;
+    }
+    const int col = min(mn0 + mn, mn_total - PC) - base_mn(mn0, mn_total);
+    const f32x4 v = load_any(base + (min(k, kend - 1) * ld + col));
+    return k >= kend ? f32x4{0.f, 0.f, 0.f, 0.f} : v;
+  }
+  // the same chunk value by value
   __device__ static f32x4 staged_values(const float* base, int64_t ld, int mn0, int mn_total, int kend,
                                         int i, int lane) {
     int mn, k;
@@ -327,8 +351,9 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
   constexpr int PRODUCTS = PARTS * (PARTS + 1) / 2;
   static_assert(PARTS == 1 || (!TA && TB && VEC && !KBLOCKED && PARTS <= 3), "prepared planes");
   const int nk1 = (K + BK - 1) / BK, krem = K - (nk1 - 1) * BK, nk = PRODUCTS * nk1;
-  const bool wide = lda >= kF32OffsetLd || ldb >= kF32OffsetLd ||
-                    (STAGED && ((TA && M < 4) || (!TB && N < 4)));
+  // (STAGED) an operand has rows shorter than a chunk
+  const bool tiny = STAGED && ((TA ? M : K) < 4 || (TB ? K : N) < 4);
+  const bool wide = lda >= kF32OffsetLd || ldb >= kF32OffsetLd || tiny;
   // the next slab to copy (its first value in the tile's first row or column);
   // past the last slab the last one is copied again, into a stage nothing reads
   const V* pa = async::uniform(A + (!TA ? (int64_t)m0 * lda : STAGED ? SA::base_mn(m0, M) : m0));
@@ -369,18 +394,19 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
   auto load = [&](int j, auto careful) -> f32x4 {
     if (decltype(careful)::value && (wide || (next >= nk - 1 && krem < BK))) {
       const int kend = next >= nk - 1 ? krem : BK;
+      const float *fa = (const float*)pa, *fb = (const float*)pb;
       int ln = lane;
       asm volatile("" : "+v"(ln));
-      return is_a(j) ? SA::staged_values((const float*)pa, lda, m0, M, kend, number(j), ln)
-                     : SB::staged_values((const float*)pb, ldb, n0, N, kend, number(j) - SA::COPIES, ln);
+      if (tiny)
+        return is_a(j) ? SA::staged_values(fa, lda, m0, M, kend, number(j), ln)
+                       : SB::staged_values(fb, ldb, n0, N, kend, number(j) - SA::COPIES, ln);
+      return is_a(j) ? SA::staged_tail(fa, lda, m0, M, kend, number(j), ln)
+                     : SB::staged_tail(fb, ldb, n0, N, kend, number(j) - SA::COPIES, ln);
     }
-    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-    const char* from = is_a(j) ? (const char*)pa : (const char*)pb;
-    return f32x4(*reinterpret_cast<const f32x4u*>(from + off[j]));
+    return SA::load_any((is_a(j) ? (const char*)pa : (const char*)pb) + off[j]);
   };
-  // careful: the slab may hold values put in place one by one
-  auto store = [&](int j, f32x4 v, uint32_t at, bool by_value) {
-    if (shifted && !by_value) {  // a shifted chunk's values move to their columns
+  auto store = [&](int j, f32x4 v, uint32_t at) {
+    if (shifted && !tiny) {  // a shifted chunk's values move to their columns
       const uint32_t sh = shifts >> 2 * j;
       if (sh & 1) v = f32x4{v.y, v.z, v.w, v.w};
       if (sh & 2) v = f32x4{v.z, v.w, v.w, v.w};
@@ -436,15 +462,11 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
     }
   };
   constexpr int NR = TM + TN;
-  bool held_by_value = false;  // how the slab in flight was loaded
-  auto by_value = [&] { return wide || (next >= nk - 1 && krem < BK); };
   if constexpr (STAGED) {
     if (nk > 0) {
       f32x4 first[STAGES - 1][NCP];
-      bool values[STAGES - 1];
 #pragma unroll
       for (int st = 0; st < STAGES - 1; st++) {
-        values[st] = by_value();
 #pragma unroll
         for (int j = 0; j < NCP; j++) first[st][j] = load(j, std::true_type{});
         advance();
@@ -452,8 +474,7 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
 #pragma unroll
       for (int st = 0; st < STAGES - 1; st++)
 #pragma unroll
-        for (int j = 0; j < NCP; j++) store(j, first[st][j], st * STAGE_BYTES, values[st]);
-      held_by_value = by_value();
+        for (int j = 0; j < NCP; j++) store(j, first[st][j], st * STAGE_BYTES);
 #pragma unroll
       for (int j = 0; j < NCP; j++) held[j] = load(j, std::true_type{});
       advance();
@@ -499,7 +520,7 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
             if (o < NR)
               read(last ? after : buf, last ? 0 : st + 1, o);
             else if constexpr (STAGED) {
-              store(c0 + o - NR, held[c0 + o - NR], put, held_by_value);
+              store(c0 + o - NR, held[c0 + o - NR], put);
               held[c0 + o - NR] = load(c0 + o - NR, careful);
             } else
               copy(c0 + o - NR, careful);
@@ -510,7 +531,6 @@ __device__ __forceinline__ void gemm_ring_tile(float* __restrict__ C, int64_t ld
       }
     };
     steps(steps, std::integral_constant<int, 0>{});
-    if (STAGED) held_by_value = by_value();
     advance();
     buf = after;
   };
