@@ -29,6 +29,14 @@ __device__ __forceinline__ void wait_lgkmcnt0() {
 #endif
 }
 
+// The wait state gfx950 needs between a write of M0, which holds a copy's LDS base,
+// and the copy.  The compiler adds it in front of its own instructions only, and
+// writes M0 directly before the asm of most copies; without it a copy can land
+// where the one before it did.  (A base in scalar registers needs five after a vector
+// instruction that wrote it.  Bases are advanced by scalar arithmetic, well past
+// that; tests/test_wait_states.py checks both in the built library.)
+#define RISE_M0_WAIT "s_nop 0\n\t"
+
 // workgroup barrier without a memory fence; the scheduling barriers keep the
 // compiler from moving any instruction across it
 __device__ __forceinline__ void barrier() {
@@ -52,7 +60,7 @@ __device__ __forceinline__ void copy16(const void* src, void* lds_base) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const uint32_t base = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)lds_base));
-  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(base) : "memory");
+  asm volatile(RISE_M0_WAIT "global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(base) : "memory");
 #endif
 }
 // 4 bytes per lane, global -> LDS at lds_base + 4 * lane, the same way
@@ -60,7 +68,7 @@ __device__ __forceinline__ void copy4(const void* src, void* lds_base) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const uint32_t base = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char*)lds_base));
-  asm volatile("global_load_lds_dword %0, off" ::"v"(src), "{m0}"(base) : "memory");
+  asm volatile(RISE_M0_WAIT "global_load_lds_dword %0, off" ::"v"(src), "{m0}"(base) : "memory");
 #endif
 }
 
@@ -86,22 +94,22 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 // uniform step.
 __device__ __forceinline__ void copy16_at(const void* base, uint32_t off, uint32_t to) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(to) : "memory");
+  asm volatile(RISE_M0_WAIT "global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(to) : "memory");
 #endif
 }
 __device__ __forceinline__ void copy4_at(const void* base, uint32_t off, uint32_t to) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("global_load_lds_dword %0, %1" ::"v"(off), "s"(base), "{m0}"(to) : "memory");
+  asm volatile(RISE_M0_WAIT "global_load_lds_dword %0, %1" ::"v"(off), "s"(base), "{m0}"(to) : "memory");
 #endif
 }
 __device__ __forceinline__ void copy16_from(const void* src, uint32_t to) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(to) : "memory");
+  asm volatile(RISE_M0_WAIT "global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(to) : "memory");
 #endif
 }
 __device__ __forceinline__ void copy4_from(const void* src, uint32_t to) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("global_load_lds_dword %0, off" ::"v"(src), "{m0}"(to) : "memory");
+  asm volatile(RISE_M0_WAIT "global_load_lds_dword %0, off" ::"v"(src), "{m0}"(to) : "memory");
 #endif
 }
 
