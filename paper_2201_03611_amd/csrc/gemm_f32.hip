@@ -19,8 +19,12 @@ using tiles::kThreads;
 // registers, or 4-byte copies.
 enum Fill { CHUNKS, STAGED, VALUES };
 
+// Two waves to a SIMD, if by two workgroups of four waves: while one waits for its
+// ring to fill or stores its tile the other computes.  (256 x 128, left to take more
+// than half of the registers, ran 4096^3 in 972 us instead of 933 and, with three slabs
+// of 4-byte copies to a tile, 6681 x 6656 x 83 in 160 instead of 119.)
 template <typename T, bool TA, bool TB, Fill FILL>
-__global__ __launch_bounds__(T::THREADS, T::WAVES / 4) void gemm_f32_kernel(
+__global__ __launch_bounds__(T::THREADS, T::WAVES < 8 ? 2 : T::WAVES / 4) void gemm_f32_kernel(
     float* __restrict__ C, int64_t ldc, const float* __restrict__ A, int64_t lda,
     const float* __restrict__ B, int64_t ldb, int M, int N, int K, int tiles_m, int tiles_n) {
   __shared__ f32x4 lds[T::LDS_CHUNKS];

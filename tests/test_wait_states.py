@@ -9,33 +9,14 @@ before it did.
 """
 import os
 import re
-import shutil
-import struct
 import subprocess
 
 import pytest
 
-import paper_2201_03611_amd as rise
+from _code_objects import code_objects, library, tool
 
-MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
-OBJDUMP = shutil.which("llvm-objdump") or "/opt/rocm/llvm/bin/llvm-objdump"
+OBJDUMP = tool("llvm-objdump")
 M0_STATES, SADDR_STATES = 1, 5
-
-
-def code_objects(path):
-    """The gfx950 code objects of a library of offload bundles."""
-    data = open(path, "rb").read()
-    at = data.find(MAGIC)
-    while at >= 0:
-        n, = struct.unpack_from("<Q", data, at + len(MAGIC))
-        p = at + len(MAGIC) + 8
-        for _ in range(n):
-            off, size, idlen = struct.unpack_from("<QQQ", data, p)
-            ident = data[p + 24:p + 24 + idlen].decode()
-            p += 24 + idlen
-            if "gfx950" in ident and size:
-                yield data[at + off:at + off + size]
-        at = data.find(MAGIC, at + len(MAGIC))
 
 
 def registers(operand):
@@ -91,9 +72,8 @@ def test_checker_sees_what_is_missing():
 
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler in this image")
 def test_copies_of_the_built_library_have_their_wait_states(tmp_path):
-    lib = os.path.join(os.path.dirname(rise.__file__), "librise.so")
     copies = 0
-    for i, code in enumerate(code_objects(lib)):
+    for i, code in enumerate(code_objects(library())):
         obj = tmp_path / f"{i}.co"
         obj.write_bytes(code)
         out = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(obj)], capture_output=True,
