@@ -92,7 +92,10 @@ int32_t rise_gemm_tiles(rise_mode mode, rise_tile* out, int32_t cap);
  * *out the tile the library picks for these sizes and mode -- the tune cache's
  * entry for them on the current device if there is one, else the built-in
  * default (Sec. IV-B/C leave that choice to a strategy outside the program;
- * this reports it).  Host-only, enqueues nothing.  Errors: sizes outside
+ * this reports it).  FP32: the default of row-major contiguous operands on
+ * 16-byte boundaries; rise_gemm itself goes by how the operands it gets are
+ * stored (transposes, leading dimensions, alignment).  Host-only, enqueues
+ * nothing.  Errors: sizes outside
  * [0, 2^31) (RISE_ERR_SHAPE), an unknown mode (RISE_ERR_UNSUPPORTED), out NULL
  * (RISE_ERR_NULL); *out is then left unchanged. */
 rise_status rise_gemm_default_tile(int64_t M, int64_t N, int64_t K, rise_mode mode,

@@ -115,7 +115,8 @@ def rise_gemm_tiles(mode):
 
 
 def rise_gemm_default_tile(M, N, K, mode="f32"):
-    """The tile rise_gemm runs with tile=None, as (bm, bn, bk)."""
+    """The tile rise_gemm runs with tile=None, as (bm, bn, bk); FP32: on row-major
+    contiguous operands (it goes by how the operands are stored)."""
     t = RiseTile()
     _check(lib.rise_gemm_default_tile(M, N, K, _mode(mode), ctypes.byref(t)),
            "rise_gemm_default_tile")

@@ -71,12 +71,15 @@ bool overlaps(Range a, Range b) {
 bool dim_ok(int64_t v) { return v >= 0 && v < kDimLimit; }
 
 // The tile a GEMM runs when the caller passes none: the tune cache's entry for
-// these sizes and mode on this device, else the built-in default of the mode.
+// these sizes and mode on this device, else the built-in default of the mode (FP32:
+// of operands stored as row-major contiguous arrays; rise_gemm looks at them).
+bool tuned_gemm_tile(int64_t M, int64_t N, int64_t K, rise_mode mode, rise_tile* t) {
+  return M > 0 && N > 0 && K > 0 && tune_lookup_gemm(M, N, K, (int)mode, t) &&
+         (mode == RISE_MODE_F32 ? gemm_f32_tile_supported(*t) : gemm_lowp_tile_supported(mode, *t));
+}
 rise_tile chosen_gemm_tile(int64_t M, int64_t N, int64_t K, rise_mode mode) {
   rise_tile t;
-  if (M > 0 && N > 0 && K > 0 && tune_lookup_gemm(M, N, K, (int)mode, &t) &&
-      (mode == RISE_MODE_F32 ? gemm_f32_tile_supported(t) : gemm_lowp_tile_supported(mode, t)))
-    return t;
+  if (tuned_gemm_tile(M, N, K, mode, &t)) return t;
   return mode == RISE_MODE_F32 ? gemm_f32_default_tile((int)M, (int)N, (int)K)
                                : gemm_lowp_default_tile(mode, (int)M, (int)N, (int)K);
 }
@@ -170,11 +173,15 @@ rise_status rise_gemm(float* C, int64_t ldc, const void* A, rise_dtype tA, int64
   if (mode == RISE_MODE_F32) {
     if (tA != RISE_F32 || tB != RISE_F32)
       return fail(RISE_ERR_DTYPE, "rise_gemm: mode F32 needs FP32 operands");
-    rise_tile t = tile ? *tile : chosen_gemm_tile(M, N, K, mode);
-    if (!gemm_f32_tile_supported(t))
-      return fail(RISE_ERR_UNSUPPORTED, "rise_gemm: tile not supported for mode F32");
     GemmF32Args a{C, ldc, (const float*)A, lda, (const float*)B, ldb, (int)M, (int)N, (int)K,
                   opA == RISE_OP_T, opB == RISE_OP_T};
+    rise_tile t;
+    if (tile)
+      t = *tile;
+    else if (!tuned_gemm_tile(M, N, K, mode, &t))
+      t = gemm_f32_default_tile(a);
+    if (!gemm_f32_tile_supported(t))
+      return fail(RISE_ERR_UNSUPPORTED, "rise_gemm: tile not supported for mode F32");
     return launch_gemm_f32(a, t, (hipStream_t)stream);
   }
 

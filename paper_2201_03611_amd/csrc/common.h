@@ -66,7 +66,9 @@ struct GemmF32Args {
   bool ta, tb;
 };
 bool gemm_f32_tile_supported(const rise_tile& t);
+// the default tile of row-major contiguous operands, and of operands as stored
 rise_tile gemm_f32_default_tile(int M, int N, int K);
+rise_tile gemm_f32_default_tile(const GemmF32Args& a);
 int gemm_f32_tiles(rise_tile* out, int cap);
 rise_status launch_gemm_f32(const GemmF32Args& a, const rise_tile& t, hipStream_t s);
 

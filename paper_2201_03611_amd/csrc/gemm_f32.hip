@@ -149,7 +149,7 @@ rise_status launch_fill(const GemmF32Args& a, hipStream_t s) {
 // memory latency (64 x 64 tiles, by values and staged: 1664 x 903 x 79 14.2 and 11.6 us, 5001 x
 // 5003 x 101 125 and 101, x 301 198 and 190).  Over a longer K copies that need no
 // registers run further ahead (1000 x 1531 x 777 32.2 and 35.5 us, 3001^3 479 and
-// 516), and 256 x 128 tiles gain nothing.
+// 516), and 256 x 128 tiles gain nothing (6681 x 6656 x 83 119 us either way).
 constexpr int kStagedMaxK = 320;
 
 template <typename T>
@@ -177,15 +177,19 @@ rise_status launch_split(const GemmF32Args& a, hipStream_t s) {
 // The tiles, and nanoseconds per 64 x 64 outputs and k that one CU takes on them
 // (measured: 256 x 128 at 4096^3, 32 x 32 x 32 at 512^3, 32 x 32 x 128 at 64 x 64 x
 // 4096, the others at 1024^3, 1000 x 1531 x 777 and 1500 x 300 x 6000; the matrix
-// cores alone need 13.6 at 2.3 GHz).  0: only where asked for.
+// cores alone need 13.6 at 2.3 GHz), where rows are whole aligned chunks and where
+// they are not (what differs is how the two kinds of 32 x 32 tiles compare with the
+// rest: the split kernel's loads keep their width).  0: only where asked for.
 struct TileCost {
   rise_tile t;
-  double ns;
+  double ns, ns_values;
 };
-const TileCost kTiles[] = {{{128, 128, 32}, 0},  {{128, 64, 32}, 16.0}, {{64, 128, 32}, 16.0},
-                           {{64, 64, 32}, 16.5}, {{256, 128, 16}, 14.6}, {{64, 96, 32}, 17.0},
-                           {{96, 64, 32}, 16.5}, {{64, 32, 64}, 19.5},  {{32, 64, 64}, 19.5},
-                           {{32, 32, 32}, 36.0}, {{32, 32, 128}, 18.5}};
+const TileCost kTiles[] = {{{128, 128, 32}, 0, 0},        {{128, 64, 32}, 16.0, 16.0},
+                           {{64, 128, 32}, 16.0, 16.0},   {{64, 64, 32}, 16.5, 16.5},
+                           {{256, 128, 16}, 14.6, 14.6},  {{64, 96, 32}, 17.0, 17.0},
+                           {{96, 64, 32}, 16.5, 16.5},    {{64, 32, 64}, 19.5, 19.5},
+                           {{32, 64, 64}, 19.5, 19.5},    {{32, 32, 32}, 36.0, 26.0},
+                           {{32, 32, 128}, 18.5, 22.0}};
 
 }  // namespace
 
@@ -201,44 +205,59 @@ int gemm_f32_tiles(rise_tile* out, int cap) {
   return n;
 }
 
-rise_tile gemm_f32_default_tile(int M, int N, int K) {
+rise_tile gemm_f32_best_tile(int M, int N, int K, bool chunks) {
   // The tile with the shortest time for the CU that gets the most tiles: what the
   // shapes differ in is mainly how evenly they cover 256 CUs (1000 x 1531: 384
   // tiles of 64 x 64, two on half of the CUs, 36 us; 256 of 64 x 96, one each, 31
-  // us; 512 x 512 x 512: 64 of 64 x 64, 14 us, 256 of 32 x 32, 8 us).  256 x 128
-  // of a long K only where rows are whole 16-byte chunks whichever way they are
-  // stored: copied value by value it measured slower than 64 x 64 (4095 x 4097 x 4096:
-  // 1.52 against 1.10 ms; 5001 x 5003 x 101 113 and 101 us, 5642 x 2784 x 139 66 and 75).
+  // us; 512 x 512 x 512: 64 of 64 x 64, 14 us, 256 of 32 x 32, 8 us).
   // 32 x 32 tiles of a short K run gemm_f32_split_kernel, whose waves wait out
   // one memory latency per 32 k but need no ring to fill (128^3: 4.1 against 4.9
-  // us); of a long K the ring (64 x 64 x 4096: 22 against 38 us).  Where rows are
-  // not whole chunks the ring's copies go value by value and the crossing lies
-  // further out (130 x 333 x 1601 16.7 against 20.2 us, 555 x 85 x 3001 27.4 and
-  // 26.4), and so is the time of the split kernel lower beside them.
+  // us); of a longer K the ring (814 x 200 x 1024, rows of whole chunks: 8.9 against
+  // 11.3 us; 64 x 64 x 4096: 22 against 38 us).  Where rows are not whole chunks the
+  // ring's copies go value by value and the crossing lies further out (130 x 333 x
+  // 1601 16.7 against 20.2 us, 555 x 85 x 3001 27.4 and 26.4), and so is the time of
+  // the split kernel lower beside them.
   // That holds while the split kernel's tiles are few; many of them read each row
-  // of A and B too often (5755 x 6140 x 112: 216 us, 256 x 128 70).
+  // of A and B too often (5755 x 6140 x 112: 216 us, 256 x 128 102).
   // Every round also pays for the stages a ring starts with and for the store of
   // the tile, as K grows short most of its time: counted as four stages and 128 k,
   // and a last round that is not full runs somewhat faster than a full one (without
-  // these 1664 x 903 x 79 took 64 x 32 tiles, 23.9 us, 32 x 32 11.0; over 900 random
-  // shapes up to 7000 x 7000 x 3000 the choice was 9.3 % above the best tile of
-  // each, 1.7 with them).
-  const bool chunks = M % 4 == 0 && N % 4 == 0 && K % 4 == 0;
-  const int split_max_k = chunks ? 1024 : 2560;
+  // these 1664 x 903 x 79 took 64 x 32 tiles, 23.9 us, 32 x 32 11.0).  256 x 128 tiles
+  // are resident in pairs, and the last ones can go in pairs to some CUs while others
+  // are idle, which counts where rows are whole chunks (5968 x 2961 x 1128, 576 tiles,
+  // takes 1.5 times as long as in 64 x 64; by 4-byte copies the fill hides more of it).
+  // `chunks` has to be how the operands are stored: M says nothing about the rows of
+  // A as stored, nor N about those of B read through transpose, and a padded row can
+  // break the alignment of sizes that are whole chunks.  Over 1500 random shapes up to
+  // 7000 x 7000 x 3000 of which every tile was timed, the choice is 1.3 to 1.8 %
+  // above the best tile of each by class, 1.6 where taken from the three sizes it was 5.0
+  // (170 x 1020 x 2304 23.1 us instead of 15.8, 480 x 447 x 2388 21.4 and 16.0).
+  const int split_max_k = chunks ? 768 : 2560;
   rise_tile best{64, 64, 32};
   double least = 0;
   for (const auto& c : kTiles) {
-    if (c.ns == 0 || (c.t.bm == 256 && !chunks && K > 512)) continue;
+    if (c.ns == 0) continue;
     if (c.t.bm == 32 && c.t.bn == 32 && (c.t.bk == 128) != (K > split_max_k)) continue;
     const bool split = c.t.bm == 32 && c.t.bn == 32 && c.t.bk == 32;
     const int64_t tiles = (((int64_t)M + c.t.bm - 1) / c.t.bm) * (((int64_t)N + c.t.bn - 1) / c.t.bn);
-    const double ns = split && !chunks && tiles <= 2048 ? 26.0 : c.ns;
+    const double ns = chunks || (split && tiles > 2048) ? c.ns : c.ns_values;
     const double k = (double)K + 128 + (split ? 0 : 4 * c.t.bk);
-    const double rounds = 0.85 * (double)((tiles + 255) / 256) + 0.15 * (double)tiles / 256;
+    double rounds = 0.85 * (double)((tiles + 255) / 256) + 0.15 * (double)tiles / 256;
+    if (c.t.bm == 256 && chunks)
+      rounds += 0.2 * (double)(2 * ((tiles + 511) / 512) - (tiles + 255) / 256);
     const double t = rounds * c.t.bm * c.t.bn * ns * k;
     if (least == 0 || t < least) least = t, best = c.t;
   }
   return best;
+}
+
+rise_tile gemm_f32_default_tile(int M, int N, int K) {
+  return gemm_f32_best_tile(M, N, K, N % 4 == 0 && K % 4 == 0);
+}
+
+rise_tile gemm_f32_default_tile(const GemmF32Args& a) {
+  return gemm_f32_best_tile(
+      a.M, a.N, a.K, tiles::whole_chunks(a.A, a.lda, a.B, a.ldb, a.M, a.N, a.K, a.ta, a.tb));
 }
 
 rise_status launch_gemm_f32(const GemmF32Args& a, const rise_tile& t, hipStream_t s) {

@@ -433,3 +433,37 @@ def test_f32_short_k_any_alignment_integer_exact(rise, ops, M, N, K):
         rise.rise_gemm(C, dA, dB, M, N, K, lda=lda, ldb=ldb, ldc=N, opA=int(ops[0]),
                        opB=int(ops[1]), mode="f32", tile=tile)
         assert np.array_equal(host(C), exact), tile
+
+
+@pytest.mark.parametrize("M,N,K,ops,pad,offset,tile,by_sizes", [
+    # rows of whole aligned chunks although M, N or K is not a multiple of 4
+    (170, 1020, 2304, (False, False), 0, 0, (32, 32, 128), (32, 32, 32)),
+    (480, 447, 2388, (False, True), 0, 0, (32, 32, 128), (32, 32, 32)),
+    (512, 512, 2001, (True, False), 0, 0, (32, 32, 128), (32, 32, 32)),
+    (4095, 4096, 528, (False, False), 0, 0, (256, 128, 16), (128, 64, 32)),
+    # sizes of whole chunks in rows that are not aligned
+    (512, 512, 2000, (False, False), 1, 0, (32, 32, 32), (32, 32, 128)),
+    (512, 512, 2000, (False, True), 0, 1, (32, 32, 32), (32, 32, 128))])
+def test_f32_default_tile_goes_by_storage(rise, M, N, K, ops, pad, offset, tile, by_sizes):
+    # the tiles sum K in different orders, so the bits tell which one ran: the one
+    # for how the rows lie in memory, not the one that the three sizes suggest
+    import torch
+
+    def placed(r, c, seed):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(seed)
+        buf = torch.rand(r * (c + pad) + 4, device="cuda", generator=gen) * 2 - 1
+        return buf[offset:offset + r * (c + pad)], c + pad
+
+    A, lda = placed(K if ops[0] else M, M if ops[0] else K, 1)
+    B, ldb = placed(N if ops[1] else K, K if ops[1] else N, 2)
+
+    def product(t):
+        C = torch.empty((M, N), device="cuda")
+        rise.rise_gemm(C, A, B, M, N, K, lda=lda, ldb=ldb, ldc=N, opA=int(ops[0]),
+                       opB=int(ops[1]), tile=t)
+        return C
+
+    C = product(None)
+    assert torch.equal(C, product(tile))
+    assert not torch.equal(C, product(by_sizes))
