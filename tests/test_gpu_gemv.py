@@ -166,3 +166,16 @@ def test_gemv_row_pairs_and_long_splits_integer_exact(rise, trans, M, K):
     exact = (A.astype(np.int64) @ x.astype(np.int64)).astype(np.float32)[:, 0]
     stored = np.ascontiguousarray(A.T) if trans else A
     assert np.array_equal(run(rise, stored, x, trans, x_offset=1), exact)
+
+
+@pytest.mark.parametrize("parts", [2, 3, 5, 31, 32, 33, 36, 60, 64, 65, 68, 100, 127, 129])
+def test_gemv_partial_rows_integer_exact(rise, parts):
+    # the reduction of the split product: fewer parts than waves, and whole and ragged
+    # rounds of loads for each wave
+    M, K = 301, 64 * parts
+    assert rise.rise_gemv_parts(M, K, rise.RISE_OP_T) == parts
+    g = ri.rng(parts)
+    A = ri.integer_matrix(g, M, K, bound=3)
+    x = ri.integer_matrix(g, K, 1, bound=3)
+    exact = (A.astype(np.int64) @ x.astype(np.int64)).astype(np.float32)[:, 0]
+    assert np.array_equal(run(rise, np.ascontiguousarray(A.T), x, True, x_offset=1), exact)
