@@ -127,8 +127,8 @@ __global__ __launch_bounds__(WAVES == 1 ? kThreads : 64 * WAVES) void gemv_rows(
 //     workgroup quarters the partial sums that a split over workgroups alone
 //     writes for the same number of waves (4096^2 with the reduction: 18.5 -> 15.3
 //     us, 512 x 16384 19.5 -> 10.3 us).
-//   KS = 1, UN = 2: 1024 columns a workgroup, for wide matrices, where one row
-//     of a workgroup is 4 KB of consecutive memory (16384^2: 171 us against 198).
+//   KS = 1, UN = 2: 1024 columns a workgroup, for large matrices: one row of a
+//     workgroup is 4 KB of consecutive memory (16384^2: 162 us against 198).
 // Lanes at the right edge load the last four columns instead (their sums are
 // written by column, so nothing is counted twice).
 template <int KS, int UN>
@@ -224,22 +224,20 @@ struct ColSplit {
 };
 ColSplit col_split(int64_t M, int64_t K) {
   ColSplit c;
-  // wide rows and enough of them for a good two workgroups per compute unit
-  // (measured, outputs x K, wide and narrow: 6000^2 31.5 and 33.5 us, 7112 x 6144 36.4
-  // and 40.0, 5000 x 8000 34.9 and 36.6; below either line 10848 x 3184 32.1 and 30.0,
-  // 4416 x 5888 27.4 and 25.3, 2176 x 12720 27.1 and 24.3)
+  // Wide workgroups, where there are enough chunks of 64 rows for them: about 400,
+  // whichever way they lie (outputs x K, wide and narrow: 16278 x 1029 15.4 and
+  // 14.8 us, 12584 x 1588 16.3 and 16.1, 8192 x 3000 18.4 both, 7060 x 3920 19.6 and 21.6,
+  // 2000 x 14000 20.4 and 21.6, 1000 x 40000 29.5 and 30.1, 3000 x 12000 24.8 and 26.3,
+  // 6000^2 24.2 and 26.8, 16384^2 162 and 198); few outputs leave most of its columns
+  // empty (64 x 200000 41.2 and 17.3, 300 x 60000 22.0 and 21.2).
   const int64_t wide_blocks = (M + kWideCols - 1) / kWideCols;
-  c.wide = M >= 4096 && wide_blocks * ((K + 63) / 64) >= 560;
+  c.wide = M >= 512 && wide_blocks * ((K + 63) / 64) >= 400;
   const int cols = c.wide ? kWideCols : kCols;
   c.mblocks = (int)((M + cols - 1) / cols);
-  // about 1024 wide workgroups in all (four per compute unit; 2048 took 202 us at
-  // 16384^2), chunks of at least 64 rows of A; as many narrow ones while a chunk
-  // stays short (outputs x K = 8192 x 3000 23.2 us with 1024, 28.2 with 2176; 7104 x
-  // 3566 24.4 and 25.8), 2176 of a longer K, for two
-  // workgroups per compute unit also when counted by 1024 columns, which a test pins
-  // (3000 x 12000 34.5 us, 30.9 with 1024)
-  const int64_t blocks = c.wide || K <= 8192 ? 1024 : 2176;
-  int64_t want = std::min<int64_t>(1024, (blocks + c.mblocks - 1) / c.mblocks);
+  // about 1024 workgroups in all, four per compute unit, and chunks of at least 64 rows
+  // of A (with 2048, 16384^2 took 202 us; narrow ones with 2176, 500 x 100000 40.9 us
+  // and 36.8, 300 x 60000 23.6 and 21.2, 3000 x 10000 22.9 and 22.6)
+  int64_t want = std::min<int64_t>(1024, (1024 + c.mblocks - 1) / c.mblocks);
   int64_t most = std::max<int64_t>(1, (K + 63) / 64);
   c.kchunks = (int)std::max<int64_t>(1, std::min(want, most));
   c.kchunk = (int)((K + c.kchunks - 1) / c.kchunks);
@@ -312,14 +310,13 @@ rise_status launch_gemv(const GemvArgs& a, void* ws, hipStream_t s) {
 // array instead of a caller workspace.  Its size covers every split col_split
 // picks: kchunks > 1 only when there are fewer column blocks than workgroups
 // wanted, and then kchunks * M <= ceil(1024 / mblocks) * mblocks * 1024 <= 2046 *
-// 1024 floats (wide) or <= 4350 * 256 floats.
+// 1024 floats (wide; a quarter of that narrow).
 // Each device holds its own copy for the life of the process; its device
 // address is looked up once per device (hipGetSymbolAddress with that device
 // current) and only that address is handed to kernels.
 // ---------------------------------------------------------------------------
 constexpr size_t kGemvScratchBytes = RISE_GEMV_NOALLOC_SCRATCH_BYTES;
-static_assert(kGemvScratchBytes >= (size_t)2046 * kWideCols * 4 &&
-                  kGemvScratchBytes >= (size_t)4350 * kCols * 4, "scratch below the largest split");
+static_assert(kGemvScratchBytes >= (size_t)2046 * kWideCols * 4, "scratch below the largest split");
 static __device__ __align__(256) unsigned char scratch[kGemvScratchBytes];
 
 namespace {

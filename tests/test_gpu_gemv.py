@@ -179,3 +179,18 @@ def test_gemv_partial_rows_integer_exact(rise, parts):
     x = ri.integer_matrix(g, K, 1, bound=3)
     exact = (A.astype(np.int64) @ x.astype(np.int64)).astype(np.float32)[:, 0]
     assert np.array_equal(run(rise, np.ascontiguousarray(A.T), x, True, x_offset=1), exact)
+
+
+@pytest.mark.parametrize("M,K", [(511, 25601), (513, 25665), (1025, 25003), (3001, 12001), (4097, 9001),
+                                 (5003, 6007), (9001, 4099), (16387, 1543)])
+def test_gemv_transposed_wide_kernel_integer_exact(rise, M, K):
+    # on both sides of its fewest outputs and well inside its range: odd outputs, rows at
+    # every 4-byte offset and chunks of K with remainders; at least 400 workgroups,
+    # counted by the columns that one has
+    cols = 1024 if M >= 512 else 256
+    assert rise.rise_gemv_parts(M, K, rise.RISE_OP_T) * ((M + cols - 1) // cols) >= 400
+    g = ri.rng(M + K)
+    A = ri.integer_matrix(g, M, K, bound=3)
+    x = ri.integer_matrix(g, K, 1, bound=3)
+    exact = (A.astype(np.int64) @ x.astype(np.int64)).astype(np.float32)[:, 0]
+    assert np.array_equal(run(rise, np.ascontiguousarray(A.T), x, True, x_offset=1), exact)
