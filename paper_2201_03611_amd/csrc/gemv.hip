@@ -266,21 +266,23 @@ rise_status launch_gemv(const GemvArgs& a, void* ws, hipStream_t s) {
     const int64_t cus = device_cu_count();
     auto go = [&](auto kernel, int rpw, int waves) {
       const int64_t groups = (a.M + rpw - 1) / rpw;
-      const int64_t blocks = waves == 1 ? std::min<int64_t>((groups + 3) / 4, cus * 32)
-                                        : std::min<int64_t>(groups, cus * 8);
+      const int64_t blocks = std::min<int64_t>(waves == 1 ? (groups + 3) / 4 : groups, cus * 32);
       hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(waves == 1 ? kThreads : 64 * waves), 0,
                          s, a.y, a.A, a.lda, a.x, a.M, a.K, groups);
     };
     // two rows to four waves: 2048 rows are four waves per SIMD,
-    // and each value of x feeds two.  8192^2 43.4 us (6.2 TB/s) where one wave a row took
-    // 46.9 and one wave for four rows 57.2; 16384^2 163.8 against 172.6 and 3566 x
-    // 7104 19.2 against 20.0 with four rows a wave.  Short rows do not feed four
-    // waves: of many, four rows go to one wave (100000 x 64 13.5 against 36.1 us,
-    // 30000 x 1000 22.2 and 25.4; 40000 x 2000 55.0 and 54.8).  Fewer rows go one to
-    // four and to sixteen waves.  Before, all went four to a wave: 4096^2 17.0 -> 13.0
-    // us, 1000 x 40000 60 -> 30, 64 x 16384 14.4 -> 5.0; 1500 x 12345, whose rows are
-    // not 16-byte aligned and went value by value, 96.9 -> 15.4
-    if (a.M >= 10240 && a.K < 2048) go(gemv_rows<4, 1, 2>, 4, 1);
+    // and each value of x feeds two.  8192^2 38.3 us (7.0 TB/s, some of it from the
+    // last-level cache) where one wave for four rows took 48.9; 16384^2 162.3 against
+    // 171.8 and 3566 x 7104 16.0 against 16.5 with four rows a wave.  The grid holds four
+    // times what is resident, as far as there are rows: with no more than is resident,
+    // each walking through the rows, the last ones end unevenly (11344 x 8448 66.3 us,
+    // 63.8 so).  Short rows do not feed four waves: of many, four rows go to one wave
+    // (100000 x 64 13.5 against 36.1 us, 15993 x 868 10.3 and 12.1, 14486 x 1151 12.2 and
+    // 12.7; but 12584 x 1588 14.7 and 13.1, 16000 x 1600 16.6 and 15.8).  Fewer rows go
+    // one to four and to sixteen waves.  Before, all went four to a wave: 4096^2 17.0 ->
+    // 13.0 us, 1000 x 40000 60 -> 30, 64 x 16384 14.4 -> 5.0; 1500 x 12345, whose rows
+    // are not 16-byte aligned and went value by value, 96.9 -> 15.4
+    if (a.M >= 10240 && a.K < 1400) go(gemv_rows<4, 1, 2>, 4, 1);
     else if (a.M >= 2048) go(gemv_rows<2, 4, 2>, 2, 4);
     else if (a.M >= 256) go(gemv_rows<1, 4, 4>, 1, 4);
     else go(gemv_rows<1, 16, 4>, 1, 16);

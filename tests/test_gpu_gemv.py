@@ -194,3 +194,15 @@ def test_gemv_transposed_wide_kernel_integer_exact(rise, M, K):
     x = ri.integer_matrix(g, K, 1, bound=3)
     exact = (A.astype(np.int64) @ x.astype(np.int64)).astype(np.float32)[:, 0]
     assert np.array_equal(run(rise, np.ascontiguousarray(A.T), x, True, x_offset=1), exact)
+
+
+@pytest.mark.parametrize("M,K", [(10239, 1399), (10240, 1399), (10241, 1401), (16383, 1400),
+                                 (16385, 2049), (32771, 1403)])
+def test_gemv_many_rows_integer_exact(rise, M, K):
+    # four rows a wave and two rows to four waves, on both sides of the line between
+    # them and of a grid that holds every row at once
+    g = ri.rng(M + K)
+    A = ri.integer_matrix(g, M, K, bound=3)
+    x = ri.integer_matrix(g, K, 1, bound=3)
+    exact = (A.astype(np.int64) @ x.astype(np.int64)).astype(np.float32)[:, 0]
+    assert np.array_equal(run(rise, A, x, False, x_offset=1), exact)
