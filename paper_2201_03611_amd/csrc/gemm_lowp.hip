@@ -74,9 +74,9 @@ __device__ __forceinline__ void store_tile(float* __restrict__ C, int64_t ldc, i
 
 template <int MODE>
 struct Parts {
-  static constexpr int n = MODE == RISE_MODE_BF16 ? 1 : MODE == RISE_MODE_BF16X3 ? 2 : 3;
+  static constexpr int n = MODE == RISE_MODE_BF16X3 ? 2 : 3;
   // kept products (part of A, part of B): parts i, j with i + j <= n - 1
-  static constexpr int nprod = n == 1 ? 1 : n == 2 ? 3 : 6;
+  static constexpr int nprod = n == 2 ? 3 : 6;
   __device__ static constexpr int pa(int q) {
     constexpr int a[6] = {0, 0, 1, 0, 1, 2};
     return a[q];
@@ -87,20 +87,19 @@ struct Parts {
   }
 };
 
-// NW waves per workgroup in an (NW/2) x 2 grid: with 8 waves two waves share
-// each SIMD, so one wave's barrier and LDS waits are covered by the other's
-// MFMAs (at 0.75 fragment reads per MFMA instead of 0.5, which the LDS
-// bandwidth available to 8 waves sustains).
-template <int BM, int BN, int BK, int MODE, int NW>
-__global__ __launch_bounds__(64 * NW, 1) void packed_bf16_kernel(
+// Split operands staged through registers, all products of a slab together, four waves
+// in a 2 x 2 grid.  Only where asked for by tile: the ring (a product of parts after
+// the other) and the K-blocked kernels are faster.
+template <int BM, int BN, int BK, int MODE>
+__global__ __launch_bounds__(kThreads, 1) void packed_bf16_kernel(
     float* __restrict__ C, int64_t ldc, const uint16_t* __restrict__ Ap,
     const uint16_t* __restrict__ Bp, int M, int N, int Kp, int Mp, int Np, int tiles_m,
     int tiles_n) {
   using P = Parts<MODE>;
   constexpr int NP = P::n;
   constexpr int CH = BK / 8;                 // 16-byte chunks per slab row
-  constexpr int T = 64 * NW;                 // threads
-  constexpr int WM = BM / (NW / 2), WN = BN / 2;
+  constexpr int T = kThreads;
+  constexpr int WM = BM / 2, WN = BN / 2;
   constexpr int TM = WM / 32, TN = WN / 32;
   constexpr int LA = BM * BK / 8 / T;        // chunks per thread per part
   constexpr int LB = BN * BK / 8 / T;
@@ -121,7 +120,6 @@ __global__ __launch_bounds__(64 * NW, 1) void packed_bf16_kernel(
   // requested one slab earlier, is written to LDS, so every global load has
   // about two slabs of MFMA time to arrive; the 256 x 256 tiles keep one set.
   constexpr int NSET = BM >= 256 ? 1 : 2;
-  static_assert(NW == 4 || NW == 8, "wave grid");
   i32x4 ra[NSET][NP][LA], rb[NSET][NP][LB];
   auto fetch = [&](int set, int k0) {
 #pragma unroll
@@ -397,8 +395,8 @@ __device__ __forceinline__ void copy4_to_lds(const void* src, void* lds_base) {
 
 // ---------------------------------------------------------------------------
 // 256 x 256 tiles over K-blocked operands, split formats and FP8.  A K-blocked part
-// holds the K block b of row r (KBB bytes: 64 FP8 codes, 32 bf16 values, or 16
-// for the split formats) at (b * rows + r) * KBB, so the blocks of consecutive
+// holds the K block b of row r (KBB bytes: 64 FP8 codes, or 16 bf16 values of the
+// split formats) at (b * rows + r) * KBB, so the blocks of consecutive
 // rows are contiguous (an FP8 row's two scale bytes of a block sit together in
 // the scale plane).  The register staging of the row-major kernels does not
 // fit beside the 256 accumulator registers of a 256 x 256 tile, so each slab
@@ -431,7 +429,7 @@ struct KBlock {
   static constexpr bool fp8 = MODE == RISE_MODE_FP8;
   static constexpr int parts = fp8 ? 1 : Parts<MODE>::n;
   static constexpr int nprod = fp8 ? 1 : Parts<MODE>::nprod;
-  static constexpr int bytes = parts == 1 ? 64 : 32;  // KBB: bytes of a K block per part
+  static constexpr int bytes = fp8 ? 64 : 32;  // KBB: bytes of a K block per part
   static constexpr int elems = bytes / (fp8 ? 1 : 2);  // K per slab
   static constexpr int ksteps = fp8 ? 1 : elems / 16;  // MFMA k-steps per slab
   static constexpr int stages = parts == 3 ? 3 : 4;
@@ -704,14 +702,11 @@ constexpr int kLongK = 2048;
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
-constexpr int kBf16Waves256 = 4;  // waves per workgroup of the 256 x 256 tiles
-
 template <int BM, int BN, int BK, int MODE>
 rise_status launch_bf16(const PackedGemm& g, hipStream_t s) {
   int tiles_m = g.Mp / BM, tiles_n = g.Np / BN;
-  constexpr int NW = BM >= 256 ? kBf16Waves256 : 4;
-  hipLaunchKernelGGL((packed_bf16_kernel<BM, BN, BK, MODE, NW>), dim3(tiles_m * tiles_n),
-                     dim3(64 * NW), 0, s, g.C, g.ldc, (const uint16_t*)g.Ap,
+  hipLaunchKernelGGL((packed_bf16_kernel<BM, BN, BK, MODE>), dim3(tiles_m * tiles_n),
+                     dim3(kThreads), 0, s, g.C, g.ldc, (const uint16_t*)g.Ap,
                      (const uint16_t*)g.Bp, g.M, g.N, g.Kp, g.Mp, g.Np, tiles_m, tiles_n);
   return check_launch("packed_bf16_kernel");
 }
