@@ -601,9 +601,10 @@ def layer_leg(rise, torch, dev, stream):
                      "frac_bf16_peak": round(tf / PEAK_BF16, 3), "gbps": round(gbs, 1),
                      "frac_hbm_peak": round(gbs / PEAK_HBM, 3)}
     res["bound_ms_forward"] = round(max(fl / (PEAK_BF16 * 1e9), 2 * act / (PEAK_HBM * 1e6)), 3)
-    res["strategy"] = {"forward": "bf16 MFMA, weights in registers, halo tiles of two rows per wave",
+    res["strategy"] = {"forward": "bf16 MFMA, weights in registers, strips of 64 columns walked a row at "
+                                  "a time, an input row feeding three output rows",
                        "dIn": "the forward kernel with rotated, channel-transposed weights",
-                       "dW": "per-workgroup partial sums over pixel tiles + ordered reduction"}
+                       "dW": "per-workgroup partial sums over strips + ordered reduction"}
     return res
 
 

@@ -301,8 +301,8 @@ rise_status rise_stencil2d(float* out, int64_t ld_out, const float* in, int64_t 
  *      in registers with a halo of fuse*(k-1)/2 (square 3x3 and 5x5 windows
  *      only; others return RISE_ERR_UNSUPPORTED);
  *   0  the library default: 4 for 3x3 windows, 1 otherwise (for 5x5 the
- *      fused steps are bound by the FMA rate and gain nothing over one launch
- *      per step).
+ *      halo that fused steps compute again costs more than they save on images
+ *      below about 3000^2; on larger ones 2 is the faster choice).
  * The last launch runs the remaining steps.  All schedules give identical
  * results (each output is the same FP32 sum in the same order).
  * Workspace: rise_stencil2d_iterate_workspace(H, W, kh, kw, steps, fuse) bytes,

@@ -186,9 +186,11 @@ __device__ __forceinline__ void iterate_segment(float* __restrict__ out, int64_t
   for (int i = 0; i < ticks; i += PF) ticks_from(ticks_from, std::integral_constant<int, 0>{}, i);
 }
 
-// Bound by the FMAs (T K^2 per column and row of a strip, with HALO columns and 2 R T
-// rows of every strip and segment computed again) where there are several waves to a
-// SIMD, and by a wave's own latency on small images.  It replaced LDS tiles of 32
+// Bound by vector issue where there are several waves to a SIMD, and by a wave's own
+// latency on small images: HALO columns and 2 R T rows of every strip and segment are
+// computed again (4096^2, 5 x 5, four steps: 26.2 M FMAs needed, 44.4 M vector
+// instructions issued, which fill 69 % of the launch; the three waves of a SIMD wait out
+// their loads and shifts in the rest).  It replaced LDS tiles of 32
 // rows by 128 columns, which read 96 bytes of LDS per eight outputs and step: 4096^2,
 // 3 x 3, four steps a launch 18.5 -> 9.9 us per step, 256^2 3.9 -> 1.9; 5 x 5 35.5 ->
 // 24 and 5.0 -> 4.0.
@@ -262,8 +264,10 @@ bool stencil_iterate_fusable(int kh, int kw) { return kh == kw && (kh == 3 || kh
 int stencil_iterate_max_fuse() { return kItTMax; }
 
 // Measured at 4096^2: for 3x3 four fused steps beat one launch per step (9.9 against
-// 21 us per step); for 5x5, bound by the FMA rate, they are even (24 and 24.5 us),
-// and below 1500^2 the single steps win (1000^2: 5.5 and 4.9 us).
+// 20 us per step).  For 5x5, whose recomputed halo costs up to half as much again as the
+// steps, one launch per step and two, three and four steps fused take 94, 69, 70 and 71 us
+// per step at 8192^2, past the last-level cache, 24.8, 21.9, 22.9 and 23.9 at 4096^2, 7.9,
+// 8.4, 8.0 and 9.4 at 2047 x 1531, and 4.8, 5.3, 5.2 and 5.4 at 1000^2.
 int stencil_iterate_default_fuse(int kh, int kw) {
   return kh == 3 && kw == 3 ? kItTMax : 1;
 }

@@ -1,7 +1,8 @@
 // Tile-level device functions shared by the one-problem kernels and the
 // persistent batched kernel.  Each function computes one output tile with the
-// whole 256-thread workgroup and takes its LDS through a pointer, so a kernel
-// that runs several kinds of tiles can overlay them in one buffer.
+// whole workgroup (256 threads for a stencil tile, RingCfg::THREADS for a GEMM tile)
+// and takes its LDS through a pointer, so a kernel that runs several kinds of tiles
+// can overlay them in one buffer.
 #pragma once
 
 #include <type_traits>
