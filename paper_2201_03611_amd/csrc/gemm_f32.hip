@@ -179,14 +179,16 @@ rise_status launch_split(const GemmF32Args& a, hipStream_t s) {
 // 4096, the others at 1024^3, 1000 x 1531 x 777 and 1500 x 300 x 6000; the matrix
 // cores alone need 13.6 at 2.3 GHz), where rows are whole aligned chunks and where
 // they are not (what differs is how the two kinds of 32 x 32 tiles compare with the
-// rest: the split kernel's loads keep their width).  0: only where asked for.
+// rest, as the split kernel's loads keep their width, and 256 x 128 of a longer K, whose
+// 4-byte copies are then more of its time: 5189 x 5376 x 1940 916 us, 64 x 64 860).  0: only
+// where asked for.
 struct TileCost {
   rise_tile t;
   double ns, ns_values;
 };
 const TileCost kTiles[] = {{{128, 128, 32}, 0, 0},        {{128, 64, 32}, 16.0, 16.0},
                            {{64, 128, 32}, 16.0, 16.0},   {{64, 64, 32}, 16.5, 16.5},
-                           {{256, 128, 16}, 14.6, 14.6},  {{64, 96, 32}, 17.0, 17.0},
+                           {{256, 128, 16}, 14.6, 15.4},  {{64, 96, 32}, 17.0, 17.0},
                            {{96, 64, 32}, 16.5, 16.5},    {{64, 32, 64}, 19.5, 19.5},
                            {{32, 64, 64}, 19.5, 19.5},    {{32, 32, 32}, 36.0, 26.0},
                            {{32, 32, 128}, 18.5, 22.0}};
@@ -240,7 +242,8 @@ rise_tile gemm_f32_best_tile(int M, int N, int K, bool chunks) {
     if (c.t.bm == 32 && c.t.bn == 32 && (c.t.bk == 128) != (K > split_max_k)) continue;
     const bool split = c.t.bm == 32 && c.t.bn == 32 && c.t.bk == 32;
     const int64_t tiles = (((int64_t)M + c.t.bm - 1) / c.t.bm) * (((int64_t)N + c.t.bn - 1) / c.t.bn);
-    const double ns = chunks || (split && tiles > 2048) ? c.ns : c.ns_values;
+    const bool as_chunks = chunks || (split && tiles > 2048) || (c.t.bm == 256 && K <= 512);
+    const double ns = as_chunks ? c.ns : c.ns_values;
     const double k = (double)K + 128 + (split ? 0 : 4 * c.t.bk);
     double rounds = 0.85 * (double)((tiles + 255) / 256) + 0.15 * (double)tiles / 256;
     if (c.t.bm == 256 && chunks)

@@ -60,7 +60,7 @@ def violations(lines):
     return copies, bad
 
 
-def test_checker_sees_what_is_missing():
+def test_missing_wait_states_are_seen():
     copy = "global_load_lds_dwordx4 v1, s[2:3]"
     assert violations(["s_mov_b32 m0, s5", copy])[1]
     assert not violations(["s_mov_b32 m0, s5", "s_nop 0", copy])[1]
